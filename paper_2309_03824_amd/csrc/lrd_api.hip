@@ -402,7 +402,8 @@ lrd_status linear_bwd_impl(const void* dY, const void* X, const void* H, const v
         LRD_TRY(run_matop(wu, st));
     }
     if (train_v) LRD_TRY(run_matop(wv, st));
-    if (dbias) LRD_TRY(column_sums(dY, dbias, T, out, dt == LRD_BF16, st));
+    // (the products are done with the workspace by then: its first cv.used bytes hold the partial sums)
+    if (dbias) LRD_TRY(column_sums(dY, dbias, T, out, dt == LRD_BF16, ws, cv.used, st));
     return LRD_OK;
 }
 }  // namespace
@@ -650,7 +651,7 @@ lrd_status lrd_linear_group_bwd(const void* dY, const void* X, const void* H, co
     }
     if (dbias)
         for (int32_t g = 0; g < groups; ++g)
-            LRD_TRY(column_sums(at(dY, (int64_t)g * T * out, dt), dbias + (int64_t)g * out, T, out, dt == LRD_BF16, st));
+            LRD_TRY(column_sums(at(dY, (int64_t)g * T * out, dt), dbias + (int64_t)g * out, T, out, dt == LRD_BF16, ws, cv.used, st));
     return LRD_OK;
 }
 

@@ -110,7 +110,8 @@ void note_kernel(const char* name);
 // Elementwise / reductions.
 hipError_t gelu_fwd(const void* Z, void* A, int64_t n, bool bf16, hipStream_t st);
 hipError_t gelu_bwd(const void* dA, const void* Z, void* dZ, int64_t n, bool bf16, hipStream_t st);
-hipError_t column_sums(const void* dY, float* out, int64_t T, int64_t n, bool bf16, hipStream_t st);
+// out[c] = sum over t of dY[t][c]; `scratch` (optional) holds partial rows, fewer of them if it is small.
+hipError_t column_sums(const void* dY, float* out, int64_t T, int64_t n, bool bf16, void* scratch, size_t scratch_bytes, hipStream_t st);
 // Zero-padding / cropping copy of a row-major matrix (elem_bytes 2 or 4).
 hipError_t copy2d(const void* src, int64_t ld_src, int64_t rows_src, int64_t cols_src, void* dst, int64_t ld_dst,
                   int64_t rows_dst, int64_t cols_dst, int elem_bytes, hipStream_t st);
