@@ -172,7 +172,8 @@ hipError_t run_matop(const MatOp& op_in, hipStream_t st)
     else if (mfma_gemm2_supported(op)) e = mfma_gemm2(op, st);
     else {
         epilogue_done = op.epilogue == EPI_NONE;
-        if (mfma_matop_supported(op)) e = mfma_matop(op, st);
+        if (f32_gemm_supported(op)) e = f32_gemm(op, st);
+        else if (mfma_matop_supported(op)) e = mfma_matop(op, st);
         else e = generic_matop(op, st);
     }
     if (e == hipSuccess && op.sgd && !op.sgd->done) {
