@@ -128,13 +128,35 @@ __device__ __forceinline__ void sgd_apply4(const SgdArgs& a, int64_t i, f32x4 g)
     }
 }
 
+// Four consecutive columns of a padded gradient to their place in the cropped one (CropFuse).
+struct CropArgs { float* dst; int rows, inner, inner_keep; };
+__device__ __forceinline__ void crop_store4(const CropArgs& c, int64_t i, int64_t N, f32x4 v)
+{
+    typedef f32x4 f32x4u __attribute__((aligned(4)));
+    const int m = (int)(i / N), n = (int)(i - (int64_t)m * N);
+    const int b = n / c.inner, q = n - b * c.inner, blocks = (int)(N / c.inner);
+    if (m >= c.rows) return;
+    float* at = c.dst + ((int64_t)m * blocks + b) * c.inner_keep + q;
+    if (q + 4 <= c.inner_keep) {
+        *reinterpret_cast<f32x4u*>(at) = v;
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (q + e < c.inner_keep) at[e] = v[e];
+    }
+}
+
+enum { SUM_STORE = 0, SUM_SGD = 1, SUM_CROP = 2 };
+
 // C[m][n] = sum_z partial[z][m][n], slices added in ascending z so the result does not depend on
 // scheduling.  VEC consecutive columns per thread (N and ldc are multiples of VEC); OutT is the
 // result type (fp32 weight gradients, or bf16 activations rounded once from the fp32 sum).
-// With SGD (VEC == 4, fp32, ldc == N) the sum feeds the optimizer step and is not stored.
-template <int VEC, class OutT, bool SGD = false>
+// With SUM_SGD (VEC == 4, fp32, ldc == N) the sum feeds the optimizer step and is not stored, with SUM_CROP
+// (VEC == 4, fp32) it goes to its place in a smaller matrix.
+template <int VEC, class OutT, int TO = SUM_STORE>
 __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __restrict__ partial, OutT* __restrict__ C,
-                                                              int64_t ldc, int64_t M, int64_t N, int splits, SgdArgs sgd = SgdArgs{})
+                                                              int64_t ldc, int64_t M, int64_t N, int splits, SgdArgs sgd = SgdArgs{},
+                                                              CropArgs crop = CropArgs{})
 {
     const int64_t total = M * N;
     const int64_t groups = total / VEC;
@@ -163,7 +185,8 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __res
             *reinterpret_cast<u32x4*>(out) = pk;
         } else if constexpr (VEC == 4 && sizeof(OutT) == 4) {
             f32x4 v = {s[0], s[1], s[2], s[3]};
-            if constexpr (SGD) sgd_apply4(sgd, i, v);
+            if constexpr (TO == SUM_SGD) sgd_apply4(sgd, i, v);
+            else if constexpr (TO == SUM_CROP) crop_store4(crop, i, N, v);
             else *reinterpret_cast<f32x4*>(out) = v;
         } else {
 #pragma unroll
@@ -177,10 +200,10 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __res
 // the slices one after the other, so LANES threads share a group of 4 outputs, thread l adds slices
 // l, l + LANES, ... in ascending order and the LANES sums are combined by a pairwise tree.  Still a
 // fixed order.
-template <int LANES, bool SGD = false>
+template <int LANES, int TO = SUM_STORE>
 __global__ __launch_bounds__(256) void reduce_partials_wide_kernel(const float* __restrict__ partial, float* __restrict__ C,
                                                                    int64_t ldc, int64_t M, int64_t N, int splits,
-                                                                   SgdArgs sgd = SgdArgs{})
+                                                                   SgdArgs sgd = SgdArgs{}, CropArgs crop = CropArgs{})
 {
     constexpr int GROUPS = 256 / LANES;       // groups of 4 outputs per block
     __shared__ f32x4 part[LANES][GROUPS + 1];
@@ -201,23 +224,80 @@ __global__ __launch_bounds__(256) void reduce_partials_wide_kernel(const float* 
     if (l == 0 && g < groups) {
         const f32x4 t = part[0][gl];
         const int64_t i = g * 4;
-        if constexpr (SGD) sgd_apply4(sgd, i, t);
+        if constexpr (TO == SUM_SGD) sgd_apply4(sgd, i, t);
+        else if constexpr (TO == SUM_CROP) crop_store4(crop, i, N, t);
         else *reinterpret_cast<f32x4*>(C + (i / N) * ldc + (i % N)) = t;
     }
 }
 
-// dst[i][j] (rows_d x cols_d, leading dimension ldd) = src[i][j] where it exists (i < rows_s, j < cols_s), else 0.
+// Zero-padding / cropping copies between dense row-major matrices, up to COPY_JOBS of them in one launch (the
+// factors, intermediates and gradients of a raw rank): dst[i][j] = src[i][j] where that exists, else 0.
+// Each is a few hundred KB to a few MB: a launch costs more than the bytes of one, so those of a pass share a launch,
+// and the loads are 16 bytes wide wherever the row starts (2-byte loads, 16 bytes apart between lanes, took a clock
+// per lane).  Forward + backward of a 4100 x 1024 x 4096 layer at rank 257: 39 us of copies as eight launches of a
+// kernel with one element and one 64-bit division per thread, 16 us as three of this one, the gradients being
+// cropped where their K-slices are summed; the 512-channel 7 x 7 convolution at rank 309: 54 against 20 us.
+// A thread writes 16 bytes of the dense destination and finds the row of its first element by one 32-bit division.
+struct CopyArgs {
+    struct Job { const void* src; void* dst; uint32_t rows_s, cols_s, cols_d, total; int elem_bytes; } job[COPY_JOBS];
+    uint32_t first_block[COPY_JOBS];
+};
 template <class T>
-__global__ __launch_bounds__(256) void copy2d_kernel(const T* __restrict__ src, int64_t lds_, int64_t rows_s, int64_t cols_s,
-                                                     T* __restrict__ dst, int64_t ldd, int64_t rows_d, int64_t cols_d)
+__device__ __forceinline__ void copy_chunk(const CopyArgs::Job& c, uint32_t e)
 {
-    const int64_t total = rows_d * cols_d;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += stride) {
-        int64_t i = e / cols_d, j = e - i * cols_d;
-        T v = (T)0.f;
-        if (i < rows_s && j < cols_s) v = src[i * lds_ + j];
-        dst[i * ldd + j] = v;
+    constexpr uint32_t V = 16 / sizeof(T);
+    typedef T TV __attribute__((ext_vector_type(V)));
+    typedef TV TU __attribute__((aligned(sizeof(T))));          // a vector at any element
+    const T* src = reinterpret_cast<const T*>(c.src);
+    T* dst = reinterpret_cast<T*>(c.dst);
+    const uint32_t i = e / c.cols_d, j = e - i * c.cols_d, left = c.cols_d - j, total_s = c.rows_s * c.cols_s;
+    const uint32_t from = i * c.cols_s + j;                     // the first element; those past the row end (from element
+    const uint32_t from2 = from + c.cols_s - c.cols_d;          // `left` on) lie as if the next row began there
+    const bool wraps = c.cols_d % V != 0;
+    TV v;
+    if (c.cols_d >= V && (!wraps || c.cols_s >= c.cols_d) && (wraps ? from2 : from) + V <= total_s) {
+        v = *reinterpret_cast<const TU*>(src + from);
+        if (wraps) {
+            const TV w = *reinterpret_cast<const TU*>(src + from2);
+#pragma unroll
+            for (uint32_t q = 0; q < V; ++q) v[q] = q < left ? v[q] : w[q];
+        } else if (c.cols_s < c.cols_d) {
+#pragma unroll
+            for (uint32_t q = 0; q < V; ++q) v[q] = j + q < c.cols_s ? v[q] : (T)0.f;
+        }
+    } else {
+        // the last row or two, and rows of less than 16 bytes
+        uint32_t ii = i, jj = j;
+#pragma unroll
+        for (uint32_t q = 0; q < V; ++q) {
+            v[q] = ii < c.rows_s && jj < c.cols_s ? src[ii * c.cols_s + jj] : (T)0.f;
+            if (++jj == c.cols_d) { jj = 0; ++ii; }
+        }
+    }
+    if (e + V <= c.total) {
+        *reinterpret_cast<TV*>(dst + e) = v;
+    } else {
+#pragma unroll
+        for (uint32_t q = 0; q < V; ++q)
+            if (e + q < c.total) dst[e + q] = v[q];
+    }
+}
+constexpr uint32_t COPY_RUN = 2;      // 16-byte groups per thread: a block is 8 KB of one destination
+__global__ __launch_bounds__(256) void copy2d_kernel(CopyArgs a)
+{
+    int k = 0;
+#pragma unroll
+    for (int q = 1; q < COPY_JOBS; ++q) k += blockIdx.x >= a.first_block[q];
+    const CopyArgs::Job c = a.job[k];
+    const uint32_t g0 = (blockIdx.x - a.first_block[k]) * (256 * COPY_RUN) + threadIdx.x;
+#pragma unroll
+    for (uint32_t q = 0; q < COPY_RUN; ++q) {
+        const uint32_t g = g0 + q * 256;
+        if (c.elem_bytes == 2) {
+            if (g * 8 < c.total) copy_chunk<bf16_t>(c, g * 8);
+        } else {
+            if (g * 4 < c.total) copy_chunk<float>(c, g * 4);
+        }
     }
 }
 
@@ -303,18 +383,37 @@ hipError_t column_sums(const void* dY, float* out, int64_t T, int64_t n, bool bf
     return reduce_partials(partial, out, false, n, 1, n, (int)rb, st);
 }
 
-hipError_t copy2d(const void* src, int64_t ld_src, int64_t rows_src, int64_t cols_src, void* dst, int64_t ld_dst,
-                  int64_t rows_dst, int64_t cols_dst, int elem_bytes, hipStream_t st)
+hipError_t copy2d(const CopyJob* jobs, int n, hipStream_t st)
 {
-    if (rows_dst <= 0 || cols_dst <= 0) return hipSuccess;
-    dim3 grid(blocks_for(rows_dst * cols_dst));
-    if (elem_bytes == 2)
-        hipLaunchKernelGGL(copy2d_kernel<bf16_t>, grid, dim3(256), 0, st, (const bf16_t*)src, ld_src, rows_src, cols_src,
-                           (bf16_t*)dst, ld_dst, rows_dst, cols_dst);
-    else
-        hipLaunchKernelGGL(copy2d_kernel<float>, grid, dim3(256), 0, st, (const float*)src, ld_src, rows_src, cols_src,
-                           (float*)dst, ld_dst, rows_dst, cols_dst);
-    return hipGetLastError();
+    CopyArgs a;
+    int used = 0;
+    uint32_t blocks = 0;
+    auto launch = [&] {
+        if (used == 0) return hipSuccess;
+        for (int i = used; i < COPY_JOBS; ++i) a.first_block[i] = 0xffffffffu;
+        hipLaunchKernelGGL(copy2d_kernel, dim3(blocks), dim3(256), 0, st, a);
+        used = 0;
+        blocks = 0;
+        return hipGetLastError();
+    };
+    for (int i = 0; i < n; ++i) {
+        const CopyJob& j = jobs[i];
+        if (j.cols_d <= 0) continue;
+        // the kernel counts elements in 32 bits: longer matrices go in runs of rows (whole 16-byte groups each)
+        const int64_t run = std::max<int64_t>(8, ((int64_t(1) << 31) / std::max(j.cols_d, j.cols_s)) & ~int64_t(7));
+        for (int64_t r0 = 0; r0 < j.rows_d; r0 += run) {
+            if (used == COPY_JOBS) {
+                const hipError_t e = launch();
+                if (e != hipSuccess) return e;
+            }
+            const int64_t rows_d = std::min(run, j.rows_d - r0), rows_s = std::max<int64_t>(0, std::min(run, j.rows_s - r0));
+            a.job[used] = {(const char*)j.src + r0 * j.cols_s * j.elem_bytes, (char*)j.dst + r0 * j.cols_d * j.elem_bytes, (uint32_t)rows_s,
+                           (uint32_t)j.cols_s, (uint32_t)j.cols_d, (uint32_t)(rows_d * j.cols_d), j.elem_bytes};
+            a.first_block[used++] = blocks;
+            blocks += (uint32_t)ceil_div(rows_d * j.cols_d, (int64_t)COPY_RUN * 256 * 16 / j.elem_bytes);
+        }
+    }
+    return launch();
 }
 
 hipError_t flip_conv_weights(const void* w, void* wt, int O, int I, int k, hipStream_t st)
@@ -334,7 +433,7 @@ hipError_t sgd_step(float* w, float* m, const float* g, void* copy, bool copy_bf
 }
 
 hipError_t reduce_partials(const float* partial, void* C, bool c_bf16, int64_t ldc, int64_t M, int64_t N, int splits,
-                           hipStream_t st, const SgdFuse* sgd)
+                           hipStream_t st, const SgdFuse* sgd, const CropFuse* crop)
 {
     if (M <= 0 || N <= 0) return hipSuccess;
     auto al16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
@@ -354,15 +453,29 @@ hipError_t reduce_partials(const float* partial, void* C, bool c_bf16, int64_t l
     if (sgd && !sgd->done && vec4 && ldc == N && al16(sgd->w) && al16(sgd->m) && (reinterpret_cast<uintptr_t>(sgd->copy) & 15u) == 0) {
         const SgdArgs a{sgd->w, sgd->m, sgd->copy, sgd->copy_bf16 ? 1 : 0, sgd->lr, sgd->mu, sgd->wd};
         if (wide64)
-            hipLaunchKernelGGL((reduce_partials_wide_kernel<64, true>), dim3((unsigned)ceil_div(M * N / 4, 4)), dim3(256), 0, st,
+            hipLaunchKernelGGL((reduce_partials_wide_kernel<64, SUM_SGD>), dim3((unsigned)ceil_div(M * N / 4, 4)), dim3(256), 0, st,
                                partial, (float*)C, ldc, M, N, splits, a);
         else if (wide16)
-            hipLaunchKernelGGL((reduce_partials_wide_kernel<16, true>), dim3((unsigned)ceil_div(M * N / 4, 16)), dim3(256), 0, st,
+            hipLaunchKernelGGL((reduce_partials_wide_kernel<16, SUM_SGD>), dim3((unsigned)ceil_div(M * N / 4, 16)), dim3(256), 0, st,
                                partial, (float*)C, ldc, M, N, splits, a);
         else
-            hipLaunchKernelGGL((reduce_partials_kernel<4, float, true>), dim3(blocks_for(M * N / 4)), dim3(256), 0, st, partial,
+            hipLaunchKernelGGL((reduce_partials_kernel<4, float, SUM_SGD>), dim3(blocks_for(M * N / 4)), dim3(256), 0, st, partial,
                                (float*)C, ldc, M, N, splits, a);
         sgd->done = true;
+        return hipGetLastError();
+    }
+    if (crop && vec4 && !crop->done && M < (int64_t(1) << 31) && N < (int64_t(1) << 31) && N % crop->inner == 0 && crop->inner % 4 == 0) {
+        const CropArgs a{crop->dst, (int)crop->rows, (int)crop->inner, (int)crop->inner_keep};
+        if (wide64)
+            hipLaunchKernelGGL((reduce_partials_wide_kernel<64, SUM_CROP>), dim3((unsigned)ceil_div(M * N / 4, 4)), dim3(256), 0, st,
+                               partial, (float*)C, ldc, M, N, splits, SgdArgs{}, a);
+        else if (wide16)
+            hipLaunchKernelGGL((reduce_partials_wide_kernel<16, SUM_CROP>), dim3((unsigned)ceil_div(M * N / 4, 16)), dim3(256), 0, st,
+                               partial, (float*)C, ldc, M, N, splits, SgdArgs{}, a);
+        else
+            hipLaunchKernelGGL((reduce_partials_kernel<4, float, SUM_CROP>), dim3(blocks_for(M * N / 4)), dim3(256), 0, st, partial,
+                               (float*)C, ldc, M, N, splits, SgdArgs{}, a);
+        crop->done = true;
         return hipGetLastError();
     }
     if (wide64)

@@ -239,12 +239,13 @@ lrd_status lrd_linear_fwd_act(const void* X, const void* V, const void* U, const
         void* Vp = cv.take((size_t)r8 * in * 2);
         void* Hp = cv.take((size_t)T * r8 * 2);
         if (!cv.ok) return LRD_ERR_WORKSPACE;
-        LRD_TRY(copy2d(U, r, out, r, Up, r8, out, r8, 2, st));
-        LRD_TRY(copy2d(V, in, r, in, Vp, in, r8, in, 2, st));
+        const CopyJob pads[] = {{U, out, r, Up, out, r8, 2}, {V, r, in, Vp, r8, in, 2}};
+        LRD_TRY(copy2d(pads, 2, st));
         lrd_status rc = lrd_linear_fwd_act(X, Vp, Up, bias, Y, Y_act, Hp, act, T, in, out, r8, dt, (char*)ws + cv.used,
                                            ws_bytes - cv.used, hip_stream);
         if (rc != LRD_OK) return rc;
-        if (H_save) LRD_TRY(copy2d(Hp, r8, T, r, H_save, r, T, r, 2, st));
+        const CopyJob crop = {Hp, T, r8, H_save, T, r, 2};
+        if (H_save) LRD_TRY(copy2d(&crop, 1, st));
         return LRD_OK;
     }
 
@@ -300,7 +301,8 @@ namespace {
 lrd_status linear_bwd_impl(const void* dY, const void* X, const void* H, const void* V, const void* U, void* dX, float* dV,
                            float* dU, float* dbias, uint32_t freeze_mask, const void* Z_in, int32_t act, int64_t T,
                            int64_t in, int64_t out, int64_t r, lrd_dtype dt, void* ws, size_t ws_bytes, void* hip_stream,
-                           const SgdFuse* sgd_u, const SgdFuse* sgd_v)
+                           const SgdFuse* sgd_u, const SgdFuse* sgd_v, const CropFuse* crop_u = nullptr,
+                           const CropFuse* crop_v = nullptr)
 {
     if (!dtype_ok(dt) || !linear_dims_ok(T, in, out, r) || !dY || !V || !U) return LRD_ERR_INVALID_ARG;
     if ((act != LRD_ACT_NONE && act != LRD_ACT_GELU) || (act == LRD_ACT_GELU && dX && !Z_in)) return LRD_ERR_INVALID_ARG;
@@ -323,16 +325,22 @@ lrd_status linear_bwd_impl(const void* dY, const void* X, const void* H, const v
         float* dUp = (float*)cvp.take((size_t)out * r8 * 4);
         float* dVp = (float*)cvp.take((size_t)r8 * in * 4);
         if (!cvp.ok) return LRD_ERR_WORKSPACE;
-        LRD_TRY(copy2d(U, r, out, r, Up, r8, out, r8, 2, st));
-        LRD_TRY(copy2d(V, in, r, in, Vp, in, r8, in, 2, st));
         const bool have_h = H && train_u;
-        if (have_h) LRD_TRY(copy2d(H, r, T, r, Hp, r8, T, r8, 2, st));
+        const CopyJob pads[] = {{U, out, r, Up, out, r8, 2}, {V, r, in, Vp, r8, in, 2}, {H, T, r, Hp, T, r8, 2}};
+        LRD_TRY(copy2d(pads, have_h ? 3 : 2, st));
         if (sgd_u || sgd_v) return LRD_ERR_INVALID_ARG;
-        lrd_status rc = lrd_linear_bwd_act(dY, X, have_h ? Hp : nullptr, Vp, Up, dX, dVp, dUp, dbias, freeze_mask, Z_in, act, T,
-                                           in, out, r8, dt, (char*)ws + cvp.used, ws_bytes - cvp.used, hip_stream);
+        // the padded gradients are cropped by the sum over their K-slices, or copied where they are not sliced
+        CropFuse cu, cw;
+        cu.dst = dU; cu.rows = out; cu.inner = r8; cu.inner_keep = r;
+        cw.dst = dV; cw.rows = r; cw.inner = in; cw.inner_keep = in;
+        lrd_status rc = linear_bwd_impl(dY, X, have_h ? Hp : nullptr, Vp, Up, dX, dVp, dUp, dbias, freeze_mask, Z_in, act, T, in, out, r8, dt,
+                                        (char*)ws + cvp.used, ws_bytes - cvp.used, hip_stream, nullptr, nullptr, &cu, &cw);
         if (rc != LRD_OK) return rc;
-        if (train_u) LRD_TRY(copy2d(dUp, r8, out, r, dU, r, out, r, 4, st));
-        if (train_v) LRD_TRY(copy2d(dVp, in, r, in, dV, in, r, in, 4, st));
+        CopyJob crops[2];
+        int n = 0;
+        if (train_u && !cu.done) crops[n++] = {dUp, out, r8, dU, out, r, 4};
+        if (train_v && !cw.done) crops[n++] = {dVp, r, in, dV, r, in, 4};
+        LRD_TRY(copy2d(crops, n, st));
         return LRD_OK;
     }
     Carver cv(ws, ws_bytes);
@@ -349,12 +357,14 @@ lrd_status linear_bwd_impl(const void* dY, const void* X, const void* H, const v
         wu = tn(dY, out, H ? H : Hre, r, dU, r, out, r, T, dt);
         wu.role = LRD_ROLE_WGRAD_U;
         wu.sgd = sgd_u;
+        wu.crop = crop_u;
         share_splits(wu, region, dt, SPLIT_WGRAD);
     }
     if (train_v) {
         wv = tn(dH, r, X, in, dV, in, r, in, T, dt);
         wv.role = LRD_ROLE_WGRAD_V;
         wv.sgd = sgd_v;
+        wv.crop = crop_v;
         share_splits(wv, region, dt, SPLIT_WGRAD);
     }
     if (!cv.ok) return LRD_ERR_WORKSPACE;
@@ -906,14 +916,16 @@ lrd_status lrd_tucker_conv_fwd(const void* X, const void* P1, const void* G, con
         void* Ap = cp.take(t.a);
         void* Bp = cp.take(t.b);
         if (!cp.ok) return LRD_ERR_WORKSPACE;
-        LRD_TRY(copy2d(P1, g->C, r1, g->C, P1p, g->C, q1, g->C, 2, st));
-        LRD_TRY(copy2d(G, r1, r2 * kk, r1, Gp, q1, q2 * kk, q1, 2, st));
-        LRD_TRY(copy2d(P2, r2, g->S, r2, P2p, q2, g->S, q2, 2, st));
+        const CopyJob pads[] = {{P1, r1, g->C, P1p, q1, g->C, 2}, {G, r2 * kk, r1, Gp, q2 * kk, q1, 2}, {P2, g->S, r2, P2p, g->S, q2, 2}};
+        LRD_TRY(copy2d(pads, 3, st));
         lrd_status rc = lrd_tucker_conv_fwd(X, P1p, Gp, P2p, Y, Ap, Bp, &t.gp, dt, (char*)ws + cp.used, ws_bytes - cp.used,
                                             hip_stream);
         if (rc != LRD_OK) return rc;
-        if (A_save) LRD_TRY(copy2d(Ap, q1, pin, r1, A_save, r1, pin, r1, 2, st));
-        if (B_save) LRD_TRY(copy2d(Bp, q2, pout, r2, B_save, r2, pout, r2, 2, st));
+        CopyJob crops[2];
+        int n = 0;
+        if (A_save) crops[n++] = {Ap, pin, q1, A_save, pin, r1, 2};
+        if (B_save) crops[n++] = {Bp, pout, q2, B_save, pout, r2, 2};
+        LRD_TRY(copy2d(crops, n, st));
         return LRD_OK;
     }
     Carver cv(ws, ws_bytes);
@@ -930,11 +942,11 @@ lrd_status lrd_tucker_conv_fwd(const void* X, const void* P1, const void* G, con
     return LRD_OK;
 }
 
-lrd_status lrd_tucker_conv_bwd(const void* dY, const void* X, const void* A, const void* B,
-                               const void* P1, const void* G, const void* P2, void* dX,
-                               float* dP1, float* dG, float* dP2, uint32_t freeze_mask,
-                               const lrd_conv_geom* g, lrd_dtype dt, void* ws, size_t ws_bytes,
-                               void* hip_stream)
+namespace {
+// lrd_tucker_conv_bwd; `crop` (for dP1, dG, dP2) is given for the padded gradients of raw ranks.
+lrd_status tucker_bwd_impl(const void* dY, const void* X, const void* A, const void* B, const void* P1, const void* G, const void* P2,
+                           void* dX, float* dP1, float* dG, float* dP2, uint32_t freeze_mask, const lrd_conv_geom* g, lrd_dtype dt,
+                           void* ws, size_t ws_bytes, void* hip_stream, const CropFuse* crop)
 {
     if (!dtype_ok(dt) || !geom_ok(g, true) || !dY || !P1 || !G || !P2) return LRD_ERR_INVALID_ARG;
     if (freeze_mask & ~uint32_t(LRD_FREEZE_L0 | LRD_FREEZE_L1 | LRD_FREEZE_L2)) return LRD_ERR_INVALID_ARG;
@@ -965,19 +977,25 @@ lrd_status lrd_tucker_conv_bwd(const void* dY, const void* X, const void* A, con
         float* dGp = (float*)cp.take(t.dg);
         float* dP2p = (float*)cp.take(t.dp2);
         if (!cp.ok) return LRD_ERR_WORKSPACE;
-        LRD_TRY(copy2d(P1, C, r1, C, P1p, C, q1, C, 2, st));
-        LRD_TRY(copy2d(G, r1, r2 * kk, r1, Gp, q1, q2 * kk, q1, 2, st));
-        LRD_TRY(copy2d(P2, r2, S, r2, P2p, q2, S, q2, 2, st));
         const bool have_a = A && need_A, have_b = B && t2;
-        if (have_a) LRD_TRY(copy2d(A, r1, pin, r1, Ap, q1, pin, q1, 2, st));
-        if (have_b) LRD_TRY(copy2d(B, r2, pout, r2, Bp, q2, pout, q2, 2, st));
-        lrd_status rc = lrd_tucker_conv_bwd(dY, X, have_a ? Ap : nullptr, have_b ? Bp : nullptr, P1p, Gp, P2p, dX, dP1p, dGp,
-                                            dP2p, freeze_mask, &t.gp, dt, (char*)ws + cp.used, ws_bytes - cp.used,
-                                            hip_stream);
+        CopyJob pads[COPY_JOBS] = {{P1, r1, C, P1p, q1, C, 2}, {G, r2 * kk, r1, Gp, q2 * kk, q1, 2}, {P2, S, r2, P2p, S, q2, 2}};
+        int n = 3;
+        if (have_a) pads[n++] = {A, pin, r1, Ap, pin, q1, 2};
+        if (have_b) pads[n++] = {B, pout, r2, Bp, pout, q2, 2};
+        LRD_TRY(copy2d(pads, n, st));
+        CropFuse cr[3];
+        cr[0].dst = dP1; cr[0].rows = r1; cr[0].inner = cr[0].inner_keep = C;
+        cr[1].dst = dG; cr[1].rows = r2; cr[1].inner = q1; cr[1].inner_keep = r1;
+        cr[2].dst = dP2; cr[2].rows = S; cr[2].inner = q2; cr[2].inner_keep = r2;
+        lrd_status rc = tucker_bwd_impl(dY, X, have_a ? Ap : nullptr, have_b ? Bp : nullptr, P1p, Gp, P2p, dX, dP1p, dGp, dP2p, freeze_mask,
+                                        &t.gp, dt, (char*)ws + cp.used, ws_bytes - cp.used, hip_stream, cr);
         if (rc != LRD_OK) return rc;
-        if (t1) LRD_TRY(copy2d(dP1p, C, r1, C, dP1, C, r1, C, 4, st));
-        if (tg) LRD_TRY(copy2d(dGp, q1, r2 * kk, r1, dG, r1, r2 * kk, r1, 4, st));
-        if (t2) LRD_TRY(copy2d(dP2p, q2, S, r2, dP2, r2, S, r2, 4, st));
+        CopyJob crops[3];
+        n = 0;
+        if (t1 && !cr[0].done) crops[n++] = {dP1p, r1, C, dP1, r1, C, 4};
+        if (tg && !cr[1].done) crops[n++] = {dGp, r2 * kk, q1, dG, r2 * kk, r1, 4};
+        if (t2 && !cr[2].done) crops[n++] = {dP2p, S, q2, dP2, S, r2, 4};
+        LRD_TRY(copy2d(crops, n, st));
         return LRD_OK;
     }
     Carver cv(ws, ws_bytes);
@@ -1015,6 +1033,11 @@ lrd_status lrd_tucker_conv_bwd(const void* dY, const void* X, const void* A, con
     const size_t flip_bytes = need_dA ? conv_dgrad_flip_bytes(cs, dt == LRD_BF16) : 0;
     void* flip = flip_bytes ? cv.take(flip_bytes) : nullptr;
     if (!cv.ok) return LRD_ERR_WORKSPACE;
+    if (crop) {
+        w1.crop = crop;
+        wg.crop = crop + 1;
+        w2.crop = crop + 2;
+    }
     if (t2) splits_for(w2);
     if (tg) {
         splits_for(wg);
@@ -1044,6 +1067,14 @@ lrd_status lrd_tucker_conv_bwd(const void* dY, const void* X, const void* A, con
     if (tg) LRD_TRY(run_matop(wg, st));
     if (t1) LRD_TRY(run_matop(w1, st));
     return LRD_OK;
+}
+}  // namespace
+
+lrd_status lrd_tucker_conv_bwd(const void* dY, const void* X, const void* A, const void* B, const void* P1, const void* G, const void* P2,
+                               void* dX, float* dP1, float* dG, float* dP2, uint32_t freeze_mask, const lrd_conv_geom* g, lrd_dtype dt,
+                               void* ws, size_t ws_bytes, void* hip_stream)
+{
+    return tucker_bwd_impl(dY, X, A, B, P1, G, P2, dX, dP1, dG, dP2, freeze_mask, g, dt, ws, ws_bytes, hip_stream, nullptr);
 }
 
 // ------------------------------------------------------------------------------------ dense conv

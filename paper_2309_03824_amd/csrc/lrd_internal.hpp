@@ -27,6 +27,15 @@ struct SgdFuse {
     mutable bool done = false;
 };
 
+// Where the caller wants a padded fp32 gradient [rows x cols] cropped: its first `rows` rows, and of each of the
+// cols / inner groups of `inner` columns the first `inner_keep`, dense in `dst`.  The sum over split-K slices
+// writes it in place of the padded result and sets `done`; otherwise the caller copies.
+struct CropFuse {
+    float* dst = nullptr;
+    int64_t rows = 0, inner = 0, inner_keep = 0;
+    mutable bool done = false;
+};
+
 // One product  C[M x N] = A[M x K] . B[N x K]^T (+ bias[n]),  fp32 accumulation.
 // A(m,k) = A[m*a_sm + k*a_sk], B(n,k) = B[n*b_sn + k*b_sk] (element strides) unless a gather mode
 // replaces the addressing of one operand by a convolution's tap geometry.
@@ -60,6 +69,7 @@ struct MatOp {
     size_t scratch_bytes = 0;
     // Optional optimizer step on the finished fp32 result (a dense weight gradient, ldc == N).
     const SgdFuse* sgd = nullptr;
+    const CropFuse* crop = nullptr;
     // A batch of products of one shape (the layers of a group): product z reads A + z * a_bs,
     // B + z * b_bs, bias + z * bias_bs and writes C + z * c_bs, aux + z * aux_bs (element strides).
     int batch = 1;
@@ -114,9 +124,14 @@ hipError_t gelu_fwd(const void* Z, void* A, int64_t n, bool bf16, hipStream_t st
 hipError_t gelu_bwd(const void* dA, const void* Z, void* dZ, int64_t n, bool bf16, hipStream_t st);
 // out[c] = sum over t of dY[t][c]; `scratch` (optional) holds partial rows, fewer of them if it is small.
 hipError_t column_sums(const void* dY, float* out, int64_t T, int64_t n, bool bf16, void* scratch, size_t scratch_bytes, hipStream_t st);
-// Zero-padding / cropping copy of a row-major matrix (elem_bytes 2 or 4).
-hipError_t copy2d(const void* src, int64_t ld_src, int64_t rows_src, int64_t cols_src, void* dst, int64_t ld_dst,
-                  int64_t rows_dst, int64_t cols_dst, int elem_bytes, hipStream_t st);
+// Zero-padding / cropping copies of dense row-major matrices (16-byte-aligned bases, elem_bytes 2 or 4), one launch.
+constexpr int COPY_JOBS = 5;
+struct CopyJob {
+    const void* src; int64_t rows_s, cols_s;
+    void* dst; int64_t rows_d, cols_d;
+    int elem_bytes;
+};
+hipError_t copy2d(const CopyJob* jobs, int n, hipStream_t st);
 hipError_t sgd_step(float* w, float* m, const float* g, void* copy, bool copy_bf16, int64_t n, float lr, float mu, float wd,
                     hipStream_t st);
 // wt [I][k][k][O] (bf16) = w [O][k][k][I] with the taps reversed: see conv_dgrad_as_fwd.
@@ -126,8 +141,8 @@ hipError_t flip_conv_weights(const void* w, void* wt, int O, int I, int k, hipSt
 size_t conv_dgrad_flip_bytes(const ConvShape& cs, bool bf16);
 // C = sum over split-K slices of partial[z][M][N], ascending z; C is fp32 or (c_bf16) bf16.
 // With `sgd` (fp32 results only) the sum is used for that step instead of being stored, when the
-// layout allows (then sgd->done is set).
+// layout allows (then sgd->done is set); with `crop` it is stored cropped (then crop->done is set).
 hipError_t reduce_partials(const float* partial, void* C, bool c_bf16, int64_t ldc, int64_t M, int64_t N,
-                           int splits, hipStream_t st, const SgdFuse* sgd = nullptr);
+                           int splits, hipStream_t st, const SgdFuse* sgd = nullptr, const CropFuse* crop = nullptr);
 
 }  // namespace lrd

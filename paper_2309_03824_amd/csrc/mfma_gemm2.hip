@@ -734,7 +734,8 @@ hipError_t launch(const MatOp& op, const Operand& A, const Operand& B, hipStream
     if (e != hipSuccess) return e;
     // a batch of sliced products is summed as one matrix of batch * M rows (supported() admits only dense results)
     if (splits > 1)
-        return reduce_partials(op.partial, op.C, !op.out_f32, op.ldc, op.M * bt.batch, op.N, splits, st, op.out_f32 ? op.sgd : nullptr);
+        return reduce_partials(op.partial, op.C, !op.out_f32, op.ldc, op.M * bt.batch, op.N, splits, st, op.out_f32 ? op.sgd : nullptr,
+                               op.out_f32 ? op.crop : nullptr);
     return hipSuccess;
 }
 
