@@ -1,4 +1,5 @@
 // Engine selection for a single matrix product and the split-K policy.
+#include <algorithm>
 #include <atomic>
 #include <cstdio>
 #include <mutex>
@@ -9,23 +10,80 @@
 
 namespace lrd {
 
-// Weight-gradient products have a long K (tokens or pixels) and a small output; K is cut into
-// slices so that the launch has enough workgroups to fill 256 compute units about twice over.
-// Measured with cold operands at K = 8192 (kernel plus reduce): a 3072 x 192 gradient is fastest
-// with 128 x 128 tiles and 10 slices (480 workgroups), a 768 x 192 one with 64 x 64 tiles and
-// 12 slices (432); more slices only add partial-sum traffic.  The count depends only on the
-// shape, so workspace queries and launches agree; the kernel launcher picks the tile from the
-// resulting workgroup count.
-int choose_splits(int64_t M, int64_t N, int64_t K, bool in_bf16)
+// What a product with a long reduction costs with each output tile: rounds of workgroups over the 256 compute units
+// times the K-steps of a workgroup times the time of a step with every unit busy (microseconds, measured: 16384 x 512
+// x 4096 takes 62.5 us in 128 x 256 tiles, 75 us in 128 x 128 ones at two workgroups per unit, 82 us in 128 x 128 ones
+// at one; 8192 x 256 x 4096 24.5 us in 128 x 64 tiles, 28.4 us in 64 x 64 ones, 52 us in 128 x 256 ones; 16384 x 4096 x
+// 4096 470 us in 256 x 256 ones against 485 us in 128 x 256 ones).  Larger tiles move fewer bytes into LDS per
+// multiplication, smaller ones fill the chip when the result is small.
+namespace {
+struct StepTime { float full, one; };      // every unit at its workgroups per unit; at most one per unit
+struct TileCost { int bm, bn, per_cu; StepTime step[GEMM_COSTS]; };
+// (COST_WGRAD: 64-column tiles of a k-major operand fetch 128 bytes per row; COST_GATHER: address arithmetic with each
+// load, which 64 x 64 tiles with one wave per SIMD cannot hide: 128 x 1152 over 25088 pixels 0.47 us a step.)
+constexpr TileCost TILES[GEMM_TILES] = {
+    {256, 256, 1, {{1.84f, 1.84f}, {1.84f, 1.84f}, {1e9f, 1e9f}}},     // (no gathers)
+    {128, 256, 1, {{0.98f, 0.98f}, {1.00f, 1.00f}, {1.20f, 1.20f}}},
+    {128, 128, 1, {{0.62f, 0.62f}, {0.64f, 0.64f}, {0.75f, 0.75f}}},
+    {128, 128, 2, {{1.17f, 0.75f}, {1.20f, 0.80f}, {1.20f, 0.90f}}},
+    {64, 128, 1, {{0.390f, 0.390f}, {0.44f, 0.44f}, {0.550f, 0.550f}}},
+    {128, 64, 1, {{0.395f, 0.395f}, {0.44f, 0.44f}, {0.545f, 0.545f}}},
+    {64, 64, 2, {{0.44f, 0.24f}, {0.50f, 0.26f}, {0.65f, 0.47f}}},
+};
+inline float gemm_tile_cost(const TileCost& t, int64_t M, int64_t N, int64_t K, int64_t splits, int64_t batch, GemmCost kind)
 {
-    (void)in_bf16;
+    const int64_t wgs = ceil_div(M, t.bm) * ceil_div(N, t.bn) * splits * batch, steps = ceil_div(ceil_div(K, 64), splits);
+    return (float)ceil_div(wgs, 256 * t.per_cu) * (float)steps * (wgs <= 256 ? t.step[kind].one : t.step[kind].full);
+}
+}  // namespace
+
+GemmTile gemm_best_tile(int64_t M, int64_t N, int64_t K, int64_t splits, int64_t batch, GemmCost kind)
+{
+    int best = TILE_64x64;
+    float least = 3e38f;
+    for (int i = 0; i < GEMM_TILES; ++i) {
+        const float c = gemm_tile_cost(TILES[i], M, N, K, splits, batch, kind);
+        if (c < least) { least = c; best = i; }
+    }
+    return (GemmTile)best;
+}
+
+namespace {
+// Slices of K for a weight gradient: the count (among those that make one or two rounds of some tile) with the least
+// cost, slices costing the partial sums' way to memory and back (about 4 TB/s) and a second kernel (4 us).
+int wgrad_splits(int64_t M, int64_t N, int64_t K, int64_t batch, int64_t most, GemmCost kind)
+{
+    int64_t best = 1;
+    float least = 3e38f;
+    for (int i = 0; i < GEMM_TILES; ++i) {
+        const int64_t tiles = ceil_div(M, TILES[i].bm) * ceil_div(N, TILES[i].bn) * batch;
+        for (int64_t s : {int64_t(1), 256 / tiles, 256 * TILES[i].per_cu / tiles}) {
+            s = std::min(s, most);
+            if (s < 1) continue;
+            const float c = gemm_tile_cost(TILES[i], M, N, K, s, batch, kind) +
+                            (s > 1 ? 4.f + (float)s * (float)batch * (float)M * (float)N * 8.f / 4e6f : 0.f);
+            if (c < least) { least = c; best = s; }
+        }
+    }
+    return (int)best;
+}
+}  // namespace
+
+// Weight-gradient products have a long K (tokens or pixels) and a small output; K is cut into slices so that the
+// launch fills the chip.  The count depends only on the shape, so workspace queries and launches agree.  (3072 x 192
+// over 8192: 3 slices, 21.4 us with the sum; 10 slices of 128 x 128 tiles took 25 us; 1024 x 256 over 8192: 4 slices
+// of 64 x 64 tiles, 13.8 us, against 18.8 us in 16.)  Never more slices than the bound below, at which the scratch
+// of callers with a fixed amount of it was set.
+int choose_splits(int64_t M, int64_t N, int64_t K, bool in_bf16, bool gather)
+{
     const int64_t t128 = ceil_div(M, 128) * ceil_div(N, 128);
     const int64_t t64 = ceil_div(M, 64) * ceil_div(N, 64);
     int64_t s = t128 >= 24 ? ceil_div(480, t128) : ceil_div(432, t64);
     const int64_t by_k = K / 256;          // keep at least 256 reduction steps per slice
     if (s > by_k) s = by_k;
     if (s > 512) s = 512;
-    return s < 2 ? 1 : (int)s;
+    if (s < 2) return 1;
+    return in_bf16 ? wgrad_splits(M, N, K, 1, s, gather ? COST_GATHER : COST_WGRAD) : (int)s;
 }
 
 // Products whose result is a [tokens x r] activation (H = X.V^T, dH = dY.U) have few output tiles
@@ -45,10 +103,8 @@ int choose_splits_act(int64_t M, int64_t N, int64_t K, bool in_bf16)
     return s < 2 ? 1 : (int)s;
 }
 
-// Weight gradients of `batch` layers of one shape in one launch.  256 x 256 tiles over all members
-// already give most compute units a workgroup when there are a dozen layers; K is sliced only while
-// they do not (12 x [1024 x 256] over 8192 tokens: 203 us unsliced, 78 us in 4 slices; 36 members:
-// 213 us unsliced, 283 us in 2 slices).
+// Weight gradients of `batch` layers of one shape in one launch: the tiles of a dozen members nearly fill the chip,
+// K is sliced only where that is cheaper all the same.
 int choose_splits_batched(int64_t M, int64_t N, int64_t K, int64_t batch)
 {
     const int64_t tiles = ceil_div(M, 256) * ceil_div(N, 256) * batch;
@@ -56,7 +112,7 @@ int choose_splits_batched(int64_t M, int64_t N, int64_t K, int64_t batch)
     const int64_t by_k = K / 512;
     if (s > by_k) s = by_k;
     if (s > 64) s = 64;
-    return s < 2 ? 1 : (int)s;
+    return s < 2 ? 1 : wgrad_splits(M, N, K, batch, s, COST_WGRAD);
 }
 
 namespace {

@@ -108,9 +108,9 @@ MatOp tn(const void* A, int64_t lda, const void* B, int64_t ldb, float* C, int64
     return op;
 }
 
-size_t partial_bytes(int64_t M, int64_t N, int64_t K, lrd_dtype dt)
+size_t partial_bytes(int64_t M, int64_t N, int64_t K, lrd_dtype dt, bool gather = false)
 {
-    int s = choose_splits(M, N, K, dt == LRD_BF16);
+    int s = choose_splits(M, N, K, dt == LRD_BF16, gather);
     return s > 1 ? round256((size_t)s * (size_t)M * (size_t)N * sizeof(float)) : 0;
 }
 
@@ -143,7 +143,7 @@ void share_splits(MatOp& op, void* region, lrd_dtype dt, SplitKind kind)
 
 void attach_splits(MatOp& op, Carver& cv, lrd_dtype dt)
 {
-    int s = choose_splits(op.M, op.N, op.K, dt == LRD_BF16);
+    int s = choose_splits(op.M, op.N, op.K, dt == LRD_BF16, op.gather != GATHER_NONE);
     if (s > 1) {
         op.partial = (float*)cv.take((size_t)s * (size_t)op.M * (size_t)op.N * sizeof(float));
         op.splits = op.partial ? s : 1;
@@ -886,7 +886,7 @@ size_t lrd_tucker_conv_workspace_bytes(const lrd_conv_geom* g, lrd_dtype dt, uin
     size_t pin = (size_t)g->N * g->H * g->W, pout = (size_t)g->N * cs.Ho * cs.Wo;
     size_t a = round256(pin * g->r1 * esize(dt)), b = round256(pout * g->r2 * esize(dt));
     size_t kk = (size_t)g->k * g->k;
-    size_t part = std::max(std::max(partial_bytes(g->S, g->r2, pout, dt), partial_bytes(g->r2, kk * g->r1, pout, dt)),
+    size_t part = std::max(std::max(partial_bytes(g->S, g->r2, pout, dt), partial_bytes(g->r2, kk * g->r1, pout, dt, true)),
                            partial_bytes(g->r1, g->C, pin, dt));
     part = std::max(part, round256(conv_direct_wgrad_bytes(cs, dt == LRD_BF16)));
     // forward: A and B when not side-stored; backward: dA, dB, recomputed A and B, partials, and the
@@ -1012,7 +1012,7 @@ lrd_status tucker_bwd_impl(const void* dY, const void* X, const void* A, const v
     float* shared_partial = nullptr;
     size_t shared_bytes = 0;
     auto splits_for = [&](MatOp& op) {
-        int s = choose_splits(op.M, op.N, op.K, dt == LRD_BF16);
+        int s = choose_splits(op.M, op.N, op.K, dt == LRD_BF16, op.gather != GATHER_NONE);
         if (s <= 1) return;
         size_t need = (size_t)s * op.M * op.N * sizeof(float);
         if (need > shared_bytes) return;
@@ -1026,7 +1026,7 @@ lrd_status tucker_bwd_impl(const void* dY, const void* X, const void* A, const v
     }
     if (t1) w1 = tn(dA, r1, X, C, dP1, C, r1, C, pin, dt);
     // one partial buffer, sized for the largest of the three products, used by them in turn
-    shared_bytes = std::max(std::max(t2 ? partial_bytes(S, r2, pout, dt) : 0, tg ? partial_bytes(r2, kk * r1, pout, dt) : 0),
+    shared_bytes = std::max(std::max(t2 ? partial_bytes(S, r2, pout, dt) : 0, tg ? partial_bytes(r2, kk * r1, pout, dt, true) : 0),
                             t1 ? partial_bytes(r1, C, pin, dt) : 0);
     if (tg) shared_bytes = std::max(shared_bytes, round256(conv_direct_wgrad_bytes(cs, dt == LRD_BF16)));
     if (shared_bytes) shared_partial = (float*)cv.take(shared_bytes);
@@ -1082,7 +1082,7 @@ size_t lrd_dense_conv_workspace_bytes(const lrd_conv_geom* g, lrd_dtype dt)
 {
     if (!dtype_ok(dt) || !geom_ok(g, false)) return 0;
     ConvShape cs = core_shape(*g, g->C, g->S);
-    return std::max(partial_bytes(g->S, (int64_t)g->k * g->k * g->C, g->N * (int64_t)cs.Ho * cs.Wo, dt),
+    return std::max(partial_bytes(g->S, (int64_t)g->k * g->k * g->C, g->N * (int64_t)cs.Ho * cs.Wo, dt, true),
                     round256(conv_direct_wgrad_bytes(cs, dt == LRD_BF16))) +
            round256(conv_dgrad_flip_bytes(cs, dt == LRD_BF16));
 }

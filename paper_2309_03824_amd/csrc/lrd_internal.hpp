@@ -92,10 +92,15 @@ hipError_t run_matop(const MatOp& op, hipStream_t st);              // picks an 
 hipError_t apply_epilogue(const MatOp& op, hipStream_t st);        // unfused form of MatOp::epilogue
 
 // Workspace floats a MatOp of this shape needs for split-K (0 if it will not be split).
-int choose_splits(int64_t M, int64_t N, int64_t K, bool in_bf16);
+int choose_splits(int64_t M, int64_t N, int64_t K, bool in_bf16, bool gather = false);
 // Split-K count for a product whose result is a narrow bf16 activation (1 = not split).
 int choose_splits_act(int64_t M, int64_t N, int64_t K, bool in_bf16);
 int choose_splits_batched(int64_t M, int64_t N, int64_t K, int64_t batch);
+// Output tiles of the MFMA product kernel for long reductions, and the fastest of them for a product cut into
+// `splits` slices of K.
+enum GemmCost { COST_PLAIN, COST_WGRAD, COST_GATHER, GEMM_COSTS };     // both operands k-major; convolution gathers
+enum GemmTile { TILE_256x256, TILE_128x256, TILE_128x128, TILE_128x128_PAIR, TILE_64x128, TILE_128x64, TILE_64x64, GEMM_TILES };
+GemmTile gemm_best_tile(int64_t M, int64_t N, int64_t K, int64_t splits, int64_t batch, GemmCost kind);
 
 // Fused pair  C2[M x N2] = (A[M x K1] . B1[R x K1]^T) . B2[N2 x R]^T : the rank-R intermediate
 // stays on chip; optionally it is also stored (mid_save, [M x R], operand dtype).

@@ -4,15 +4,18 @@
 //   data gradient               C = A . B            A [M x K], B [K x N]   (B k-major)
 //   weight gradient (fp32 out)  C = A^T . B          A [K x M], B [K x N]   (both k-major), split-K
 //
-// Main loop: straight-line code, no data-dependent branches.  Every thread owns fixed 16-byte
-// chunks of the operand tiles.  Plain operands are read with buffer loads whose range check returns
-// zeros outside the operand (rows or columns that do not exist get an offset no descriptor admits);
-// convolution gathers clamp the ADDRESS (so the load is always legal) and zero the VALUE when it is
-// written to LDS.  Either way the loads have no consumers until the LDS hand-off and stay in flight
-// across DEPTH K-steps; long reductions run a branch-free steady-state loop, the last steps a drain
-// loop.  K-major operands are copied to LDS as they lie in memory and transposed by the LDS read
-// (ds_read_b64_tr_b16) when the MFMA fragments are fetched, so no layout costs a VALU instruction.
+// Operand tiles go from memory straight into LDS (buffer loads with the LDS bit), STAGES K-steps of them in a
+// ring; a wave's loads complete in order, so "all but the newest n" (s_waitcnt vmcnt) plus one barrier per K-step
+// hand a stage over, and nothing waits for the loads that are still under way.  The range check of the buffer
+// descriptor supplies the zeros: rows, columns and k that do not exist, and the padding of a convolution, get an
+// offset no descriptor admits.  K-major operands lie in LDS as in memory and are transposed by the LDS read
+// (ds_read_b64_tr_b16) when the MFMA fragments are fetched, so no layout costs a VALU instruction.  A load writes
+// 64 consecutive 16-byte chunks of LDS, so rows cannot be padded against bank conflicts: instead each lane picks
+// which chunk of its row it loads (kc_swz, km_swz), and the readers apply the same permutation.
 // bf16 results leave through LDS so that each lane stores 16 contiguous bytes of an output row.
+// Against tiles staged through registers and padded rows (two buffers, loads two steps ahead): 16384 x 512 x 4096
+// 99 -> 62 us, 16384 x 4096 x 512 119 -> 80 us, 8192 x 256 x 4096 40 -> 24 us, 8192 x 4096 x 256 32 -> 26 us, weight
+// gradient 4096 x 512 x 16384 118 -> 78 us.
 //
 // Convolutions are the same kernel with gather tiles in place of the plain ones (implicit GEMM:
 // forward, data gradient, weight gradient).  The data gradient of a strided convolution runs as one
@@ -21,6 +24,7 @@
 #include <algorithm>
 #include <cstdio>
 #include <string>
+#include <type_traits>
 
 #include "lrd_internal.hpp"
 
@@ -28,7 +32,6 @@ namespace lrd {
 namespace {
 
 constexpr int BK = 64;
-constexpr int LDK = BK + 8;
 
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c)
 {
@@ -47,12 +50,8 @@ struct BatchArgs {
     int64_t a_bs = 0, b_bs = 0, c_bs = 0, aux_bs = 0, bias_bs = 0;
 };
 
-// Plain (strided) operands are read with buffer loads: the descriptor's base is the tile's first
-// element for this K-step (wave-uniform), each chunk keeps one 32-bit byte offset, and the range
-// check of the descriptor returns zeros for anything past the operand's last element.  A chunk
-// whose row (or column group) does not exist gets an offset no descriptor admits, so static
-// validity costs nothing per step; only the tail of K inside a row needs a mask, and only in the
-// last step (store<true>).
+// Loads go through buffer descriptors: 32-bit byte offsets from a wave-uniform base, and zeros for any
+// offset past num_records (into LDS as well).
 constexpr uint32_t BUF_FLAGS = 0x00020000u;      // raw buffer, 32-bit data format
 constexpr uint32_t BUF_OOB = 0xFFFFFFF0u;        // >= every num_records used here
 constexpr int64_t BUF_MAX_LD = int64_t(1) << 22; // keeps (256 rows x ld + K) x 2 bytes below BUF_OOB
@@ -70,121 +69,123 @@ __device__ __forceinline__ const char* uni_ptr(const void* p)
     return reinterpret_cast<const char*>(uni64((int64_t)reinterpret_cast<uintptr_t>(p)));
 }
 
-__device__ __forceinline__ u32x4 buf_load16(const char* base, uint32_t span, uint32_t voff)
+// 16 bytes per lane from memory into LDS: lane l's chunk lands at byte address lds + 16 l (lds is wave-uniform).
+// As an instruction of its own and not the builtin: the compiler waits for every load of that builtin still in
+// flight before each LDS read that might alias it, which is all of them here.  It has no register result; the
+// waits are wait_vm's.  (s_nop: M0 must be written one state before an LDS load reads it.)
+__device__ __forceinline__ void load_to_lds(uint32_t lds, const char* base, uint32_t span, uint32_t voff)
 {
     __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, (int)span, (int)BUF_FLAGS);
-    return __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, 0, 0);
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(r) : "memory");
 }
+// Until all but this wave's newest N vector-memory operations have completed.
+template <int N>
+__device__ __forceinline__ void wait_vm()
+{
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+// The same for N = min(rem, D) stages of LPS loads each.
+template <int D, int LPS>
+__device__ __forceinline__ void wait_stages(int rem)
+{
+    if constexpr (D == 0) wait_vm<0>();
+    else if (rem >= D) wait_vm<D * LPS>();
+    else wait_stages<D - 1, LPS>(rem);
+}
+// A barrier after this wave's own LDS reads have returned (not its loads: those are counted by wait_vm).
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// ---- k-contiguous tile: ROWS x BK, chunk c -> row c>>3, k-chunk c&7 ------------------------------
-template <int ROWS, int NT, int DEPTH>
+// Every tile type: init() once; step(k0) before the loads of a K-step, then one(i) for each of its CH loads.
+// Load i of wave w fills the 1024 bytes at (i * NW + w) * 1024 of the tile's part of a stage.
+
+// ---- k-contiguous tile: ROWS x BK, a row is 128 bytes of LDS; a load covers 8 rows.  Chunk c of row r lies in slot
+// c ^ kc_swz(r): the fragment reads of 16 consecutive rows then fall on 16 different 16-byte columns of the banks.
+__device__ __forceinline__ constexpr int kc_swz(int row) { return (row >> 1) & 7; }
+template <int ROWS, int NW>
 struct KcTile {
-    static_assert(NT % 8 == 0, "every chunk of a thread has the same k offset");
-    static constexpr int CH = (ROWS * 8 + NT - 1) / NT;
-    static constexpr bool FULL = (ROWS * 8) % NT == 0;
+    static_assert(ROWS % (8 * NW) == 0 && NW % 2 == 0, "every load of a lane has the same k offset");
+    static constexpr int CH = ROWS / (8 * NW), BYTES = ROWS * BK * 2;
     const char* base;     // first row of the tile, k = 0
     uint32_t span;        // bytes from base to the end of the tile's last existing row
+    const char* at;       // base and span at the current K-step
+    uint32_t left;
+    int kc, k0;
     uint32_t voff[CH];
-    int kc8;
-    u32x4 st[DEPTH][CH];
 
-    __device__ __forceinline__ void init(const Operand& o, int row0, int tid, const ConvShape&, int K, int)
+    __device__ __forceinline__ void init(const Operand& o, int row0, int wave, int lane, const ConvShape&, int K, int)
     {
         base = uni_ptr(o.p + (int64_t)row0 * o.ld);
         const int rows_here = min(o.rows - row0, ROWS);
         span = uni((uint32_t)(((int64_t)(rows_here - 1) * o.ld + K) * 2));
-        kc8 = (tid & 7) * 8;
+        kc = ((lane & 7) ^ kc_swz(wave * 8 + (lane >> 3))) * 8;
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
-            int r = (tid + i * NT) >> 3;
-            voff[i] = r < rows_here ? (uint32_t)((r * o.ld + kc8) * 2) : BUF_OOB;
+            const int r = (i * NW + wave) * 8 + (lane >> 3);
+            voff[i] = r < rows_here ? (uint32_t)((r * o.ld + kc) * 2) : BUF_OOB;
         }
     }
-    __device__ __forceinline__ void load(int d, int k0, int, int tid)
+    __device__ __forceinline__ void step(int k, int)
     {
-        const uint32_t kb = uni((uint32_t)k0) * 2u;
-        const char* b = base + kb;
-        const uint32_t left = span - kb;      // k0 < K, so kb < span (a saturating form would leave the scalar unit)
-#pragma unroll
-        for (int i = 0; i < CH; ++i)
-            if (FULL || tid + i * NT < ROWS * 8) st[d][i] = buf_load16(b, left, voff[i]);
+        k0 = (int)uni((uint32_t)k);
+        at = base + k0 * 2;
+        left = span - (uint32_t)k0 * 2u;      // k0 < K
     }
-    template <bool TAIL>
-    __device__ __forceinline__ void store(int d, bf16_t* lds, int k0, int kend, int tid) const
+    __device__ __forceinline__ void one(int i, uint32_t lds, int kend, int wave)
     {
-        const u32x4 z = {0u, 0u, 0u, 0u};
-        const bool inside = !TAIL || k0 + kc8 < kend;
-#pragma unroll
-        for (int i = 0; i < CH; ++i) {
-            int c = tid + i * NT;
-            if (FULL || c < ROWS * 8)
-                *reinterpret_cast<u32x4*>(lds + (c >> 3) * LDK + (c & 7) * 8) = inside ? st[d][i] : z;
-        }
+        load_to_lds(lds + (i * NW + wave) * 1024, at, left, k0 + kc < kend ? voff[i] : BUF_OOB);
     }
 };
 
-// ---- k-major tile: BK x COLS kept in LDS as it is stored in memory ([k][column], columns
-// contiguous); chunk c -> k = c / (COLS/8), column chunk c % (COLS/8).  The transposition the MFMA
-// operand layout needs is done by the LDS read itself (ds_read_b64_tr_b16, see km_frag).
-template <int COLS, int NT, int DEPTH>
+// ---- k-major tile: BK x COLS, in LDS as in memory ([k][column]); a load covers 512 / COLS rows of k.  Chunk c of
+// row k lies in slot c ^ km_swz(k): a transposing read takes 64 bytes from each of four consecutive k, which then
+// fall on different quarters of the banks.  km_swz(k) = km_swz(k + 4) = km_swz(k + 8).
+template <int COLS>
+__device__ __forceinline__ constexpr int km_swz(int k)
+{
+    return COLS >= 128 ? (k & 3) << 2 : COLS >= 64 ? (k & 2) << 1 : 0;
+}
+template <int COLS, int NW>
 struct KmTile {
     static constexpr int CPK = COLS / 8;                 // 16-byte chunks per k row
-    static constexpr int LDM = COLS + 16;                // LDS row length: stride = 8 banks mod 32
-    static constexpr int CH = (BK * CPK + NT - 1) / NT;
-    static constexpr bool FULL = (BK * CPK) % NT == 0;
+    static constexpr int KPI = 64 / CPK;                 // k rows per load
+    static constexpr int CH = BK / (KPI * NW), BYTES = COLS * BK * 2;
+    static_assert(64 % CPK == 0 && BK % (KPI * NW) == 0, "whole loads");
     const char* base;     // k = 0, first column of the tile
     int64_t ld;
-    int K, cols_here;     // columns that exist from the tile's first one on
+    int cols_here;        // columns that exist from the tile's first one on
+    const char* at;
+    uint32_t left;
     uint32_t voff[CH];
-    int krow[CH];
-    u32x4 st[DEPTH][CH];
 
-    __device__ __forceinline__ void init(const Operand& o, int col0, int tid, const ConvShape&, int Kdim, int)
+    __device__ __forceinline__ void init(const Operand& o, int col0, int wave, int lane, const ConvShape&, int, int)
     {
         ld = uni64(o.ld);
-        K = (int)uni((uint32_t)Kdim);
         cols_here = (int)uni((uint32_t)(o.rows - col0));
         base = uni_ptr(o.p + col0);
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
-            int c = tid + i * NT;
-            int col = (c % CPK) * 8;
-            krow[i] = c / CPK;
-            voff[i] = col < cols_here ? (uint32_t)((krow[i] * o.ld + col) * 2) : BUF_OOB;
+            const int k = (i * NW + wave) * KPI + lane / CPK;
+            const int col = ((lane % CPK) ^ km_swz<COLS>(k)) * 8;
+            voff[i] = col < cols_here ? (uint32_t)((k * o.ld + col) * 2) : BUF_OOB;
         }
     }
-    __device__ __forceinline__ void load(int d, int k0, int, int tid)
+    __device__ __forceinline__ void step(int k, int kend)
     {
-        // bytes from this step's first k row to the last element of its last existing k row (at most
-        // BK rows) in these columns; rows past K fall outside because ld >= cols_here
-        const int ku = (int)uni((uint32_t)k0);
-        const char* b = base + (int64_t)ku * ld * 2;
-        const uint32_t left = (uint32_t)(min(K - ku, BK) - 1) * ((uint32_t)ld * 2u) + (uint32_t)cols_here * 2u;
-#pragma unroll
-        for (int i = 0; i < CH; ++i)
-            if (FULL || tid + i * NT < BK * CPK) st[d][i] = buf_load16(b, left, voff[i]);
+        // bytes from this step's first k row to the last element of its last k row (at most BK rows) in these
+        // columns; rows from kend on fall outside because ld >= cols_here
+        const int ku = (int)uni((uint32_t)k);
+        at = base + (int64_t)ku * ld * 2;
+        left = (uint32_t)(min(kend - ku, BK) - 1) * ((uint32_t)ld * 2u) + (uint32_t)cols_here * 2u;
     }
-    template <bool TAIL>
-    __device__ __forceinline__ void store(int d, bf16_t* lds, int k0, int kend, int tid) const
-    {
-        const u32x4 z = {0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int i = 0; i < CH; ++i) {
-            int c = tid + i * NT;
-            if (FULL || c < BK * CPK)
-                *reinterpret_cast<u32x4*>(lds + (c / CPK) * LDM + (c % CPK) * 8) =
-                    (!TAIL || k0 + krow[i] < kend) ? st[d][i] : z;
-        }
-    }
+    __device__ __forceinline__ void one(int i, uint32_t lds, int, int wave) { load_to_lds(lds + (i * NW + wave) * 1024, at, left, voff[i]); }
 };
 
 // ---- implicit-GEMM operands of a k x k convolution on NHWC data ---------------------------------
-// Same LDS layouts as the plain tiles; the address of a 16-byte chunk comes from the tap geometry,
-// out-of-image taps and tails are clamped to a legal address and zeroed when the chunk is written
-// to LDS.  Channel counts are multiples of 8 on this path, so a chunk never straddles two taps.
-// K-steps are loaded strictly in order (k0 = kbeg, kbeg + BK, ...), so the decomposition of k into
-// (tap, channel) or (image, y, x) is kept as state and advanced by BK after every load: the only
-// integer divisions are in init().
+// Same LDS layouts as the plain tiles; the offset of a 16-byte chunk comes from the tap geometry, out-of-image
+// taps and tails get the offset past the descriptor.  Channel counts are multiples of 8 on this path, so a chunk
+// never straddles two taps.  K-steps are loaded strictly in order (k0 = kbeg, kbeg + BK, ...), so the
+// decomposition of k into (tap, channel) or (image, y, x) is kept as state and advanced by BK with the loads:
+// the only integer divisions are in init().
 
 // floor(t / d) for 0 <= t * d < 65536 by multiplication with ceil(65536 / d): taps by the kernel size
 // (d < 32, t <= d * d + 8) and, in the data gradient, pixel coordinates by the stride.
@@ -192,26 +193,26 @@ __device__ __forceinline__ int small_div(int t, int magic) { return (t * magic) 
 
 // A operand, k-contiguous.  FWD:   row = output pixel, k = (u, v, i), reads X[n, y*s+u-p, x*s+v-p, i].
 //                           DGRAD: row = input pixel,  k = (u, v, o), reads dY[n, (a+p-u)/s, (b+p-v)/s, o].
-template <int ROWS, int NT, int DEPTH, bool DGRAD>
+template <int ROWS, int NW, bool DGRAD>
 struct ConvRowsTile {
-    static_assert(NT % 8 == 0, "every chunk of a thread has the same k offset");
-    static constexpr int CH = (ROWS * 8 + NT - 1) / NT;
-    static constexpr bool FULL = (ROWS * 8) % NT == 0;
-    const bf16_t* base;
+    static_assert(ROWS % (8 * NW) == 0 && NW % 2 == 0, "every load of a lane has the same k offset");
+    static constexpr int CH = ROWS / (8 * NW), BYTES = ROWS * BK * 2;
+    const char* base;
+    uint32_t span;
     ConvShape cs;
-    int img[CH], py[CH], px[CH];
-    bool rowok[CH];
-    int kc8, tap, c0;         // this thread's k of the next load, as (tap, channel); same for all its chunks
-    int ch, q_tap, r_ch, magic, magic_s;
+    // FWD: image coordinates of tap (0, 0), and the offset of that pixel; DGRAD: those of the input pixel plus pad, and
+    // the first row of its image.  A row that does not exist gets coordinates no tap brings into the image.
+    int oy[CH], ox[CH], pix[CH];
+    int kc, k0, tap, c0;      // this lane's k of the current step, as (tap, channel); same for all its loads
+    int ch, q_tap, r_ch, magic, magic_s, u, v;
     int kdiv, u0, v0, ustep;  // tap index -> (u, v): u = u0 + ustep * (tap / kdiv), v = v0 + ustep * (tap % kdiv)
-    bool ok[DEPTH][CH];
-    u32x4 st[DEPTH][CH];
 
-    __device__ __forceinline__ void init(const Operand& o, int row0, int tid, const ConvShape& shape, int, int kbeg)
+    __device__ __forceinline__ void init(const Operand& o, int row0, int wave, int lane, const ConvShape& shape, int, int kbeg)
     {
-        base = o.p;
         cs = shape;
         ch = DGRAD ? cs.O : cs.I;            // channels of the tensor being gathered
+        base = uni_ptr(o.p);
+        span = uni((uint32_t)cs.N * (uint32_t)(DGRAD ? cs.Ho * cs.Wo : cs.H * cs.W) * (uint32_t)ch * 2u);
         q_tap = BK / ch;
         r_ch = BK - q_tap * ch;
         const bool cls = DGRAD && cs.cls;
@@ -222,105 +223,90 @@ struct ConvRowsTile {
         ustep = cls ? cs.stride : 1;
         magic = (65536 + kdiv - 1) / kdiv;
         magic_s = (65536 + cs.stride - 1) / cs.stride;
-        kc8 = (tid & 7) * 8;
-        tap = (kbeg + kc8) / ch;
-        c0 = (kbeg + kc8) - tap * ch;
+        kc = ((lane & 7) ^ kc_swz(wave * 8 + (lane >> 3))) * 8;
+        tap = (kbeg + kc) / ch - q_tap;          // step() advances to the first K-step
+        c0 = (kbeg + kc) % ch - r_ch;
         // rows: output pixels, input pixels, or the input pixels of one parity class
         const int gw = !DGRAD ? cs.Wo : cls ? class_extent(cs.W, cs.cx, cs.stride) : cs.W;
         const int gh = !DGRAD ? cs.Ho : cls ? class_extent(cs.H, cs.cy, cs.stride) : cs.H;
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
-            int c = tid + i * NT;
-            int row = row0 + (c >> 3);
-            rowok[i] = row < o.rows;
-            row = min(row, o.rows - 1);
-            px[i] = row % gw;
-            int q = row / gw;
-            py[i] = q % gh;
-            img[i] = q / gh;
+            const int row = row0 + (i * NW + wave) * 8 + (lane >> 3);
+            const int q = row / gw;
+            int px = row - q * gw, py = q % gh;
+            const int img = q / gh;
             if (cls) {
-                px[i] = px[i] * cs.stride + cs.cx;
-                py[i] = py[i] * cs.stride + cs.cy;
+                px = px * cs.stride + cs.cx;
+                py = py * cs.stride + cs.cy;
             }
+            oy[i] = DGRAD ? py + cs.pad : py * cs.stride - cs.pad;
+            ox[i] = DGRAD ? px + cs.pad : px * cs.stride - cs.pad;
+            pix[i] = DGRAD ? img * cs.Ho : (img * cs.H + oy[i]) * cs.W + ox[i];
+            if (row >= o.rows) oy[i] = DGRAD ? -1 : cs.H;
         }
     }
-    __device__ __forceinline__ void load(int d, int k0, int kend, int tid)
+    __device__ __forceinline__ void step(int k, int)
     {
-        const int sh = DGRAD ? cs.Ho : cs.H, sw = DGRAD ? cs.Wo : cs.W;
-        const int tq = small_div(tap, magic);
-        const int u = u0 + ustep * tq, v = v0 + ustep * (tap - tq * kdiv);
-        const bool kin = k0 + kc8 < kend;
-#pragma unroll
-        for (int i = 0; i < CH; ++i)
-            if (FULL || tid + i * NT < ROWS * 8) {
-                int yy, xx;
-                bool inside;
-                if (DGRAD) {
-                    // output pixel (ys, xs) / stride, if that is a whole number inside the output
-                    const int ys = py[i] + cs.pad - u, xs = px[i] + cs.pad - v;
-                    const int yp = max(ys, 0), xp = max(xs, 0);
-                    yy = small_div(yp, magic_s);
-                    xx = small_div(xp, magic_s);
-                    inside = ys >= 0 && xs >= 0 && yy * cs.stride == yp && xx * cs.stride == xp && yy < sh && xx < sw;
-                } else {
-                    yy = py[i] * cs.stride + u - cs.pad;
-                    xx = px[i] * cs.stride + v - cs.pad;
-                    inside = yy >= 0 && xx >= 0 && yy < sh && xx < sw;
-                }
-                ok[d][i] = inside && rowok[i] && kin;
-                yy = min(max(yy, 0), sh - 1);          // also covers taps past the last one (tail of K)
-                xx = min(max(xx, 0), sw - 1);
-                st[d][i] = *reinterpret_cast<const u32x4*>(base + ((int64_t)(img[i] * sh + yy) * sw + xx) * ch + c0);
-            }
+        k0 = (int)uni((uint32_t)k);
         c0 += r_ch;
         tap += q_tap;
         if (c0 >= ch) {
             c0 -= ch;
             ++tap;
         }
+        const int tq = small_div(tap, magic);
+        u = u0 + ustep * tq;
+        v = v0 + ustep * (tap - tq * kdiv);
     }
-    template <bool TAIL>
-    __device__ __forceinline__ void store(int d, bf16_t* lds, int, int, int tid) const
+    __device__ __forceinline__ void one(int i, uint32_t lds, int kend, int wave)
     {
-        const u32x4 z = {0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int i = 0; i < CH; ++i) {
-            int c = tid + i * NT;
-            if (FULL || c < ROWS * 8)
-                *reinterpret_cast<u32x4*>(lds + (c >> 3) * LDK + (c & 7) * 8) = ok[d][i] ? st[d][i] : z;
+        bool ok = k0 + kc < kend;
+        int at;
+        if (DGRAD) {
+            // output pixel (ys, xs) / stride, if that is a whole number inside the output
+            const int ys = oy[i] - u, xs = ox[i] - v;
+            const int yp = max(ys, 0), xp = max(xs, 0);
+            const int yy = small_div(yp, magic_s), xx = small_div(xp, magic_s);
+            ok = ok && ys >= 0 && xs >= 0 && yy * cs.stride == yp && xx * cs.stride == xp && yy < cs.Ho && xx < cs.Wo;
+            at = (pix[i] + yy) * cs.Wo + xx;
+        } else {
+            ok = ok && (uint32_t)(oy[i] + u) < (uint32_t)cs.H && (uint32_t)(ox[i] + v) < (uint32_t)cs.W;
+            at = pix[i] + u * cs.W + v;
         }
+        load_to_lds(lds + (i * NW + wave) * 1024, base, span, ok ? ((uint32_t)at * (uint32_t)ch + (uint32_t)c0) * 2u : BUF_OOB);
     }
 };
 
 // B operand, k-major.  DGRAD: column = input channel i, k = (u, v, o), reads W[o][u][v][i].
 //                      WGRAD: column = (u, v, i),        k = output pixel, reads X[n, y*s+u-p, x*s+v-p, i].
-template <int COLS, int NT, int DEPTH, bool WGRAD>
+template <int COLS, int NW, bool WGRAD>
 struct ConvKmTile {
-    static constexpr int CPK = COLS / 8;
-    static constexpr int LDM = COLS + 16;
-    static constexpr int CH = (BK * CPK + NT - 1) / NT;
-    static constexpr bool FULL = (BK * CPK) % NT == 0;
-    const bf16_t* base;
+    static constexpr int CPK = COLS / 8, KPI = 64 / CPK;
+    static constexpr int CH = BK / (KPI * NW), BYTES = COLS * BK * 2;
+    static_assert(64 % CPK == 0 && BK % (KPI * NW) == 0, "whole loads");
+    static constexpr int KS = KPI * NW % 4 == 0 ? 1 : CH;    // distinct swizzles, hence columns, among a lane's loads
+    const char* base;
+    uint32_t span;
     ConvShape cs;
-    int c0[CH], tu[CH], tv[CH];
-    bool colok[CH];
+    int c0[KS], tu[KS], tv[KS];
+    bool colok[KS];
     // k of the next load, per chunk.  DGRAD: (tap, o) in s1, s0.  WGRAD: output pixel as (n, y, x) in s2, s1, s0.
     int s0[CH], s1[CH], s2[CH], kk[CH];
     int d0, d1, d2;           // BK in the same mixed radix
     int ntaps, nv, magic_nv, u0, v0, ustep;   // DGRAD: the taps K runs over (all, or those of a parity class)
-    bool ok[DEPTH][CH];
-    u32x4 st[DEPTH][CH];
 
-    __device__ __forceinline__ void init(const Operand& o, int col0, int tid, const ConvShape& shape, int, int kbeg)
+    __device__ __forceinline__ void init(const Operand& o, int col0, int wave, int lane, const ConvShape& shape, int, int kbeg)
     {
-        base = o.p;
+        base = uni_ptr(o.p);
         cs = shape;
         if (WGRAD) {
+            span = uni((uint32_t)cs.N * (uint32_t)(cs.H * cs.W) * (uint32_t)cs.I * 2u);
             d2 = BK / (cs.Ho * cs.Wo);
             int rem = BK - d2 * cs.Ho * cs.Wo;
             d1 = rem / cs.Wo;
             d0 = rem - d1 * cs.Wo;
         } else {
+            span = uni((uint32_t)cs.O * (uint32_t)(cs.k * cs.k) * (uint32_t)cs.I * 2u);
             d2 = 0;
             d1 = BK / cs.O;
             d0 = BK - d1 * cs.O;
@@ -333,129 +319,126 @@ struct ConvKmTile {
             ustep = cs.cls ? cs.stride : 1;
         }
 #pragma unroll
-        for (int i = 0; i < CH; ++i) {
-            int c = tid + i * NT;
-            int col = col0 + (c % CPK) * 8;
+        for (int i = 0; i < KS; ++i) {
+            const int col = col0 + ((lane % CPK) ^ km_swz<COLS>((i * NW + wave) * KPI + lane / CPK)) * 8;
             colok[i] = col < o.rows;
-            col = min(col, o.rows - 8);
-            const int k = kbeg + c / CPK;
+            if (WGRAD) {
+                const int tap = col / cs.I;
+                c0[i] = col - tap * cs.I;
+                tu[i] = tap / cs.k - cs.pad;
+                tv[i] = tap % cs.k - cs.pad;
+            } else {
+                c0[i] = col;
+                tu[i] = tv[i] = 0;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const int k = kbeg + (i * NW + wave) * KPI + lane / CPK;
             kk[i] = k;
             if (WGRAD) {
-                int tap = col / cs.I;
-                c0[i] = col - tap * cs.I;
-                tu[i] = tap / cs.k;
-                tv[i] = tap - tu[i] * cs.k;
                 s0[i] = k % cs.Wo;
                 int q = k / cs.Wo;
                 s1[i] = q % cs.Ho;
                 s2[i] = q / cs.Ho;
             } else {
-                c0[i] = col;
-                tu[i] = tv[i] = 0;
                 s1[i] = k / cs.O;
                 s0[i] = k - s1[i] * cs.O;
                 s2[i] = 0;
             }
         }
     }
-    __device__ __forceinline__ void load(int d, int, int kend, int tid)
+    __device__ __forceinline__ void step(int, int) {}
+    __device__ __forceinline__ void one(int i, uint32_t lds, int kend, int wave)
     {
-#pragma unroll
-        for (int i = 0; i < CH; ++i)
-            if (FULL || tid + i * NT < BK * CPK) {
-                const bool kin = kk[i] < kend;
-                bool inside = true;
-                int64_t off;
-                if (WGRAD) {
-                    int yy = s1[i] * cs.stride + tu[i] - cs.pad, xx = s0[i] * cs.stride + tv[i] - cs.pad;
-                    inside = yy >= 0 && xx >= 0 && yy < cs.H && xx < cs.W;
-                    yy = min(max(yy, 0), cs.H - 1);
-                    xx = min(max(xx, 0), cs.W - 1);
-                    int n = min(s2[i], cs.N - 1);           // pixels past the last one (tail of K) stay in the tensor
-                    off = ((int64_t)(n * cs.H + yy) * cs.W + xx) * cs.I + c0[i];
-                } else {
-                    const int t = min(s1[i], ntaps - 1);     // likewise for taps past the last one
-                    const int tq = small_div(t, magic_nv);
-                    const int tap = (u0 + ustep * tq) * cs.k + v0 + ustep * (t - tq * nv);
-                    off = ((int64_t)s0[i] * cs.k * cs.k + tap) * cs.I + c0[i];
-                }
-                ok[d][i] = inside && colok[i] && kin;
-                st[d][i] = *reinterpret_cast<const u32x4*>(base + off);
-                // advance this chunk's k by BK
-                kk[i] += BK;
-                s0[i] += d0;
-                s1[i] += d1;
-                if (WGRAD) {
-                    if (s0[i] >= cs.Wo) { s0[i] -= cs.Wo; ++s1[i]; }
-                    s2[i] += d2;
-                    if (s1[i] >= cs.Ho) { s1[i] -= cs.Ho; ++s2[i]; }
-                } else {
-                    if (s0[i] >= cs.O) { s0[i] -= cs.O; ++s1[i]; }
-                }
-            }
-    }
-    template <bool TAIL>
-    __device__ __forceinline__ void store(int d, bf16_t* lds, int, int, int tid) const
-    {
-        const u32x4 z = {0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int i = 0; i < CH; ++i) {
-            int c = tid + i * NT;
-            if (FULL || c < BK * CPK)
-                *reinterpret_cast<u32x4*>(lds + (c / CPK) * LDM + (c % CPK) * 8) = ok[d][i] ? st[d][i] : z;
+        const int c = KS == 1 ? 0 : i;
+        bool ok = colok[c] && kk[i] < kend;
+        uint32_t off;
+        if (WGRAD) {
+            const int yy = s1[i] * cs.stride + tu[c], xx = s0[i] * cs.stride + tv[c];
+            ok = ok && (uint32_t)yy < (uint32_t)cs.H && (uint32_t)xx < (uint32_t)cs.W;
+            off = (uint32_t)((s2[i] * cs.H + yy) * cs.W + xx) * (uint32_t)cs.I + (uint32_t)c0[c];
+        } else {
+            const int t = min(s1[i], ntaps - 1);     // (taps past the last one: tail of K)
+            const int tq = small_div(t, magic_nv);
+            const int tap = (u0 + ustep * tq) * cs.k + v0 + ustep * (t - tq * nv);
+            off = (uint32_t)(s0[i] * cs.k * cs.k + tap) * (uint32_t)cs.I + (uint32_t)c0[c];
+        }
+        load_to_lds(lds + (i * NW + wave) * 1024, base, span, ok ? off * 2u : BUF_OOB);
+        // advance this load's k by BK
+        kk[i] += BK;
+        s0[i] += d0;
+        s1[i] += d1;
+        if (WGRAD) {
+            if (s0[i] >= cs.Wo) { s0[i] -= cs.Wo; ++s1[i]; }
+            s2[i] += d2;
+            if (s1[i] >= cs.Ho) { s1[i] -= cs.Ho; ++s2[i]; }
+        } else {
+            if (s0[i] >= cs.O) { s0[i] -= cs.O; ++s1[i]; }
         }
     }
 };
 
 // Tile type by layout (k-major or not) and gather mode (GATHER_* of the product).
-template <int ROWS, int NT, int DEPTH, bool KM, int G, bool IS_A>
-struct TileSel { typedef KcTile<ROWS, NT, DEPTH> type; };
-template <int ROWS, int NT, int DEPTH, int G, bool IS_A>
-struct TileSel<ROWS, NT, DEPTH, true, G, IS_A> { typedef KmTile<ROWS, NT, DEPTH> type; };
-template <int ROWS, int NT, int DEPTH>
-struct TileSel<ROWS, NT, DEPTH, false, GATHER_CONV_FWD, true> { typedef ConvRowsTile<ROWS, NT, DEPTH, false> type; };
-template <int ROWS, int NT, int DEPTH>
-struct TileSel<ROWS, NT, DEPTH, false, GATHER_CONV_DGRAD, true> { typedef ConvRowsTile<ROWS, NT, DEPTH, true> type; };
-template <int ROWS, int NT, int DEPTH>
-struct TileSel<ROWS, NT, DEPTH, true, GATHER_CONV_DGRAD, false> { typedef ConvKmTile<ROWS, NT, DEPTH, false> type; };
-template <int ROWS, int NT, int DEPTH>
-struct TileSel<ROWS, NT, DEPTH, true, GATHER_CONV_WGRAD, false> { typedef ConvKmTile<ROWS, NT, DEPTH, true> type; };
+template <int ROWS, int NW, bool KM, int G, bool IS_A>
+struct TileSel { typedef KcTile<ROWS, NW> type; };
+template <int ROWS, int NW, int G, bool IS_A>
+struct TileSel<ROWS, NW, true, G, IS_A> { typedef KmTile<ROWS, NW> type; };
+template <int ROWS, int NW>
+struct TileSel<ROWS, NW, false, GATHER_CONV_FWD, true> { typedef ConvRowsTile<ROWS, NW, false> type; };
+template <int ROWS, int NW>
+struct TileSel<ROWS, NW, false, GATHER_CONV_DGRAD, true> { typedef ConvRowsTile<ROWS, NW, true> type; };
+template <int ROWS, int NW>
+struct TileSel<ROWS, NW, true, GATHER_CONV_DGRAD, false> { typedef ConvKmTile<ROWS, NW, false> type; };
+template <int ROWS, int NW>
+struct TileSel<ROWS, NW, true, GATHER_CONV_WGRAD, false> { typedef ConvKmTile<ROWS, NW, true> type; };
 
-// Operand fragment of one 32-row block for one 16-wide k step, in the register layout of
-// v_mfma_f32_32x32x16_bf16: lane L holds row (L & 31), k = 8 * (L >> 5) + 0..7.
-// k-contiguous tile [row][k]: one 16-byte read.
-__device__ __forceinline__ bf16x8 kc_frag(const bf16_t* tile, int row_block, int kk, int lane)
-{
-    return *reinterpret_cast<const bf16x8*>(tile + (row_block * 32 + (lane & 31)) * LDK + kk * 16 + (lane >> 5) * 8);
-}
-
-// k-major tile [k][row]: km_frag (two transposing reads).
-template <int TM, int TN, bool A_KM, bool B_KM, int LDMA, int LDMB>
-__device__ __forceinline__ void mma_step(f32x16 (&acc)[TM][TN], const bf16_t* a_lds, int a_row0, const bf16_t* b_lds,
-                                         int b_row0, int lane)
-{
+// Operand fragments of the T 32-row blocks of a wave for one 16-wide k step, in the register layout of
+// v_mfma_f32_32x32x16_bf16: lane L holds row (L & 31), k = 8 * (L >> 5) + 0..7.  The lane's byte offsets in the
+// tile are fixed before the loop.
+template <int ROWS, int T, bool KM>
+struct Frag {     // k-contiguous tile [row][k]: one 16-byte read
+    uint32_t off[BK / 16];
+    __device__ __forceinline__ void init(int row0, int lane)
+    {
+        const int r = row0 + (lane & 31);
 #pragma unroll
-    for (int kk = 0; kk < BK / 16; ++kk) {
-        bf16x8 a[TM], b[TN];
-#pragma unroll
-        for (int i = 0; i < TM; ++i) a[i] = A_KM ? km_frag<LDMA>(a_lds + a_row0, i, kk, lane) : kc_frag(a_lds + a_row0 * LDK, i, kk, lane);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) b[j] = B_KM ? km_frag<LDMB>(b_lds + b_row0, j, kk, lane) : kc_frag(b_lds + b_row0 * LDK, j, kk, lane);
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j) acc[i][j] = mfma32(b[j], a[i], acc[i][j]);   // roles swapped: lane <-> row m
+        for (int kk = 0; kk < BK / 16; ++kk) off[kk] = r * (BK * 2) + (((kk * 2 + (lane >> 5)) ^ kc_swz(r)) << 4);
     }
-}
+    __device__ __forceinline__ bf16x8 get(const char* tile, int i, int kk) const
+    {
+        return *reinterpret_cast<const bf16x8*>(tile + off[kk] + i * 32 * (BK * 2));
+    }
+};
+template <int COLS, int T>
+struct Frag<COLS, T, true> {     // k-major tile [k][row]: two transposing reads (see km_frag for their lane layout)
+    uint32_t off[T];
+    __device__ __forceinline__ void init(int col0, int lane)
+    {
+        const int blk = lane >> 4, s = lane & 15;
+        const int k = 8 * (blk >> 1) + (s >> 2);
+#pragma unroll
+        for (int i = 0; i < T; ++i) {
+            const int col = col0 + i * 32 + 16 * (blk & 1) + 4 * (s & 3);
+            off[i] = k * COLS * 2 + (((col >> 3) ^ km_swz<COLS>(k)) << 4) + (col & 7) * 2;
+        }
+    }
+    __device__ __forceinline__ bf16x8 get(const char* tile, int i, int kk) const
+    {
+        typedef short s16x4 __attribute__((ext_vector_type(4)));
+        typedef short s16x8 __attribute__((ext_vector_type(8)));
+        const char* p = tile + off[i] + kk * 16 * COLS * 2;
+        s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p));
+        s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p + 4 * COLS * 2));
+        s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        return __builtin_bit_cast(bf16x8, v);
+    }
+};
 
-// Elements one operand tile occupies in LDS.
-template <int ROWS, bool KM>
-constexpr int tile_elems() { return KM ? BK * (ROWS + 16) : ROWS * LDK; }
-
-template <int BM, int BN, bool A_KM, bool B_KM, class OutT>
+template <int BM, int BN, int STAGES, class OutT>
 constexpr int gemm2_lds_bytes()
 {
-    int main = 2 * (tile_elems<BM, A_KM>() + tile_elems<BN, B_KM>()) * 2;
+    int main = STAGES * (BM + BN) * BK * 2;
     int epi = sizeof(OutT) == 2 ? BM * (BN + 8) * 2 : 0;
     return main > epi ? main : epi;
 }
@@ -464,9 +447,9 @@ constexpr int gemm2_lds_bytes()
 // lane to global memory, with the optional GELU epilogue.  Results (and the pre-activation the
 // gradient epilogue reads) are streamed with non-temporal accesses: 10 % faster on the wide products.  Every wave must be past its last read
 // of the operand tiles in LDS (the staging tile overlays them); ends without a barrier.
-template <int BM, int BN, int WGM, int WGN, bool MAPROWS, int TM, int TN>
+template <int BM, int BN, int WGM, int WGN, bool MAPROWS, int EPI, int TM, int TN>
 __device__ __forceinline__ void store_bf16_tile(const f32x16 (&acc)[TM][TN], bf16_t* lds, bf16_t* __restrict__ out, int64_t ldc,
-                                                const float* __restrict__ bias, int M, int N, int m0, int n0, int epilogue,
+                                                const float* __restrict__ bias, int M, int N, int m0, int n0,
                                                 bf16_t* __restrict__ aux, int64_t ldaux, int tid, const ConvShape& cs)
 {
     constexpr int NT = 64 * WGM * WGN;
@@ -481,7 +464,7 @@ __device__ __forceinline__ void store_bf16_tile(const f32x16 (&acc)[TM][TN], bf1
     // The activation-gradient epilogue reads the pre-activation: start those loads now, so they
     // are in flight while the accumulators go through LDS.
     bf16x8 z8[PER];
-    if (epilogue == EPI_ACT_GRAD) {
+    if constexpr (EPI == EPI_ACT_GRAD) {
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
             int c = tid + q * NT;
@@ -489,24 +472,25 @@ __device__ __forceinline__ void store_bf16_tile(const f32x16 (&acc)[TM][TN], bf1
             z8[q] = __builtin_bit_cast(bf16x8, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(aux + (int64_t)m * ldaux + n)));
         }
     }
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        int ml = wm * WTM + i * 32 + r;
+    auto stage = [&](auto with_bias) {
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                int nl = wn * WTN + j * 32 + 8 * g + 4 * h;
-                f32x4 v = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
-                if (bias) {
-                    int n = min(n0 + nl, N - 4);
-                    f32x4 b4 = *reinterpret_cast<const f32x4*>(bias + n);
-                    v += b4;
+                const int nl = wn * WTN + j * 32 + 8 * g + 4 * h;
+                f32x4 b4 = {0.f, 0.f, 0.f, 0.f};
+                if constexpr (with_bias) b4 = *reinterpret_cast<const f32x4*>(bias + min(n0 + nl, N - 4));
+#pragma unroll
+                for (int i = 0; i < TM; ++i) {
+                    f32x4 v = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+                    if constexpr (with_bias) v += b4;
+                    const u32x2 pk = {pack_bf16(v.x, v.y), pack_bf16(v.z, v.w)};
+                    *reinterpret_cast<u32x2*>(lds + (wm * WTM + i * 32 + r) * LDC + nl) = pk;
                 }
-                u32x2 pk = {pack_bf16(v.x, v.y), pack_bf16(v.z, v.w)};
-                *reinterpret_cast<u32x2*>(lds + ml * LDC + nl) = pk;
             }
-    }
+    };
+    if (bias) stage(std::true_type{});
+    else stage(std::false_type{});
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
@@ -523,14 +507,14 @@ __device__ __forceinline__ void store_bf16_tile(const f32x16 (&acc)[TM][TN], bf1
             const int ix = mm % gw, q = mm / gw;
             mrow = ((int64_t)(q / gh) * cs.H + (q % gh) * cs.stride + cs.cy) * cs.W + ix * cs.stride + cs.cx;
         }
-        if (epilogue == EPI_ACT_GRAD) {
+        if constexpr (EPI == EPI_ACT_GRAD) {
             bf16x8 c8 = __builtin_bit_cast(bf16x8, v);
 #pragma unroll
             for (int e = 0; e < 8; ++e) c8[e] = (bf16_t)((float)c8[e] * gelu_grad_bf16_f((float)z8[q][e]));
             v = __builtin_bit_cast(u32x4, c8);
         }
         if (ok) __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(out + mrow * ldc + n));
-        if (epilogue == EPI_ACT_STORE) {
+        if constexpr (EPI == EPI_ACT_STORE) {
             bf16x8 c8 = __builtin_bit_cast(bf16x8, v);
 #pragma unroll
             for (int e = 0; e < 8; ++e) c8[e] = (bf16_t)gelu_bf16_f((float)c8[e]);
@@ -539,28 +523,47 @@ __device__ __forceinline__ void store_bf16_tile(const f32x16 (&acc)[TM][TN], bf1
     }
 }
 
-template <int BM, int BN, int WGM, int WGN, int DEPTH, bool A_KM, bool B_KM, class OutT, int G>
+template <int BM, int BN, int WGM, int WGN, int STAGES, bool A_KM, bool B_KM, class OutT, int G, int EPI>
 __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm2_kernel(Operand A, Operand B, ConvShape cs, OutT* __restrict__ C, int64_t ldc,
                                                                const float* __restrict__ bias, float* __restrict__ partial,
-                                                               int M, int N, int K, int k_per_split, int epilogue,
+                                                               int M, int N, int K, int k_per_split,
                                                                bf16_t* __restrict__ aux, int64_t ldaux, BatchArgs bt)
 {
-    constexpr int NT = 64 * WGM * WGN;
+    constexpr int NW = WGM * WGN;
     constexpr int WTM = BM / WGM, WTN = BN / WGN;
     constexpr int TM = WTM / 32, TN = WTN / 32;
-    constexpr int A_ELEMS = tile_elems<BM, A_KM>();
-    constexpr int STAGE = A_ELEMS + tile_elems<BN, B_KM>();
+    typedef typename TileSel<BM, NW, A_KM, G, true>::type TileA;
+    typedef typename TileSel<BN, NW, B_KM, G, false>::type TileB;
+    constexpr int STAGE = TileA::BYTES + TileB::BYTES, LPS = TileA::CH + TileB::CH;   // bytes and loads per wave of a stage
     extern __shared__ __align__(16) unsigned char smem[];
-    bf16_t* lds = reinterpret_cast<bf16_t*>(smem);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = (int)uni(tid >> 6);
     const int wm = wave / WGN, wn = wave % WGN;
-    const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
-    // blockIdx.z = K-slice, or (batch index, K-slice) for a batch of products of one shape
-    int zslice = blockIdx.z, zbatch = 0;
+    // Consecutive workgroups go to the 8 dies in turn, each with an L2 of its own: die x takes a run of consecutive
+    // tiles, slice (or batch member) by slice, and within a slice so that the tiles which share rows of the taller
+    // operand follow one another: those rows come through one L2 and at one time.
+    int tm = blockIdx.x, tn = blockIdx.y, tz = blockIdx.z;
+    if constexpr (G != GATHER_CONV_DGRAD) {
+        const uint32_t gx = gridDim.x, gy = gridDim.y, tiles = gx * gy, total = tiles * gridDim.z;
+        const uint32_t f = (blockIdx.z * gy + blockIdx.y) * gx + blockIdx.x;
+        const uint32_t die = f & 7u, per = total >> 3, more = total & 7u;
+        uint32_t t = die * per + min(die, more) + (f >> 3);
+        tz = (int)(t / tiles);
+        t -= (uint32_t)tz * tiles;
+        if (M >= N) {
+            tm = (int)(t / gy);
+            tn = (int)(t - (uint32_t)tm * gy);
+        } else {
+            tn = (int)(t / gx);
+            tm = (int)(t - (uint32_t)tn * gx);
+        }
+    }
+    const int m0 = tm * BM, n0 = tn * BN;
+    // z = K-slice, or (batch index, K-slice) for a batch of products of one shape
+    int zslice = tz, zbatch = 0;
     if constexpr (G == GATHER_NONE) {
         if (bt.batch > 1) {
-            zbatch = blockIdx.z / bt.nsplit;
-            zslice = blockIdx.z - zbatch * bt.nsplit;
+            zbatch = tz / bt.nsplit;
+            zslice = tz - zbatch * bt.nsplit;
             A.p += zbatch * bt.a_bs;
             B.p += zbatch * bt.b_bs;
             C += zbatch * bt.c_bs;
@@ -594,73 +597,117 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm2_kernel(Operand A, Ope
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-    typename TileSel<BM, NT, DEPTH, A_KM, G, true>::type ta;
-    typename TileSel<BN, NT, DEPTH, B_KM, G, false>::type tb;
-    ta.init(A, m0, tid, cs, K, kbeg);
-    tb.init(B, n0, tid, cs, K, kbeg);
-
-    int kt0 = 0;
-    if (nk >= 2 * DEPTH) {
-        // Long reductions.  Prologue and steady state are straight-line code: the loads of DEPTH steps
-        // are issued unconditionally and stay in flight from one iteration to the next (a branch in
-        // here makes the compiler wait for every outstanding load at the top of each step).
+    TileA ta;
+    TileB tb;
+    ta.init(A, m0, wave, lane, cs, K, kbeg);
+    tb.init(B, n0, wave, lane, cs, K, kbeg);
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
+    auto step = [&](int kt) {
+        ta.step(kbeg + kt * BK, kend);
+        tb.step(kbeg + kt * BK, kend);
+    };
+    auto load_one = [&](int d, int stage) {      // load d of the LPS of the step that step() named
+        if (d < TileA::CH) ta.one(d, lds0 + stage * STAGE, kend, wave);
+        else tb.one(d - TileA::CH, lds0 + stage * STAGE + TileA::BYTES, kend, wave);
+    };
 #pragma unroll
-        for (int d = 0; d < DEPTH; ++d) {
-            ta.load(d, kbeg + d * BK, kend, tid);
-            tb.load(d, kbeg + d * BK, kend, tid);
+    for (int s = 0; s < STAGES - 1; ++s)
+        if (s < nk) {
+            step(s);
+#pragma unroll
+            for (int d = 0; d < LPS; ++d) load_one(d, s);
         }
-        ta.template store<false>(0, lds, kbeg, kend, tid);
-        tb.template store<false>(0, lds + A_ELEMS, kbeg, kend, tid);
-        __syncthreads();
-        // Each step issues the loads of step +DEPTH, multiplies, and hands step +1 to LDS.
-        for (; kt0 + 2 * DEPTH <= nk; kt0 += DEPTH) {
+    Frag<BM, TM, A_KM> fa;
+    Frag<BN, TN, B_KM> fb;
+    fa.init(wm * WTM, lane);
+    fb.init(wn * WTN, lane);
+    bf16x8 a[2][TM], b[2][TN];
+    auto fetch = [&](int set, int stage, int kk) {
+        const char* at = reinterpret_cast<const char*>(smem) + stage * STAGE;
 #pragma unroll
-            for (int d = 0; d < DEPTH; ++d) {
-                const int kt = kt0 + d;
-                bf16_t* cur = lds + (kt & 1) * STAGE;
-                bf16_t* nxt = lds + ((kt + 1) & 1) * STAGE;
-                ta.load(d, kbeg + (kt + DEPTH) * BK, kend, tid);
-                tb.load(d, kbeg + (kt + DEPTH) * BK, kend, tid);
-                __builtin_amdgcn_sched_barrier(0);   // keep the loads first: the scheduler otherwise sinks them below the MFMAs
-                mma_step<TM, TN, A_KM, B_KM, BM + 16, BN + 16>(acc, cur, wm * WTM, cur + A_ELEMS, wn * WTN, lane);
-                ta.template store<false>((d + 1) % DEPTH, nxt, kbeg + (kt + 1) * BK, kend, tid);
-                tb.template store<false>((d + 1) % DEPTH, nxt + A_ELEMS, kbeg + (kt + 1) * BK, kend, tid);
-                __syncthreads();
+        for (int i = 0; i < TM; ++i) a[set][i] = fa.get(at, i, kk);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) b[set][j] = fb.get(at + TileA::BYTES, j, kk);
+    };
+    if constexpr (STAGES == 2) {
+        // Two or more workgroups per compute unit, which overlap one another: a step waits for its stage, starts the
+        // loads of the next one and multiplies.
+        for (int kt = 0; kt < nk; ++kt) {
+            wait_vm<0>();
+            lds_barrier();
+            if (kt + 1 < nk) {
+                step(kt + 1);
+#pragma unroll
+                for (int d = 0; d < LPS; ++d) load_one(d, (kt + 1) & 1);
+            }
+#pragma unroll
+            for (int kk = 0; kk < BK / 16; ++kk) {
+                fetch(kk & 1, kt & 1, kk);
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) acc[i][j] = mfma32(b[kk & 1][j], a[kk & 1][i], acc[i][j]);
             }
         }
-    } else {
+    } else if (nk > 0) {
+        // One workgroup per compute unit: its own waves have to keep the matrix pipes fed.  The fragments of a k-group are
+        // read while the one before is multiplied, across the barrier too, and the loads of step +STAGES - 1 are spread
+        // between the matrix instructions: issued in one go after the barrier, they held up every wave's fragment reads
+        // behind them (128 x 256 tiles, 16384 x 512 x 4096: 71 -> 62 us).
+        constexpr int MM = TM * TN, SPREAD = 3 * MM;      // the loads follow the first three k-groups
+        auto multiply = [&](int set, int kk, bool loads, int stage) {
 #pragma unroll
-        for (int d = 0; d < DEPTH; ++d)
-            if (d < nk) {
-                ta.load(d, kbeg + d * BK, kend, tid);
-                tb.load(d, kbeg + d * BK, kend, tid);
-            }
-        if (nk > 0) {
-            ta.template store<true>(0, lds, kbeg, kend, tid);
-            tb.template store<true>(0, lds + A_ELEMS, kbeg, kend, tid);
-        }
-        __syncthreads();
-    }
-    // Drain: the last (up to 2 * DEPTH - 1) steps, which stop loading and then stop storing.
-    for (; kt0 < nk; kt0 += DEPTH) {
+            for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int d = 0; d < DEPTH; ++d) {
-            const int kt = kt0 + d;
-            if (kt < nk) {
-                bf16_t* cur = lds + (kt & 1) * STAGE;
-                bf16_t* nxt = lds + ((kt + 1) & 1) * STAGE;
-                if (kt + DEPTH < nk) {
-                    ta.load(d, kbeg + (kt + DEPTH) * BK, kend, tid);
-                    tb.load(d, kbeg + (kt + DEPTH) * BK, kend, tid);
+                for (int j = 0; j < TN; ++j) {
+                    acc[i][j] = mfma32(b[set][j], a[set][i], acc[i][j]);
+                    if (loads) {
+#pragma unroll
+                        for (int d = 0; d < LPS; ++d)
+                            if (d * SPREAD / LPS == kk * MM + i * TN + j) {
+                                __builtin_amdgcn_sched_barrier(0);
+                                load_one(d, stage);
+                                __builtin_amdgcn_sched_barrier(0);
+                            }
+                    }
                 }
-                mma_step<TM, TN, A_KM, B_KM, BM + 16, BN + 16>(acc, cur, wm * WTM, cur + A_ELEMS, wn * WTN, lane);
-                if (kt + 1 < nk) {
-                    ta.template store<true>((d + 1) % DEPTH, nxt, kbeg + (kt + 1) * BK, kend, tid);
-                    tb.template store<true>((d + 1) % DEPTH, nxt + A_ELEMS, kbeg + (kt + 1) * BK, kend, tid);
-                }
-                __syncthreads();
-            }
-        }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto group = [&](int set, int stage, int kk) {
+            fetch(set, stage, kk);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        wait_stages<STAGES - 2, LPS>(nk - 1);
+        lds_barrier();
+        group(0, 0, 0);
+        int cur = 0, freed = STAGES - 1;      // `freed`: the stage read last, which the next loads may overwrite
+        auto body = [&](int kt, bool loads) {
+            const int nxt = cur + 1 == STAGES ? 0 : cur + 1;
+            if (loads) step(kt + STAGES - 1);
+            group(1, cur, 1);
+            multiply(0, 0, loads, freed);
+            group(0, cur, 2);
+            multiply(1, 1, loads, freed);
+            group(1, cur, 3);
+            multiply(0, 2, loads, freed);
+            if (loads) wait_vm<(STAGES - 2) * LPS>();
+            else wait_stages<STAGES - 2, LPS>(nk - 2 - kt);
+            lds_barrier();
+            group(0, nxt, 0);
+            multiply(1, 3, false, 0);
+            freed = cur;
+            cur = nxt;
+        };
+        int kt = 0;
+        for (; kt + STAGES - 1 < nk; ++kt) body(kt, true);
+        for (; kt + 1 < nk; ++kt) body(kt, false);
+        group(1, cur, 1);
+        multiply(0, 0, false, 0);
+        group(0, cur, 2);
+        multiply(1, 1, false, 0);
+        group(1, cur, 3);
+        multiply(0, 2, false, 0);
+        multiply(1, 3, false, 0);
     }
 
     const int r = lane & 31, h = lane >> 5;
@@ -684,8 +731,9 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm2_kernel(Operand A, Ope
                 }
         }
     } else {
-        store_bf16_tile<BM, BN, WGM, WGN, G == GATHER_CONV_DGRAD>(acc, lds, reinterpret_cast<bf16_t*>(C), ldc, bias, M, N, m0, n0,
-                                                                  epilogue, aux, ldaux, tid, cs);
+        lds_barrier();      // the staging tile overlays the operand stages
+        store_bf16_tile<BM, BN, WGM, WGN, G == GATHER_CONV_DGRAD, EPI>(acc, reinterpret_cast<bf16_t*>(smem), reinterpret_cast<bf16_t*>(C), ldc, bias, M, N, m0, n0,
+                                                                  aux, ldaux, tid, cs);
     }
 }
 
@@ -698,12 +746,13 @@ inline int effective_splits(const MatOp& op, int* k_per_split)
     return (int)ceil_div(op.K, kps);
 }
 
-template <int BM, int BN, int WGM, int WGN, int DEPTH, bool A_KM, bool B_KM, class OutT, int G = GATHER_NONE>
-hipError_t launch(const MatOp& op, const Operand& A, const Operand& B, hipStream_t st)
+template <int BM, int BN, int WGM, int WGN, int STAGES, bool A_KM, bool B_KM, class OutT, int G, int EPI>
+hipError_t launch_epi(const MatOp& op, const Operand& A, const Operand& B, hipStream_t st)
 {
     constexpr int NT = 64 * WGM * WGN;
-    constexpr int lds_bytes = gemm2_lds_bytes<BM, BN, A_KM, B_KM, OutT>();
-    auto kern = gemm2_kernel<BM, BN, WGM, WGN, DEPTH, A_KM, B_KM, OutT, G>;
+    constexpr int lds_bytes = gemm2_lds_bytes<BM, BN, STAGES, OutT>();
+    static_assert(lds_bytes <= 160 * 1024, "LDS of a compute unit");
+    auto kern = gemm2_kernel<BM, BN, WGM, WGN, STAGES, A_KM, B_KM, OutT, G, EPI>;
     static bool lds_allowed = false;
     if (!lds_allowed) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -729,7 +778,7 @@ hipError_t launch(const MatOp& op, const Operand& A, const Operand& B, hipStream
     dim3 grid((unsigned)ceil_div(op.M, BM), (unsigned)ceil_div(op.N, BN), (unsigned)(splits * bt.batch));
     if (G == GATHER_CONV_DGRAD && op.cs.cls) grid.z = (unsigned)(op.cs.stride * op.cs.stride);   // one slab of workgroups per parity class
     hipLaunchKernelGGL(kern, grid, dim3(NT), lds_bytes, st, A, B, op.cs, (OutT*)op.C, op.ldc, op.bias, partial, (int)op.M,
-                       (int)op.N, (int)op.K, kps, op.epilogue, (bf16_t*)op.aux, op.ldaux, bt);
+                       (int)op.N, (int)op.K, kps, (bf16_t*)op.aux, op.ldaux, bt);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     // a batch of sliced products is summed as one matrix of batch * M rows (supported() admits only dense results)
@@ -739,40 +788,54 @@ hipError_t launch(const MatOp& op, const Operand& A, const Operand& B, hipStream
     return hipSuccess;
 }
 
+// The activation epilogues exist for plain bf16 products (the only ones that carry one).
+template <int BM, int BN, int WGM, int WGN, int STAGES, bool A_KM, bool B_KM, class OutT, int G = GATHER_NONE>
+hipError_t launch(const MatOp& op, const Operand& A, const Operand& B, hipStream_t st)
+{
+    if constexpr (sizeof(OutT) == 2 && G == GATHER_NONE) {
+        if (op.epilogue == EPI_ACT_STORE) return launch_epi<BM, BN, WGM, WGN, STAGES, A_KM, B_KM, OutT, G, EPI_ACT_STORE>(op, A, B, st);
+        if (op.epilogue == EPI_ACT_GRAD) return launch_epi<BM, BN, WGM, WGN, STAGES, A_KM, B_KM, OutT, G, EPI_ACT_GRAD>(op, A, B, st);
+    }
+    return launch_epi<BM, BN, WGM, WGN, STAGES, A_KM, B_KM, OutT, G, EPI_NONE>(op, A, B, st);
+}
+
 inline bool al16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// Tile choice: the largest tile that still yields about one workgroup per compute unit.
+// Tile choice (see gemm_tile_cost for the figures behind it).
 template <bool A_KM, bool B_KM, class OutT, int G = GATHER_NONE>
 hipError_t by_tile(const MatOp& op, const Operand& A, const Operand& B, hipStream_t st)
 {
-    const int64_t splits = effective_splits(op, nullptr);
-    auto wgs = [&](int bm, int bn) { return ceil_div(op.M, bm) * ceil_div(op.N, bn) * splits * (G == GATHER_NONE ? op.batch : 1); };
-    // Large products in every layout: 256 x 256 tiles on eight waves (wave tile 128 x 64): half the operand
-    // bytes per flop from L2 into LDS of a 128 x 128 tile, and a quarter of the barriers.  16384 x 4096 x 4096:
-    // forward 551 -> 445 us, data gradient 609 -> 440 us, weight gradient 538 -> 407 us against 128 x 128 tiles.
-    if constexpr (G == GATHER_NONE && ((sizeof(OutT) == 2 && !A_KM) || (sizeof(OutT) == 4 && A_KM && B_KM))) {
-        // (a batch of weight gradients: from 128 tiles on, 213 against 368 us for 36 x [1024 x 256] over 8192 tokens)
-        const int64_t enough = (sizeof(OutT) == 4 && op.batch >= 8) ? 128 : 224;
-        // (not for results that fill less than two thirds of their 256 x 256 tiles: the 32 x 64 weight gradient of a
-        // 1x1 convolution has thousands of K-slices and would multiply 32 times its size)
-        const bool fills = 3 * op.M * op.N >= 2 * ceil_div(op.M, 256) * ceil_div(op.N, 256) * 65536;
-        if (op.K >= 1024 && fills && wgs(256, 256) >= enough) return launch<256, 256, 2, 4, 2, A_KM, B_KM, OutT>(op, A, B, st);
-    }
+    const int64_t splits = effective_splits(op, nullptr), batch = G == GATHER_NONE ? op.batch : 1;
+    auto wgs = [&](int bm, int bn) { return ceil_div(op.M, bm) * ceil_div(op.N, bn) * splits * batch; };
+    constexpr bool WGRAD = sizeof(OutT) == 4 && A_KM;
     // Results at most 32 columns wide (1x1 and core convolutions at Tucker ranks <= 32): a 128 x 32 tile
     // does a quarter of the MFMA and LDS work of a 128 x 128 one (15 against 23 us at 401408 x 32 x 64).
-    if constexpr (sizeof(OutT) == 2 && !A_KM && G != GATHER_CONV_WGRAD) {
-        if (op.N <= 32 && wgs(128, 32) >= 256) return launch<128, 32, 4, 1, 2, false, B_KM, OutT, G>(op, A, B, st);
-    }
-    if (op.M > 64 && op.N > 64 && (wgs(128, 128) >= 200 || wgs(64, 64) > 2048)) {
-        // Short reductions with bf16 results (K = rank: second product of a forward pair or of a data
-        // gradient) are dominated by the epilogue; eight waves per tile overlap it better than four
-        // (31.8 against 36.0 us at 8192 x 3072 x 192 with the GELU epilogue).
-        if constexpr (sizeof(OutT) == 2 && !A_KM && G == GATHER_NONE) {
-            if (op.K <= 4 * BK) return launch<128, 128, 2, 4, 2, A_KM, B_KM, OutT, G>(op, A, B, st);
+    if constexpr (sizeof(OutT) == 2 && G != GATHER_CONV_WGRAD) {
+        if (op.N <= 32 && wgs(128, 32) >= 256) {
+            if (op.K <= 2 * BK) return launch<128, 32, 4, 1, 2, A_KM, B_KM, OutT, G>(op, A, B, st);
+            return launch<128, 32, 4, 1, 4, A_KM, B_KM, OutT, G>(op, A, B, st);
         }
-        return launch<128, 128, 2, 2, 2, A_KM, B_KM, OutT, G>(op, A, B, st);
     }
-    return launch<64, 64, 2, 2, 2, A_KM, B_KM, OutT, G>(op, A, B, st);
+    // Short reductions (K = rank: second product of a forward pair or of a data gradient) are mostly prologue and
+    // epilogue: two workgroups per compute unit, two stages each, overlap them (8192 x 4096 x 256: 27.8 us, against
+    // 30 us with 128 x 256 tiles in three stages, one workgroup per unit); eight waves per tile do so better than four.
+    if (!WGRAD && op.K <= 8 * BK) {
+        if (op.M > 64 && op.N > 64 && (wgs(128, 128) >= 200 || wgs(64, 64) > 2048))
+            return launch<128, 128, 2, 4, 2, A_KM, B_KM, OutT, G>(op, A, B, st);
+        if (op.K <= 4 * BK) return launch<64, 64, 2, 2, 2, A_KM, B_KM, OutT, G>(op, A, B, st);
+        return launch<64, 64, 2, 2, 4, A_KM, B_KM, OutT, G>(op, A, B, st);
+    }
+    switch (gemm_best_tile(op.M, op.N, op.K, splits, batch, G != GATHER_NONE ? COST_GATHER : WGRAD ? COST_WGRAD : COST_PLAIN)) {
+    case TILE_256x256:
+        if constexpr (G == GATHER_NONE) return launch<256, 256, 2, 4, 2, A_KM, B_KM, OutT, G>(op, A, B, st);
+        [[fallthrough]];
+    case TILE_128x256: return launch<128, 256, 2, 4, 3, A_KM, B_KM, OutT, G>(op, A, B, st);
+    case TILE_128x128: return launch<128, 128, 2, 4, 4, A_KM, B_KM, OutT, G>(op, A, B, st);
+    case TILE_128x128_PAIR: return launch<128, 128, 2, 4, 2, A_KM, B_KM, OutT, G>(op, A, B, st);
+    case TILE_64x128: return launch<64, 128, 2, 4, 4, A_KM, B_KM, OutT, G>(op, A, B, st);
+    case TILE_128x64: return launch<128, 64, 4, 2, 4, A_KM, B_KM, OutT, G>(op, A, B, st);
+    default: return launch<64, 64, 2, 2, 4, A_KM, B_KM, OutT, G>(op, A, B, st);
+    }
 }
 
 }  // namespace
@@ -794,8 +857,10 @@ bool mfma_gemm2_supported(const MatOp& op)
     } else {
         // implicit-GEMM convolution: channel counts must keep every 16-byte chunk inside one tap
         if (op.cs.I % 8 != 0 || op.cs.O % 8 != 0 || op.cs.k < 1 || op.cs.k > 31 || op.cs.stride < 1) return false;
-        if ((int64_t)op.cs.N * op.cs.H * op.cs.W * op.cs.I >= (int64_t(1) << 31)) return false;
-        if ((int64_t)op.cs.N * op.cs.Ho * op.cs.Wo * op.cs.O >= (int64_t(1) << 31)) return false;
+        // byte offsets below BUF_OOB
+        const int64_t most = (int64_t(1) << 31) - 16;
+        if ((int64_t)op.cs.N * op.cs.H * op.cs.W * op.cs.I >= most || (int64_t)op.cs.N * op.cs.Ho * op.cs.Wo * op.cs.O >= most) return false;
+        if ((int64_t)op.cs.O * op.cs.k * op.cs.k * op.cs.I >= most) return false;
         if (op.gather == GATHER_CONV_FWD) {
             akm = false; bkm = false;
             if (op.b_sk != 1 || op.b_sn % 8 != 0) return false;
@@ -829,7 +894,7 @@ bool mfma_gemm2_supported(const MatOp& op)
         if (op.splits > 1 && op.partial && (!op.out_f32 || op.ldc != op.N || op.c_bs != op.M * op.N)) return false;
     }
     if (op.gather == GATHER_NONE && ((akm ? op.a_sk : op.a_sm) > BUF_MAX_LD || (bkm ? op.b_sk : op.b_sn) > BUF_MAX_LD)) return false;
-    if (op.epilogue != EPI_NONE && (op.out_f32 || !op.aux || !al16(op.aux) || op.ldaux % 8 != 0)) return false;
+    if (op.epilogue != EPI_NONE && (op.out_f32 || op.gather != GATHER_NONE || !op.aux || !al16(op.aux) || op.ldaux % 8 != 0)) return false;
     return true;
 }
 
