@@ -524,7 +524,7 @@ __device__ __forceinline__ void store_bf16_tile(const f32x16 (&acc)[TM][TN], bf1
 }
 
 template <int BM, int BN, int WGM, int WGN, int STAGES, bool A_KM, bool B_KM, class OutT, int G, int EPI>
-__global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm2_kernel(Operand A, Operand B, ConvShape cs, OutT* __restrict__ C, int64_t ldc,
+__global__ __launch_bounds__(64 * WGM * WGN, STAGES == 1 ? 6 : 2) void gemm2_kernel(Operand A, Operand B, ConvShape cs, OutT* __restrict__ C, int64_t ldc,
                                                                const float* __restrict__ bias, float* __restrict__ partial,
                                                                int M, int N, int K, int k_per_split,
                                                                bf16_t* __restrict__ aux, int64_t ldaux, BatchArgs bt)
@@ -629,7 +629,26 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm2_kernel(Operand A, Ope
 #pragma unroll
         for (int j = 0; j < TN; ++j) b[set][j] = fb.get(at + TileA::BYTES, j, kk);
     };
-    if constexpr (STAGES == 2) {
+    if constexpr (STAGES == 1) {
+        // Three or more workgroups per compute unit, so that nothing needs to overlap inside one (80 registers per lane
+        // at most: six waves per SIMD).
+        for (int kt = 0; kt < nk; ++kt) {
+            if (kt > 0) lds_barrier();
+            step(kt);
+#pragma unroll
+            for (int d = 0; d < LPS; ++d) load_one(d, 0);
+            wait_vm<0>();
+            lds_barrier();
+#pragma unroll
+            for (int kk = 0; kk < BK / 16; ++kk) {
+                fetch(kk & 1, 0, kk);
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) acc[i][j] = mfma32(b[kk & 1][j], a[kk & 1][i], acc[i][j]);
+            }
+        }
+    } else if constexpr (STAGES == 2) {
         // Two or more workgroups per compute unit, which overlap one another: a step waits for its stage, starts the
         // loads of the next one and multiplies.
         for (int kt = 0; kt < nk; ++kt) {
@@ -812,16 +831,31 @@ hipError_t by_tile(const MatOp& op, const Operand& A, const Operand& B, hipStrea
     // does a quarter of the MFMA and LDS work of a 128 x 128 one (15 against 23 us at 401408 x 32 x 64).
     if constexpr (sizeof(OutT) == 2 && G != GATHER_CONV_WGRAD) {
         if (op.N <= 32 && wgs(128, 32) >= 256) {
+            if (op.K <= BK) return launch<128, 32, 4, 1, 1, A_KM, B_KM, OutT, G>(op, A, B, st);
             if (op.K <= 2 * BK) return launch<128, 32, 4, 1, 2, A_KM, B_KM, OutT, G>(op, A, B, st);
             return launch<128, 32, 4, 1, 4, A_KM, B_KM, OutT, G>(op, A, B, st);
         }
     }
     // Short reductions (K = rank: second product of a forward pair or of a data gradient) are mostly prologue and
-    // epilogue: two workgroups per compute unit, two stages each, overlap them (8192 x 4096 x 256: 27.8 us, against
-    // 30 us with 128 x 256 tiles in three stages, one workgroup per unit); eight waves per tile do so better than four.
+    // epilogue, which only other workgroups on the unit can overlap; eight waves per tile do so better than four.
     if (!WGRAD && op.K <= 8 * BK) {
-        if (op.M > 64 && op.N > 64 && (wgs(128, 128) >= 200 || wgs(64, 64) > 2048))
+        if (op.M > 64 && op.N > 64 && (wgs(128, 128) >= 200 || wgs(64, 64) > 2048)) {
+            if constexpr (sizeof(OutT) == 2 && G == GATHER_NONE) {
+                // From three rounds on, 256 x 256 tiles where the multiplication weighs more (16384 x 4096 x 512: 80 us,
+                // 83 us in the next kind, 90 us in the last); else one stage and three workgroups per unit, against two
+                // stages and two of them: 8192 x 4096 x 256 29.0 -> 27.9 us, with GELU 37.3 -> 35.8 us, with its
+                // gradient 44.8 -> 40.8 us.  Below three workgroups per unit two stages are faster (8192 x 1024 x 256:
+                // 7.9 against 8.2 us), and over K = 192 with the GELU epilogue (25.8 against 27.6 us; its gradient
+                // 32.0 -> 28.5 us all the same).
+                if (op.K > 6 * BK && op.M > 192 && op.N > 192 && wgs(256, 256) >= 768)
+                    return launch<256, 256, 2, 4, 2, A_KM, B_KM, OutT, G>(op, A, B, st);
+                if (wgs(128, 128) > 768 && (op.K > 3 * BK || op.epilogue == EPI_ACT_GRAD))
+                    return launch<128, 128, 2, 4, 1, A_KM, B_KM, OutT, G>(op, A, B, st);
+            }
             return launch<128, 128, 2, 4, 2, A_KM, B_KM, OutT, G>(op, A, B, st);
+        }
+        // a single K-step needs a single stage: 401408 x 64 x 32 15.1 -> 13.0 us
+        if (op.K <= BK) return launch<64, 64, 2, 2, 1, A_KM, B_KM, OutT, G>(op, A, B, st);
         if (op.K <= 4 * BK) return launch<64, 64, 2, 2, 2, A_KM, B_KM, OutT, G>(op, A, B, st);
         return launch<64, 64, 2, 2, 4, A_KM, B_KM, OutT, G>(op, A, B, st);
     }
