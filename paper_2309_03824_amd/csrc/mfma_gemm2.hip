@@ -843,13 +843,14 @@ hipError_t by_tile(const MatOp& op, const Operand& A, const Operand& B, hipStrea
             if constexpr (sizeof(OutT) == 2 && G == GATHER_NONE) {
                 // From three rounds on, 256 x 256 tiles where the multiplication weighs more (16384 x 4096 x 512: 80 us,
                 // 83 us in the next kind, 90 us in the last); else one stage and three workgroups per unit, against two
-                // stages and two of them: 8192 x 4096 x 256 29.0 -> 27.9 us, with GELU 37.3 -> 35.8 us, with its
-                // gradient 44.8 -> 40.8 us.  Below three workgroups per unit two stages are faster (8192 x 1024 x 256:
-                // 7.9 against 8.2 us), and over K = 192 with the GELU epilogue (25.8 against 27.6 us; its gradient
-                // 32.0 -> 28.5 us all the same).
+                // stages and two of them: 4100 x 4096 x 264 22.6 -> 20.5 us, 8192 x 4096 x 256 with the GELU gradient
+                // 47.3 -> 43.8 us inside the encoder step.  Two stages stay faster below three workgroups per unit
+                // (8192 x 1024 x 256: 7.9 against 8.2 us) and up to K = 256 without that gradient's second operand to
+                // wait for (in the same step, with GELU 40.3 against 41.6 us, three members of 1024 columns 24.1
+                // against 26.3 us).
                 if (op.K > 6 * BK && op.M > 192 && op.N > 192 && wgs(256, 256) >= 768)
                     return launch<256, 256, 2, 4, 2, A_KM, B_KM, OutT, G>(op, A, B, st);
-                if (wgs(128, 128) > 768 && (op.K > 3 * BK || op.epilogue == EPI_ACT_GRAD))
+                if (wgs(128, 128) > 768 && (op.K > 4 * BK || op.epilogue == EPI_ACT_GRAD))
                     return launch<128, 128, 2, 4, 1, A_KM, B_KM, OutT, G>(op, A, B, st);
             }
             return launch<128, 128, 2, 4, 2, A_KM, B_KM, OutT, G>(op, A, B, st);
