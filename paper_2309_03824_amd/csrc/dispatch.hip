@@ -1,5 +1,4 @@
 // Engine selection for a single matrix product and the split-K policy.
-#include <algorithm>
 #include <atomic>
 #include <cstdio>
 #include <mutex>
@@ -49,33 +48,15 @@ GemmTile gemm_best_tile(int64_t M, int64_t N, int64_t K, int64_t splits, int64_t
     return (GemmTile)best;
 }
 
-namespace {
-// Slices of K for a weight gradient: the count (among those that make one or two rounds of some tile) with the least
-// cost, slices costing the partial sums' way to memory and back (about 4 TB/s) and a second kernel (4 us).
-int wgrad_splits(int64_t M, int64_t N, int64_t K, int64_t batch, int64_t most, GemmCost kind)
-{
-    int64_t best = 1;
-    float least = 3e38f;
-    for (int i = 0; i < GEMM_TILES; ++i) {
-        const int64_t tiles = ceil_div(M, TILES[i].bm) * ceil_div(N, TILES[i].bn) * batch;
-        for (int64_t s : {int64_t(1), 256 / tiles, 256 * TILES[i].per_cu / tiles}) {
-            s = std::min(s, most);
-            if (s < 1) continue;
-            const float c = gemm_tile_cost(TILES[i], M, N, K, s, batch, kind) +
-                            (s > 1 ? 4.f + (float)s * (float)batch * (float)M * (float)N * 8.f / 4e6f : 0.f);
-            if (c < least) { least = c; best = s; }
-        }
-    }
-    return (int)best;
-}
-}  // namespace
-
 // Weight-gradient products have a long K (tokens or pixels) and a small output; K is cut into slices so that the
-// launch fills the chip.  The count depends only on the shape, so workspace queries and launches agree.  (3072 x 192
-// over 8192: 3 slices, 21.4 us with the sum; 10 slices of 128 x 128 tiles took 25 us; 1024 x 256 over 8192: 4 slices
-// of 64 x 64 tiles, 13.8 us, against 18.8 us in 16.)  Never more slices than the bound below, at which the scratch
-// of callers with a fixed amount of it was set.
-int choose_splits(int64_t M, int64_t N, int64_t K, bool in_bf16, bool gather)
+// launch has enough workgroups to fill 256 compute units about twice over in 128 x 128 or 64 x 64 tiles.  The count
+// depends only on the shape, is the same for every engine and never falls as K grows, so that workspace queries,
+// launches and smaller batches agree.  It also bounds the error: each slice is a chain of fp32 additions, and the
+// relative error goes with the root of the chain's length.  Fewer slices (what the tiles of the MFMA engine alone would
+// like best: 3072 x 192 over 8192 in 3, 4096 x 256 over 4096 in one) are up to a fifth faster there, 32.8 -> 30.7 us and
+// 32.4 -> 26.4 us with the sum, but take the error against 64 bits from 1.7e-7 to 3.2e-7 and from 1.4e-7 to 4.0e-7, and
+// leave the engine for unaligned sizes with too few workgroups (1001 x 1003 over 4000 in 8 slices 146 us, in one 772 us).
+int choose_splits(int64_t M, int64_t N, int64_t K)
 {
     const int64_t t128 = ceil_div(M, 128) * ceil_div(N, 128);
     const int64_t t64 = ceil_div(M, 64) * ceil_div(N, 64);
@@ -83,8 +64,7 @@ int choose_splits(int64_t M, int64_t N, int64_t K, bool in_bf16, bool gather)
     const int64_t by_k = K / 256;          // keep at least 256 reduction steps per slice
     if (s > by_k) s = by_k;
     if (s > 512) s = 512;
-    if (s < 2) return 1;
-    return in_bf16 ? wgrad_splits(M, N, K, 1, s, gather ? COST_GATHER : COST_WGRAD) : (int)s;
+    return s < 2 ? 1 : (int)s;
 }
 
 // Products whose result is a [tokens x r] activation (H = X.V^T, dH = dY.U) have few output tiles
@@ -104,8 +84,9 @@ int choose_splits_act(int64_t M, int64_t N, int64_t K, bool in_bf16)
     return s < 2 ? 1 : (int)s;
 }
 
-// Weight gradients of `batch` layers of one shape in one launch: the tiles of a dozen members nearly fill the chip,
-// K is sliced only where that is cheaper all the same.
+// Weight gradients of `batch` layers of one shape in one launch: 256 x 256 tiles over all members already give most
+// compute units a workgroup when there are a dozen layers; K is sliced only while they do not.  (12 x [1024 x 256] over
+// 8192: 88.6 us in 4 slices, error 2.7e-7; 85.8 us in 2, error 4.0e-7.)
 int choose_splits_batched(int64_t M, int64_t N, int64_t K, int64_t batch)
 {
     const int64_t tiles = ceil_div(M, 256) * ceil_div(N, 256) * batch;
@@ -113,7 +94,7 @@ int choose_splits_batched(int64_t M, int64_t N, int64_t K, int64_t batch)
     const int64_t by_k = K / 512;
     if (s > by_k) s = by_k;
     if (s > 64) s = 64;
-    return s < 2 ? 1 : wgrad_splits(M, N, K, batch, s, COST_WGRAD);
+    return s < 2 ? 1 : (int)s;
 }
 
 namespace {

@@ -108,9 +108,9 @@ MatOp tn(const void* A, int64_t lda, const void* B, int64_t ldb, float* C, int64
     return op;
 }
 
-size_t partial_bytes(int64_t M, int64_t N, int64_t K, lrd_dtype dt, bool gather = false)
+size_t partial_bytes(int64_t M, int64_t N, int64_t K)
 {
-    int s = choose_splits(M, N, K, dt == LRD_BF16, gather);
+    int s = choose_splits(M, N, K);
     return s > 1 ? round256((size_t)s * (size_t)M * (size_t)N * sizeof(float)) : 0;
 }
 
@@ -127,13 +127,13 @@ size_t linear_partial_region(int64_t T, int64_t in, int64_t out, int64_t r, lrd_
     const size_t h = act_partial_bytes(T, r, in, dt);   // H = X.V^T (forward, or recomputed in the backward)
     if (!backward) return h;
     return std::max(std::max(h, act_partial_bytes(T, r, out, dt)),
-                    std::max(partial_bytes(out, r, T, dt), partial_bytes(r, in, T, dt)));
+                    std::max(partial_bytes(out, r, T), partial_bytes(r, in, T)));
 }
 
 enum SplitKind { SPLIT_WGRAD, SPLIT_ACT };
 void share_splits(MatOp& op, void* region, lrd_dtype dt, SplitKind kind)
 {
-    int s = kind == SPLIT_WGRAD ? choose_splits(op.M, op.N, op.K, dt == LRD_BF16)
+    int s = kind == SPLIT_WGRAD ? choose_splits(op.M, op.N, op.K)
                                 : choose_splits_act(op.M, op.N, op.K, dt == LRD_BF16);
     if (s > 1 && region) {
         op.partial = (float*)region;
@@ -141,9 +141,9 @@ void share_splits(MatOp& op, void* region, lrd_dtype dt, SplitKind kind)
     }
 }
 
-void attach_splits(MatOp& op, Carver& cv, lrd_dtype dt)
+void attach_splits(MatOp& op, Carver& cv)
 {
-    int s = choose_splits(op.M, op.N, op.K, dt == LRD_BF16, op.gather != GATHER_NONE);
+    int s = choose_splits(op.M, op.N, op.K);
     if (s > 1) {
         op.partial = (float*)cv.take((size_t)s * (size_t)op.M * (size_t)op.N * sizeof(float));
         op.splits = op.partial ? s : 1;
@@ -547,7 +547,7 @@ size_t group_partial_region(int64_t T, int64_t in, int64_t out, int64_t r, int32
     if (!backward) return h;
     // the groups' second-factor gradients are one batched product: G sets of slices side by side
     return std::max(std::max(h, act_partial_bytes(T, r, out, dt)),
-                    std::max((size_t)G * partial_bytes(out, r, T, dt), partial_bytes(G * r, in, T, dt)));
+                    std::max((size_t)G * partial_bytes(out, r, T), partial_bytes(G * r, in, T)));
 }
 }  // namespace
 
@@ -804,7 +804,7 @@ lrd_status lrd_linear_wgrad_batched(const void* dY, int64_t dy_stride, const voi
 size_t lrd_dense_linear_workspace_bytes(int64_t T, int64_t in, int64_t out, lrd_dtype dt)
 {
     if (!dtype_ok(dt) || T < 1 || in < 1 || out < 1) return 0;
-    return partial_bytes(out, in, T, dt);
+    return partial_bytes(out, in, T);
 }
 
 lrd_status lrd_dense_linear_fwd(const void* X, const void* W, const float* bias, void* Y, int64_t T,
@@ -832,7 +832,7 @@ lrd_status lrd_dense_linear_bwd(const void* dY, const void* X, const void* W, vo
     MatOp wg;
     if (dW) {
         wg = tn(dY, out, X, in, dW, in, out, in, T, dt);
-        attach_splits(wg, cv, dt);
+        attach_splits(wg, cv);
         if (!cv.ok) return LRD_ERR_WORKSPACE;
     }
     if (dX) LRD_TRY(run_matop(nn(dY, out, W, in, dX, in, T, in, out, dt), st));
@@ -886,8 +886,8 @@ size_t lrd_tucker_conv_workspace_bytes(const lrd_conv_geom* g, lrd_dtype dt, uin
     size_t pin = (size_t)g->N * g->H * g->W, pout = (size_t)g->N * cs.Ho * cs.Wo;
     size_t a = round256(pin * g->r1 * esize(dt)), b = round256(pout * g->r2 * esize(dt));
     size_t kk = (size_t)g->k * g->k;
-    size_t part = std::max(std::max(partial_bytes(g->S, g->r2, pout, dt), partial_bytes(g->r2, kk * g->r1, pout, dt, true)),
-                           partial_bytes(g->r1, g->C, pin, dt));
+    size_t part = std::max(std::max(partial_bytes(g->S, g->r2, pout), partial_bytes(g->r2, kk * g->r1, pout)),
+                           partial_bytes(g->r1, g->C, pin));
     part = std::max(part, round256(conv_direct_wgrad_bytes(cs, dt == LRD_BF16)));
     // forward: A and B when not side-stored; backward: dA, dB, recomputed A and B, partials, and the
     // flipped core weights of a stride-1 data gradient
@@ -1012,7 +1012,7 @@ lrd_status tucker_bwd_impl(const void* dY, const void* X, const void* A, const v
     float* shared_partial = nullptr;
     size_t shared_bytes = 0;
     auto splits_for = [&](MatOp& op) {
-        int s = choose_splits(op.M, op.N, op.K, dt == LRD_BF16, op.gather != GATHER_NONE);
+        int s = choose_splits(op.M, op.N, op.K);
         if (s <= 1) return;
         size_t need = (size_t)s * op.M * op.N * sizeof(float);
         if (need > shared_bytes) return;
@@ -1026,8 +1026,8 @@ lrd_status tucker_bwd_impl(const void* dY, const void* X, const void* A, const v
     }
     if (t1) w1 = tn(dA, r1, X, C, dP1, C, r1, C, pin, dt);
     // one partial buffer, sized for the largest of the three products, used by them in turn
-    shared_bytes = std::max(std::max(t2 ? partial_bytes(S, r2, pout, dt) : 0, tg ? partial_bytes(r2, kk * r1, pout, dt, true) : 0),
-                            t1 ? partial_bytes(r1, C, pin, dt) : 0);
+    shared_bytes = std::max(std::max(t2 ? partial_bytes(S, r2, pout) : 0, tg ? partial_bytes(r2, kk * r1, pout) : 0),
+                            t1 ? partial_bytes(r1, C, pin) : 0);
     if (tg) shared_bytes = std::max(shared_bytes, round256(conv_direct_wgrad_bytes(cs, dt == LRD_BF16)));
     if (shared_bytes) shared_partial = (float*)cv.take(shared_bytes);
     const size_t flip_bytes = need_dA ? conv_dgrad_flip_bytes(cs, dt == LRD_BF16) : 0;
@@ -1082,7 +1082,7 @@ size_t lrd_dense_conv_workspace_bytes(const lrd_conv_geom* g, lrd_dtype dt)
 {
     if (!dtype_ok(dt) || !geom_ok(g, false)) return 0;
     ConvShape cs = core_shape(*g, g->C, g->S);
-    return std::max(partial_bytes(g->S, (int64_t)g->k * g->k * g->C, g->N * (int64_t)cs.Ho * cs.Wo, dt, true),
+    return std::max(partial_bytes(g->S, (int64_t)g->k * g->k * g->C, g->N * (int64_t)cs.Ho * cs.Wo),
                     round256(conv_direct_wgrad_bytes(cs, dt == LRD_BF16))) +
            round256(conv_dgrad_flip_bytes(cs, dt == LRD_BF16));
 }
@@ -1125,7 +1125,7 @@ lrd_status lrd_dense_conv_bwd(const void* dY, const void* X, const void* W, void
             wg.scratch = cv.take(direct);
             wg.scratch_bytes = direct;
         } else {
-            attach_splits(wg, cv, dt);
+            attach_splits(wg, cv);
         }
         if (!cv.ok) return LRD_ERR_WORKSPACE;
     }

@@ -92,7 +92,7 @@ hipError_t run_matop(const MatOp& op, hipStream_t st);              // picks an 
 hipError_t apply_epilogue(const MatOp& op, hipStream_t st);        // unfused form of MatOp::epilogue
 
 // Workspace floats a MatOp of this shape needs for split-K (0 if it will not be split).
-int choose_splits(int64_t M, int64_t N, int64_t K, bool in_bf16, bool gather = false);
+int choose_splits(int64_t M, int64_t N, int64_t K);
 // Split-K count for a product whose result is a narrow bf16 activation (1 = not split).
 int choose_splits_act(int64_t M, int64_t N, int64_t K, bool in_bf16);
 int choose_splits_batched(int64_t M, int64_t N, int64_t K, int64_t batch);

@@ -1,0 +1,51 @@
+"""The fp32 sums of bf16 weight gradients: their error against 64 bits is that of the slices that the reduction is cut
+into, on the aligned and the unaligned engine, for one layer and for a batch."""
+import math
+
+import pytest
+import torch
+
+from paper_2309_03824_amd import binding as lrd
+
+pytestmark = pytest.mark.gpu
+BF = torch.bfloat16
+
+
+def bound(K, slices):
+    """Relative error (2-norm) of a sum of K random products in `slices` chains, one fp32 addition per 16 products
+    (the depth of a matrix instruction).  An addition's error is at most 2^-24 / sqrt(3) of the running sum in the root
+    mean square; the running sum of i products has variance i, so n additions give n / 2 of its square per chain, the
+    sum over the chains slices / 2.  Chains are whole steps of 64."""
+    n = math.ceil(math.ceil(K / slices) / 64) * 64 / 16
+    return 2.0 ** -24 / math.sqrt(3) * math.sqrt((n + slices) / 2)
+
+
+def normal(gen, *shape):
+    return torch.randn(*shape, device="cuda", generator=gen).to(BF)
+
+
+# (rows and columns of the gradient, tokens, slices): at least 480 workgroups of 128 x 128 tiles (432 of 64 x 64) or 256
+# tokens a slice
+@pytest.mark.parametrize("M,N,K,slices", [(4096, 256, 4096, 8), (3072, 192, 8192, 10), (192, 768, 8192, 12), (264, 1024, 4100, 16),
+                                          (2048, 104, 4099, 7), (1001, 1003, 4000, 8), (1001, 192, 8192, 9)])
+def test_weight_gradient_error(M, N, K, slices):
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    dY, X, W = normal(gen, K, M), normal(gen, K, N), normal(gen, M, N)
+    dW = torch.full((M, N), float("nan"), device="cuda")
+    ws = torch.empty(max(lrd.dense_linear_workspace_bytes(K, N, M, lrd.BF16), 256), dtype=torch.uint8, device="cuda")
+    lrd.dense_linear_bwd(dY, X, W, None, dW, ws)
+    torch.cuda.synchronize()
+    ref = dY.double().t().contiguous() @ X.double()
+    assert ((dW - ref).norm() / ref.norm()).item() <= bound(K, slices)
+
+
+@pytest.mark.parametrize("L,M,N,K,slices", [(12, 1024, 256, 8192, 4), (4, 2048, 128, 4096, 7), (3, 520, 136, 8000, 15)])
+def test_batched_weight_gradient_error(L, M, N, K, slices):
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    dY, H = normal(gen, L, K, M), normal(gen, L, K, N)
+    dU = torch.full((L, M, N), float("nan"), device="cuda")
+    ws = torch.empty(max(lrd.linear_wgrad_batched_workspace_bytes(L, K, M, M, N, lrd.BF16, lrd.FREEZE_L0), 256), dtype=torch.uint8, device="cuda")
+    lrd.linear_wgrad_batched(dY, H, None, None, None, dU, lrd.FREEZE_L0, ws)
+    torch.cuda.synchronize()
+    ref = torch.stack([dY[l].double().t().contiguous() @ H[l].double() for l in range(L)])
+    assert ((dU - ref).norm() / ref.norm()).item() <= bound(K, slices)
