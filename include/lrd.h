@@ -27,7 +27,9 @@
  *     activation outputs (Y, dX, H_save, ...) are bfloat16, weight gradients are fp32.
  *     dtype LRD_F32: everything is fp32.
  *   - The caller owns every buffer, including the workspace `ws` (size from the matching
- *     *_workspace_bytes query; may be NULL when that query returns 0).  The library keeps no
+ *     *_workspace_bytes query; may be NULL when that query returns 0).  The queries of the layer
+ *     passes never fall as the token count T or the image count N grows, so a workspace for the
+ *     largest batch serves every smaller one of the same layer.  The library keeps no
  *     device memory and the calls declared here keep no mutable state between calls (the
  *     measurement aids of lrd_measure.h, a separate header, are the exception and say so).
  *   - Work is enqueued on `hip_stream` (a hipStream_t passed as void*, NULL = default stream).
@@ -140,7 +142,7 @@ lrd_status lrd_select_rank(const double* times, int32_t r_min, int32_t r_max, do
  * ---------------------------------------------------------------------------------------- */
 
 /* Bytes of workspace lrd_linear_fwd / lrd_linear_bwd need for these sizes (upper bound over
- * every nullable-argument combination).  0 on bad arguments. */
+ * every nullable-argument combination and every token count up to T).  0 on bad arguments. */
 size_t lrd_linear_workspace_bytes(int64_t T, int64_t in, int64_t out, int64_t r, lrd_dtype dt,
                                   uint32_t freeze_mask);
 
@@ -175,8 +177,9 @@ lrd_status lrd_linear_bwd(const void* dY, const void* X, const void* H, const vo
  * the library instead of a caller workspace.
  *   - The array holds LRD_STATIC_SCRATCH_BYTES (64 MiB) on every GPU the library is used on, from
  *     the first call on that GPU until the process ends.
- *   - A shape whose lrd_linear_workspace_bytes exceeds that size is rejected with
- *     LRD_ERR_WORKSPACE before anything is launched (lrd_linear_bwd_static_fits tells in advance).
+ *   - A shape that needs more than that is rejected with LRD_ERR_WORKSPACE before anything is
+ *     launched (lrd_linear_bwd_static_fits tells in advance; a shape whose
+ *     lrd_linear_workspace_bytes does not exceed it always fits).
  *   - The call allocates nothing and frees nothing; the first call on a device looks up the
  *     array's address (no allocation either).
  *   - All calls on one GPU share the array and it keeps the previous call's contents; every region

@@ -434,6 +434,12 @@ size_t conv_direct_wgrad_bytes(const ConvShape& cs, bool bf16)
     return (size_t)slices * 9 * cs.I * cs.O * sizeof(float);
 }
 
+size_t conv_direct_wgrad_bytes_up_to(const ConvShape& cs, bool bf16)
+{
+    // 256 tiles make 256 slices, 257 of them 129
+    return bf16 && shape_ok(cs) ? (size_t)std::min<int64_t>(tiling(cs.N, cs.Ho, cs.Wo).ntiles, 256) * 9 * cs.I * cs.O * sizeof(float) : 0;
+}
+
 bool conv_direct_supported(const MatOp& op)
 {
     if (op.gather == GATHER_NONE || !op.in_bf16 || op.bias || op.epilogue != EPI_NONE || !shape_ok(op.cs)) return false;

@@ -114,19 +114,31 @@ size_t partial_bytes(int64_t M, int64_t N, int64_t K)
     return s > 1 ? round256((size_t)s * (size_t)M * (size_t)N * sizeof(float)) : 0;
 }
 
-// The same for a product whose result is a narrow activation.
-size_t act_partial_bytes(int64_t M, int64_t N, int64_t K, lrd_dtype dt)
+// What a call takes of the workspace for exactly its tokens, or what a size query promises: enough for them and for
+// every smaller number (a last batch runs in the workspace of the others).
+enum Tokens { THESE, UP_TO };
+
+// The same for a product whose result is a narrow activation.  Fewer tokens are cut into more slices, so the bytes
+// rise and fall with the tokens; the slices change only from one row of 64 x 64 tiles to the next, and from 256 tiles on
+// there are none.
+size_t act_partial_bytes(int64_t M, int64_t N, int64_t K, lrd_dtype dt, Tokens tokens = THESE)
 {
-    int s = choose_splits_act(M, N, K, dt == LRD_BF16);
-    return s > 1 ? round256((size_t)s * (size_t)M * (size_t)N * sizeof(float)) : 0;
+    auto bytes = [&](int64_t m) {
+        int s = choose_splits_act(m, N, K, dt == LRD_BF16);
+        return s > 1 ? round256((size_t)s * (size_t)m * (size_t)N * sizeof(float)) : 0;
+    };
+    size_t most = bytes(M);
+    if (tokens == UP_TO)
+        for (int64_t m = 64; m < M && ceil_div(m, 64) * ceil_div(N, 64) < 256; m += 64) most = std::max(most, bytes(m));
+    return most;
 }
 
 // Split products of one linear pass run one after the other on the stream and share one region.
-size_t linear_partial_region(int64_t T, int64_t in, int64_t out, int64_t r, lrd_dtype dt, bool backward)
+size_t linear_partial_region(int64_t T, int64_t in, int64_t out, int64_t r, lrd_dtype dt, bool backward, Tokens tokens = THESE)
 {
-    const size_t h = act_partial_bytes(T, r, in, dt);   // H = X.V^T (forward, or recomputed in the backward)
+    const size_t h = act_partial_bytes(T, r, in, dt, tokens);   // H = X.V^T (forward, or recomputed in the backward)
     if (!backward) return h;
-    return std::max(std::max(h, act_partial_bytes(T, r, out, dt)),
+    return std::max(std::max(h, act_partial_bytes(T, r, out, dt, tokens)),
                     std::max(partial_bytes(out, r, T), partial_bytes(r, in, T)));
 }
 
@@ -194,22 +206,29 @@ int32_t lrd_set_fusion(int32_t mode)
 }
 
 // ------------------------------------------------------------------------------------ linear
-size_t lrd_linear_workspace_bytes(int64_t T, int64_t in, int64_t out, int64_t r, lrd_dtype dt,
-                                  uint32_t freeze_mask)
+namespace {
+size_t linear_bytes(int64_t T, int64_t in, int64_t out, int64_t r, lrd_dtype dt, Tokens tokens)
 {
-    (void)freeze_mask;
     if (!dtype_ok(dt) || !linear_dims_ok(T, in, out, r)) return 0;
     if (pads_rank(in, out, r, dt)) {
         const size_t r8 = (size_t)pad8(r);
         size_t pads = round256((size_t)out * r8 * 2) + round256(r8 * (size_t)in * 2) + round256((size_t)T * r8 * 2) +
                       round256((size_t)out * r8 * 4) + round256(r8 * (size_t)in * 4);
-        return pads + lrd_linear_workspace_bytes(T, in, out, (int64_t)r8, dt, freeze_mask);
+        return pads + linear_bytes(T, in, out, (int64_t)r8, dt, tokens);
     }
     size_t act = round256((size_t)T * (size_t)r * esize(dt));
     // forward: H when not side-stored; backward: dH and a recomputed H; both: one split-K region
-    size_t fwd = act + linear_partial_region(T, in, out, r, dt, false);
-    size_t bwd = 2 * act + linear_partial_region(T, in, out, r, dt, true);
+    size_t fwd = act + linear_partial_region(T, in, out, r, dt, false, tokens);
+    size_t bwd = 2 * act + linear_partial_region(T, in, out, r, dt, true, tokens);
     return std::max(fwd, bwd);
+}
+}  // namespace
+
+size_t lrd_linear_workspace_bytes(int64_t T, int64_t in, int64_t out, int64_t r, lrd_dtype dt,
+                                  uint32_t freeze_mask)
+{
+    (void)freeze_mask;
+    return linear_bytes(T, in, out, r, dt, UP_TO);
 }
 
 lrd_status lrd_linear_fwd(const void* X, const void* V, const void* U, const float* bias, void* Y,
@@ -454,7 +473,8 @@ void* scratch_on_current_device()
 
 int32_t lrd_linear_bwd_static_fits(int64_t T, int64_t in, int64_t out, int64_t r, lrd_dtype dt, uint32_t freeze_mask)
 {
-    const size_t need = lrd_linear_workspace_bytes(T, in, out, r, dt, freeze_mask);
+    (void)freeze_mask;
+    const size_t need = linear_bytes(T, in, out, r, dt, THESE);
     if (!dtype_ok(dt) || !linear_dims_ok(T, in, out, r)) return 0;
     return need <= LRD_STATIC_SCRATCH_BYTES ? 1 : 0;
 }
@@ -541,12 +561,13 @@ inline bool group_dims_ok(int64_t T, int64_t in, int64_t out, int64_t r, int32_t
 }
 inline const char* at(const void* p, int64_t elems, lrd_dtype dt) { return (const char*)p + elems * (int64_t)esize(dt); }
 
-size_t group_partial_region(int64_t T, int64_t in, int64_t out, int64_t r, int32_t G, lrd_dtype dt, bool backward)
+size_t group_partial_region(int64_t T, int64_t in, int64_t out, int64_t r, int32_t G, lrd_dtype dt, bool backward,
+                            Tokens tokens = THESE)
 {
-    const size_t h = act_partial_bytes(T, G * r, in, dt);
+    const size_t h = act_partial_bytes(T, G * r, in, dt, tokens);
     if (!backward) return h;
     // the groups' second-factor gradients are one batched product: G sets of slices side by side
-    return std::max(std::max(h, act_partial_bytes(T, r, out, dt)),
+    return std::max(std::max(h, act_partial_bytes(T, r, out, dt, tokens)),
                     std::max((size_t)G * partial_bytes(out, r, T), partial_bytes(G * r, in, T)));
 }
 }  // namespace
@@ -557,8 +578,8 @@ size_t lrd_linear_group_workspace_bytes(int64_t T, int64_t in, int64_t out, int6
     (void)freeze_mask;
     if (!dtype_ok(dt) || !group_dims_ok(T, in, out, r, groups)) return 0;
     const size_t act = round256((size_t)T * (size_t)groups * (size_t)r * esize(dt));
-    const size_t fwd = act + group_partial_region(T, in, out, r, groups, dt, false);
-    const size_t bwd = 2 * act + group_partial_region(T, in, out, r, groups, dt, true);
+    const size_t fwd = act + group_partial_region(T, in, out, r, groups, dt, false, UP_TO);
+    const size_t bwd = 2 * act + group_partial_region(T, in, out, r, groups, dt, true, UP_TO);
     return std::max(fwd, bwd);
 }
 
@@ -888,7 +909,7 @@ size_t lrd_tucker_conv_workspace_bytes(const lrd_conv_geom* g, lrd_dtype dt, uin
     size_t kk = (size_t)g->k * g->k;
     size_t part = std::max(std::max(partial_bytes(g->S, g->r2, pout), partial_bytes(g->r2, kk * g->r1, pout)),
                            partial_bytes(g->r1, g->C, pin));
-    part = std::max(part, round256(conv_direct_wgrad_bytes(cs, dt == LRD_BF16)));
+    part = std::max(part, round256(conv_direct_wgrad_bytes_up_to(cs, dt == LRD_BF16)));
     // forward: A and B when not side-stored; backward: dA, dB, recomputed A and B, partials, and the
     // flipped core weights of a stride-1 data gradient
     return 2 * (a + b) + part + round256(conv_dgrad_flip_bytes(cs, dt == LRD_BF16));
@@ -1083,7 +1104,7 @@ size_t lrd_dense_conv_workspace_bytes(const lrd_conv_geom* g, lrd_dtype dt)
     if (!dtype_ok(dt) || !geom_ok(g, false)) return 0;
     ConvShape cs = core_shape(*g, g->C, g->S);
     return std::max(partial_bytes(g->S, (int64_t)g->k * g->k * g->C, g->N * (int64_t)cs.Ho * cs.Wo),
-                    round256(conv_direct_wgrad_bytes(cs, dt == LRD_BF16))) +
+                    round256(conv_direct_wgrad_bytes_up_to(cs, dt == LRD_BF16))) +
            round256(conv_dgrad_flip_bytes(cs, dt == LRD_BF16));
 }
 

@@ -88,6 +88,7 @@ hipError_t f32_gemm(const MatOp& op, hipStream_t st);
 bool conv_direct_supported(const MatOp& op);                       // 3 x 3 stride-1 convolution with 32 / 64 channels?
 hipError_t conv_direct(const MatOp& op, hipStream_t st);
 size_t conv_direct_wgrad_bytes(const ConvShape& cs, bool bf16);    // scratch its weight gradient wants (0: not covered)
+size_t conv_direct_wgrad_bytes_up_to(const ConvShape& cs, bool bf16);    // the most of it for cs.N images or fewer
 hipError_t run_matop(const MatOp& op, hipStream_t st);              // picks an engine
 hipError_t apply_epilogue(const MatOp& op, hipStream_t st);        // unfused form of MatOp::epilogue
 
