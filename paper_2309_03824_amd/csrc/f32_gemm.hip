@@ -213,10 +213,14 @@ hipError_t f32_gemm(const MatOp& op, hipStream_t st)
     // 64 x 64 tiles (each operand value read half as often) from about one workgroup per compute unit on: 2048 x 432
     // over 1024 36.5 us with 32 x 32 tiles, 34.2 us with these; below, 32 x 32, and while those leave half of the
     // chip idle, 16 x 16 ([256 x 208] over 768: 8.2 -> 5.2 us).
-    if (t64 >= 192) return launch<2, 2, 2, 2, 4>(op, 1, st);
-    // K is cut over workgroups too only where the tiles leave most of the chip idle and the reduction is long
-    int64_t splits = op.partial && !op.bias ? std::min<int64_t>(op.splits, 256 / t32) : 1;
-    if (op.K < 1024 || splits < 2) splits = 1;
+    // The waves of a workgroup and the workgroups together cut K into at least as many chains of additions as the
+    // caller asked for slices: the error grows with the root of a chain's length (1000 x 1000 over 20000 in 8 chains
+    // 9.0e-7, in 2 1.8e-6).
+    const int64_t slices = op.partial && !op.bias ? op.splits : 1;
+    if (t64 >= 192) return launch<2, 2, 2, 2, 4>(op, (int)ceil_div(slices, 2), st);
+    // Beyond that, K is cut over workgroups only where the tiles leave most of the chip idle and the reduction is long
+    int64_t splits = op.K < 1024 ? 1 : std::max<int64_t>(1, std::min(slices, 256 / t32));
+    splits = std::max(splits, ceil_div(slices, 8));
     if (t32 * splits < 128) return launch<1, 1, 1, 8, 8>(op, (int)splits, st);
     return launch<2, 1, 1, 8, 4>(op, (int)splits, st);
 }

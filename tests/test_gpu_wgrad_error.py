@@ -1,5 +1,5 @@
-"""The fp32 sums of bf16 weight gradients: their error against 64 bits is that of the slices that the reduction is cut
-into, on the aligned and the unaligned engine, for one layer and for a batch."""
+"""The fp32 sums of weight gradients: their error against 64 bits is that of the slices that the reduction is cut into, on
+the aligned, the unaligned and the fp32 engine, for one layer and for a batch."""
 import math
 
 import pytest
@@ -11,17 +11,29 @@ pytestmark = pytest.mark.gpu
 BF = torch.bfloat16
 
 
-def bound(K, slices):
-    """Relative error (2-norm) of a sum of K random products in `slices` chains, one fp32 addition per 16 products
-    (the depth of a matrix instruction).  An addition's error is at most 2^-24 / sqrt(3) of the running sum in the root
-    mean square; the running sum of i products has variance i, so n additions give n / 2 of its square per chain, the
-    sum over the chains slices / 2.  Chains are whole steps of 64."""
-    n = math.ceil(math.ceil(K / slices) / 64) * 64 / 16
+def bound(K, slices, depth=16):
+    """Relative error (2-norm) of a sum of K random products in `slices` chains, one fp32 addition per `depth` products
+    (16: the depth of a bf16 matrix instruction; 1: every fp32 product is rounded).  An addition's error is at most
+    2^-24 / sqrt(3) of the running sum in the root mean square; the running sum of i products has variance i, so n
+    additions give n / 2 of its square per chain, the sum over the chains slices / 2.  Chains are whole steps of 64."""
+    n = math.ceil(math.ceil(K / slices) / 64) * 64 / depth
     return 2.0 ** -24 / math.sqrt(3) * math.sqrt((n + slices) / 2)
 
 
-def normal(gen, *shape):
-    return torch.randn(*shape, device="cuda", generator=gen).to(BF)
+def normal(gen, *shape, dt=BF):
+    return torch.randn(*shape, device="cuda", generator=gen).to(dt)
+
+
+def dense_error(M, N, K, dt):
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    dY, X, W = normal(gen, K, M, dt=dt), normal(gen, K, N, dt=dt), normal(gen, M, N, dt=dt)
+    dW = torch.full((M, N), float("nan"), device="cuda")
+    code = lrd.BF16 if dt == BF else lrd.F32
+    ws = torch.empty(max(lrd.dense_linear_workspace_bytes(K, N, M, code), 256), dtype=torch.uint8, device="cuda")
+    lrd.dense_linear_bwd(dY, X, W, None, dW, ws)
+    torch.cuda.synchronize()
+    ref = dY.double().t().contiguous() @ X.double()
+    return ((dW - ref).norm() / ref.norm()).item()
 
 
 # (rows and columns of the gradient, tokens, slices): at least 480 workgroups of 128 x 128 tiles (432 of 64 x 64) or 256
@@ -29,14 +41,14 @@ def normal(gen, *shape):
 @pytest.mark.parametrize("M,N,K,slices", [(4096, 256, 4096, 8), (3072, 192, 8192, 10), (192, 768, 8192, 12), (264, 1024, 4100, 16),
                                           (2048, 104, 4099, 7), (1001, 1003, 4000, 8), (1001, 192, 8192, 9)])
 def test_weight_gradient_error(M, N, K, slices):
-    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
-    dY, X, W = normal(gen, K, M), normal(gen, K, N), normal(gen, M, N)
-    dW = torch.full((M, N), float("nan"), device="cuda")
-    ws = torch.empty(max(lrd.dense_linear_workspace_bytes(K, N, M, lrd.BF16), 256), dtype=torch.uint8, device="cuda")
-    lrd.dense_linear_bwd(dY, X, W, None, dW, ws)
-    torch.cuda.synchronize()
-    ref = dY.double().t().contiguous() @ X.double()
-    assert ((dW - ref).norm() / ref.norm()).item() <= bound(K, slices)
+    assert dense_error(M, N, K, BF) <= bound(K, slices)
+
+
+# few and many tiles of 32 x 32 and 64 x 64 (waves of a workgroup that share a reduction: 8 and 2)
+@pytest.mark.parametrize("M,N,K,slices", [(2048, 1024, 1024, 4), (1000, 1000, 20000, 8), (640, 640, 16384, 20),
+                                          (771, 705, 8191, 12), (130, 70, 5000, 19)])
+def test_f32_weight_gradient_error(M, N, K, slices):
+    assert dense_error(M, N, K, torch.float32) <= bound(K, slices, depth=1)
 
 
 @pytest.mark.parametrize("L,M,N,K,slices", [(12, 1024, 256, 8192, 4), (4, 2048, 128, 4096, 7), (3, 520, 136, 8000, 15)])
