@@ -69,15 +69,28 @@ __device__ __forceinline__ const char* uni_ptr(const void* p)
     return reinterpret_cast<const char*>(uni64((int64_t)reinterpret_cast<uintptr_t>(p)));
 }
 
+// Base and extent of a descriptor, five wait states after whatever vector instructions (readfirstlane) wrote them; the
+// results are scalar registers of their own, which only scalar instructions touch from here on.
+__device__ __forceinline__ void settle(const char*& base, uint32_t& span)
+{
+    asm volatile("s_nop 4" : "+s"(base), "+s"(span));
+}
+
 // 16 bytes per lane from memory into LDS: lane l's chunk lands at byte address lds + 16 l (lds is wave-uniform).
 // As an instruction of its own and not the builtin: the compiler waits for every load of that builtin still in
 // flight before each LDS read that might alias it, which is all of them here.  It has no register result; the
-// waits are wait_vm's.  (s_nop: M0 must be written one state before an LDS load reads it.)
+// waits are wait_vm's.  (s_nop: M0 must be written one state before an LDS load reads it.)  The compiler does not see a
+// vector-memory instruction here, so it does not keep the five wait states between a scalar register written by a vector
+// instruction and its use in a descriptor: what a descriptor is made of goes through settle() first.  M0 is a reserved
+// register, for whose clobber the compiler warns; nothing is kept in it across this, and it has to know of the write.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void load_to_lds(uint32_t lds, const char* base, uint32_t span, uint32_t voff)
 {
     __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, (int)span, (int)BUF_FLAGS);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(r) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds), "v"(voff), "s"(r) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 // Until all but this wave's newest N vector-memory operations have completed.
 template <int N>
 __device__ __forceinline__ void wait_vm()
@@ -129,6 +142,7 @@ struct KcTile {
         k0 = (int)uni((uint32_t)k);
         at = base + k0 * 2;
         left = span - (uint32_t)k0 * 2u;      // k0 < K
+        settle(at, left);
     }
     __device__ __forceinline__ void one(int i, uint32_t lds, int kend, int wave)
     {
@@ -176,6 +190,7 @@ struct KmTile {
         const int ku = (int)uni((uint32_t)k);
         at = base + (int64_t)ku * ld * 2;
         left = (uint32_t)(min(kend - ku, BK) - 1) * ((uint32_t)ld * 2u) + (uint32_t)cols_here * 2u;
+        settle(at, left);
     }
     __device__ __forceinline__ void one(int i, uint32_t lds, int, int wave) { load_to_lds(lds + (i * NW + wave) * 1024, at, left, voff[i]); }
 };
@@ -213,6 +228,7 @@ struct ConvRowsTile {
         ch = DGRAD ? cs.O : cs.I;            // channels of the tensor being gathered
         base = uni_ptr(o.p);
         span = uni((uint32_t)cs.N * (uint32_t)(DGRAD ? cs.Ho * cs.Wo : cs.H * cs.W) * (uint32_t)ch * 2u);
+        settle(base, span);
         q_tap = BK / ch;
         r_ch = BK - q_tap * ch;
         const bool cls = DGRAD && cs.cls;
@@ -318,6 +334,7 @@ struct ConvKmTile {
             v0 = cs.cls ? cv.first : 0;
             ustep = cs.cls ? cs.stride : 1;
         }
+        settle(base, span);
 #pragma unroll
         for (int i = 0; i < KS; ++i) {
             const int col = col0 + ((lane % CPK) ^ km_swz<COLS>((i * NW + wave) * KPI + lane / CPK)) * 8;
