@@ -798,8 +798,9 @@ hipError_t launch_epi(const MatOp& op, const Operand& A, const Operand& B, hipSt
     }
     static const std::string tag = [] {
         char b[64];
-        snprintf(b, sizeof(b), "gemm2_kernel<%d,%d,%d,%d,%s,%s,%s%s>", BM, BN, WGM, WGN, A_KM ? "A_KM" : "A_KC", B_KM ? "B_KM" : "B_KC",
-                 sizeof(OutT) == 2 ? "bf16" : "f32", G == GATHER_NONE ? "" : ",conv");
+        snprintf(b, sizeof(b), "gemm2_kernel<%d,%d,%d,%d,%d,%s,%s,%s%s%s>", BM, BN, WGM, WGN, STAGES, A_KM ? "A_KM" : "A_KC", B_KM ? "B_KM" : "B_KC",
+                 sizeof(OutT) == 2 ? "bf16" : "f32", G == GATHER_NONE ? "" : ",conv",
+                 EPI == EPI_ACT_STORE ? ",gelu" : EPI == EPI_ACT_GRAD ? ",gelu_grad" : "");
         return std::string(b);
     }();
     note_kernel(tag.c_str());

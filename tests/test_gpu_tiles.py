@@ -1,5 +1,6 @@
 """The output tiles of the MFMA product kernel, each at sizes off its edges: rows, columns and K that end inside a tile, a
-load and a K-step; against fp32 products of the same bf16 operands."""
+load and a K-step; against fp32 products of the same bf16 operands.  Each shape names its tile, and the event log has to
+agree."""
 import pytest
 import torch
 
@@ -7,20 +8,26 @@ from paper_2309_03824_amd import binding as lrd
 
 BF = torch.bfloat16
 
-# (tokens, in, out, rank): the tile that the first product, tokens x rank over in, is given
-SHAPES = [(200, 1000, 520, 72),        # 64 x 64
-          (200, 1000, 520, 264),       # 64 x 64, second product of more than 256
-          (8201, 600, 640, 184),       # 128 x 64
-          (4100, 1032, 1024, 264),     # 64 x 128
-          (16001, 584, 600, 256),      # 128 x 128
-          (7999, 1032, 776, 760),      # 128 x 256
-          (16264, 1032, 1032, 1024),   # 256 x 256
-          (64, 8, 16, 8)]              # less than one of anything
+# (tokens, in, out, rank), and the tile (rows, columns, waves down and across, stages) that the products
+# tokens x rank over in and tokens x out over rank are given
+SHAPES = [((200, 1000, 520, 72), "64,64,2,2,4", "64,64,2,2,2"),
+          ((200, 1000, 520, 264), "64,64,2,2,4", "64,64,2,2,4"),
+          ((8201, 600, 640, 184), "128,64,4,2,4", "128,128,2,4,2"),
+          ((4100, 1032, 1024, 264), "64,128,2,4,4", "128,128,2,4,2"),
+          ((16001, 584, 600, 256), "128,128,2,4,4", "128,128,2,4,2"),
+          ((7999, 1032, 776, 760), "128,256,2,4,3", "128,256,2,4,3"),
+          ((16264, 1032, 1032, 1024), "256,256,2,4,2", "128,256,2,4,3"),
+          ((64, 8, 16, 8), "64,64,2,2,1", "64,64,2,2,1")]      # less than one of anything
+
+
+def kernel(tile, b_km=False, epilogue=""):
+    return f"gemm2_kernel<{tile},A_KC,{'B_KM' if b_km else 'B_KC'},bf16{epilogue}>"
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("T,n_in,n_out,r", SHAPES)
-def test_tiles(T, n_in, n_out, r):
+@pytest.mark.parametrize("shape,first,second", SHAPES)
+def test_tiles(shape, first, second):
+    T, n_in, n_out, r = shape
     gen = torch.Generator(device="cuda").manual_seed(T + r)
 
     def normal(*shape, std=1.0):
@@ -34,7 +41,10 @@ def test_tiles(T, n_in, n_out, r):
     Y, H, dX = (torch.full((T, n), float("nan"), device="cuda", dtype=BF) for n in (n_out, r, n_in))
     dU, dV = (torch.full(s, float("nan"), device="cuda") for s in ((n_out, r), (r, n_in)))
     ws = torch.empty(lrd.linear_workspace_bytes(T, n_in, n_out, r, lrd.BF16, 0), dtype=torch.uint8, device="cuda")
-    lrd.linear_fwd(X, V, U, None, Y, H, ws)
+    with lrd.ProfileLog(8) as log:
+        lrd.linear_fwd(X, V, U, None, Y, H, ws)
+        torch.cuda.synchronize()
+    assert [row["kernel"] for row in log.rows()] == [kernel(first), kernel(second)]
     lrd.linear_bwd(dY, X, H, V, U, dX, dV, dU, None, 0, ws)
     torch.cuda.synchronize()
     # one rounding to bf16 is at most 2^-9 of a value; dX and dV go through a dH rounded on either side, whose
