@@ -55,3 +55,60 @@ def test_tiles(shape, first, second):
     assert rel(dX, dH @ V.float()) < 4e-3
     assert rel(dU, dY.float().t() @ H.float()) < 2e-5
     assert rel(dV, dH.t() @ X.float()) < 2e-3
+
+
+# Short reductions with the activation in the epilogue, off every edge of their tiles: (tokens, narrow side, wide side, rank)
+# and the tile of tokens x wide over rank with GELU, with the gradient of GELU
+ACTIVATIONS = [((4100, 1024, 3080, 192), "128,128,2,4,2", "128,128,2,4,1"),
+               ((8201, 1032, 4104, 256), "128,128,2,4,2", "128,128,2,4,1"),
+               ((12300, 1032, 3080, 264), "128,128,2,4,1", "128,128,2,4,1"),
+               ((16200, 2056, 3080, 456), "256,256,2,4,2", "256,256,2,4,2"),
+               ((6100, 512, 520, 72), "128,128,2,4,2", "128,128,2,4,2"),
+               ((300, 512, 520, 72), "64,64,2,2,2", "64,64,2,2,2")]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,forward,gradient", ACTIVATIONS)
+def test_tiles_with_activation(shape, forward, gradient):
+    """The fused epilogues against the plain product followed by the elementwise kernels (the same values, bit for bit),
+    and the plain product against fp32."""
+    T, narrow, wide, r = shape
+    gen = torch.Generator(device="cuda").manual_seed(T + r)
+
+    def normal(*shape, std=1.0, dt=BF):
+        return torch.randn(*shape, device="cuda", generator=gen).mul_(std).to(dt)
+
+    def nan(*shape):
+        return torch.full(shape, float("nan"), device="cuda", dtype=BF)
+
+    def rel(a, b):
+        return ((a.float() - b).norm() / b.norm()).item()
+
+    def logged(call, *args):
+        with lrd.ProfileLog(4) as log:
+            call(*args)
+            torch.cuda.synchronize()
+        return log.rows()[-1]["kernel"]
+
+    # forward, narrow -> wide, with a bias
+    X, bias = normal(T, narrow), normal(wide, std=0.1, dt=torch.float32)
+    U, V = normal(wide, r, std=r ** -0.5), normal(r, narrow, std=narrow ** -0.5)
+    ws = torch.empty(lrd.linear_workspace_bytes(T, narrow, wide, r, lrd.BF16, 0), dtype=torch.uint8, device="cuda")
+    Y, A, H, plain, A2 = nan(T, wide), nan(T, wide), nan(T, r), nan(T, wide), nan(T, wide)
+    assert logged(lrd.linear_fwd_act, X, V, U, bias, Y, A, H, lrd.ACT_GELU, ws) == kernel(forward, epilogue=",gelu")
+    lrd.linear_fwd(X, V, U, bias, plain, None, ws)
+    lrd.gelu_fwd(plain, A2)
+    torch.cuda.synchronize()
+    # one rounding to bf16 is at most 2^-9 of a value
+    assert rel(plain, H.float() @ U.float().t() + bias) < 2e-3
+    assert torch.equal(Y, plain) and torch.equal(A, A2)
+    # data gradient of a layer wide -> narrow whose input is an activation
+    dY, Z = normal(T, narrow), normal(T, wide)
+    U, V = normal(narrow, r, std=r ** -0.5), normal(r, wide, std=wide ** -0.5)
+    dX, plain, dH, dX2 = nan(T, wide), nan(T, wide), nan(T, r), nan(T, wide)
+    assert logged(lrd.linear_bwd_data, dY, V, U, dX, dH, Z, lrd.ACT_GELU, ws) == kernel(gradient, True, ",gelu_grad")
+    lrd.linear_bwd_data(dY, V, U, plain, dH, None, lrd.ACT_NONE, ws)
+    lrd.gelu_bwd(plain, Z, dX2)
+    torch.cuda.synchronize()
+    assert rel(plain, dH.float() @ V.float()) < 2e-3
+    assert torch.equal(dX, dX2)
