@@ -300,12 +300,12 @@ struct ConvKmTile {
     static constexpr int CPK = COLS / 8, KPI = 64 / CPK;
     static constexpr int CH = BK / (KPI * NW), BYTES = COLS * BK * 2;
     static_assert(64 % CPK == 0 && BK % (KPI * NW) == 0, "whole loads");
-    static constexpr int KS = KPI * NW % 4 == 0 ? 1 : CH;    // distinct swizzles, hence columns, among a lane's loads
+    static_assert(KPI * NW % 4 == 0, "all loads of a lane have one swizzle, hence one column");
     const char* base;
     uint32_t span;
     ConvShape cs;
-    int c0[KS], tu[KS], tv[KS];
-    bool colok[KS];
+    int c0, tu, tv;
+    bool colok;
     // k of the next load, per chunk.  DGRAD: (tap, o) in s1, s0.  WGRAD: output pixel as (n, y, x) in s2, s1, s0.
     int s0[CH], s1[CH], s2[CH], kk[CH];
     int d0, d1, d2;           // BK in the same mixed radix
@@ -335,19 +335,16 @@ struct ConvKmTile {
             ustep = cs.cls ? cs.stride : 1;
         }
         settle(base, span);
-#pragma unroll
-        for (int i = 0; i < KS; ++i) {
-            const int col = col0 + ((lane % CPK) ^ km_swz<COLS>((i * NW + wave) * KPI + lane / CPK)) * 8;
-            colok[i] = col < o.rows;
-            if (WGRAD) {
-                const int tap = col / cs.I;
-                c0[i] = col - tap * cs.I;
-                tu[i] = tap / cs.k - cs.pad;
-                tv[i] = tap % cs.k - cs.pad;
-            } else {
-                c0[i] = col;
-                tu[i] = tv[i] = 0;
-            }
+        const int col = col0 + ((lane % CPK) ^ km_swz<COLS>(wave * KPI + lane / CPK)) * 8;
+        colok = col < o.rows;
+        if (WGRAD) {
+            const int tap = col / cs.I;
+            c0 = col - tap * cs.I;
+            tu = tap / cs.k - cs.pad;
+            tv = tap % cs.k - cs.pad;
+        } else {
+            c0 = col;
+            tu = tv = 0;
         }
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
@@ -368,18 +365,17 @@ struct ConvKmTile {
     __device__ __forceinline__ void step(int, int) {}
     __device__ __forceinline__ void one(int i, uint32_t lds, int kend, int wave)
     {
-        const int c = KS == 1 ? 0 : i;
-        bool ok = colok[c] && kk[i] < kend;
+        bool ok = colok && kk[i] < kend;
         uint32_t off;
         if (WGRAD) {
-            const int yy = s1[i] * cs.stride + tu[c], xx = s0[i] * cs.stride + tv[c];
+            const int yy = s1[i] * cs.stride + tu, xx = s0[i] * cs.stride + tv;
             ok = ok && (uint32_t)yy < (uint32_t)cs.H && (uint32_t)xx < (uint32_t)cs.W;
-            off = (uint32_t)((s2[i] * cs.H + yy) * cs.W + xx) * (uint32_t)cs.I + (uint32_t)c0[c];
+            off = (uint32_t)((s2[i] * cs.H + yy) * cs.W + xx) * (uint32_t)cs.I + (uint32_t)c0;
         } else {
             const int t = min(s1[i], ntaps - 1);     // (taps past the last one: tail of K)
             const int tq = small_div(t, magic_nv);
             const int tap = (u0 + ustep * tq) * cs.k + v0 + ustep * (t - tq * nv);
-            off = (uint32_t)(s0[i] * cs.k * cs.k + tap) * (uint32_t)cs.I + (uint32_t)c0[c];
+            off = (uint32_t)(s0[i] * cs.k * cs.k + tap) * (uint32_t)cs.I + (uint32_t)c0;
         }
         load_to_lds(lds + (i * NW + wave) * 1024, base, span, ok ? off * 2u : BUF_OOB);
         // advance this load's k by BK
