@@ -203,8 +203,9 @@ struct KmTile {
 // the only integer divisions are in init().
 
 // floor(t / d) for 0 <= t * d < 65536 by multiplication with ceil(65536 / d): taps by the kernel size
-// (d < 32, t <= d * d + 8) and, in the data gradient, pixel coordinates by the stride.
-__device__ __forceinline__ int small_div(int t, int magic) { return (t * magic) >> 16; }
+// (d < 32, t <= d * d + 8) and, in the data gradient, pixel coordinates by the stride.  (Unsigned: with d = 1 the product
+// reaches 65535 * 65536.)
+__device__ __forceinline__ int small_div(int t, int magic) { return (int)(((uint32_t)t * (uint32_t)magic) >> 16); }
 
 // A operand, k-contiguous.  FWD:   row = output pixel, k = (u, v, i), reads X[n, y*s+u-p, x*s+v-p, i].
 //                           DGRAD: row = input pixel,  k = (u, v, o), reads dY[n, (a+p-u)/s, (b+p-v)/s, o].

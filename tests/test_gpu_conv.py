@@ -211,3 +211,15 @@ def test_tucker_stage_full_size_sampled_bf16(C, hw):
     check(host(g2), go["dP2"], "bf16", "dP2")
     rest = [n for n in range(N) if n not in picks]
     assert torch.all(gX[rest] == 0), "input gradient of an image whose output gradient is zero"
+
+
+def test_data_gradient_of_a_long_image():
+    """Pixel coordinates from 32768 on: the division by the stride multiplies in 32 unsigned bits."""
+    W, C, S = 40000, 16, 24
+    gen = torch.Generator(device="cuda").manual_seed(W)
+    dY, K = (torch.randn(*s, device="cuda", generator=gen).bfloat16() for s in ((1, 1, W, S), (S, 1, 1, C)))
+    g = lrd.conv_geom(1, 1, W, C, S, 1, 1, 1, 1, 0)
+    dX = empty((1, 1, W, C), "bf16")
+    lrd.dense_conv_bwd(dY, None, K, dX, None, g, workspace(lrd.dense_conv_workspace_bytes(g, lrd.BF16)))
+    torch.cuda.synchronize()
+    check(host(dX).reshape(W, C), host(dY).reshape(W, S) @ host(K).reshape(S, C), "bf16", "dX")
