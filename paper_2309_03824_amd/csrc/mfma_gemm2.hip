@@ -851,6 +851,14 @@ hipError_t by_tile(const MatOp& op, const Operand& A, const Operand& B, hipStrea
             return launch<128, 32, 4, 1, 4, A_KM, B_KM, OutT, G>(op, A, B, st);
         }
     }
+    // Gathers that give a unit many workgroups: two stages of 64 x 64 tiles, five workgroups to a unit, and not four stages
+    // or a wider tile, whose two or one cannot cover the address arithmetic of each load.  Results up to 64 columns wide
+    // from 3.5 workgroups a unit on (128 images of 56 x 56, 40 -> 40 channels 47.9 -> 35.3 us; 64 -> 64 with stride 2
+    // 23.5 -> 17.8 us; at 1.5 a unit over 2304 k 15.5 against 18.5 us), and from 3 on the parity classes of a strided data
+    // gradient, whose workgroups run over 1 to 4 taps (128 images of 56 x 56, 64 <- 128 channels 75.5 -> 54.7 us; 64 of
+    // 28 x 28, 128 <- 256 36.1 -> 28.3 us; at 1.2 a unit 9.7 against 10.2 us) unless 128 x 128 tiles are the cheaper ones.
+    const bool classes = G == GATHER_CONV_DGRAD && op.cs.cls && wgs(64, 64) * op.cs.stride * op.cs.stride >= 3 * 256;
+    const bool narrow = G == GATHER_CONV_FWD && op.N <= 64 && 2 * wgs(64, 64) >= 7 * 256;
     // Short reductions (K = rank: second product of a forward pair or of a data gradient) are mostly prologue and
     // epilogue, which only other workgroups on the unit can overlap; eight waves per tile do so better than four.
     if (!WGRAD && op.K <= 8 * BK) {
@@ -872,10 +880,12 @@ hipError_t by_tile(const MatOp& op, const Operand& A, const Operand& B, hipStrea
         }
         // a single K-step needs a single stage: 401408 x 64 x 32 15.1 -> 13.0 us
         if (op.K <= BK) return launch<64, 64, 2, 2, 1, A_KM, B_KM, OutT, G>(op, A, B, st);
-        if (op.K <= 4 * BK) return launch<64, 64, 2, 2, 2, A_KM, B_KM, OutT, G>(op, A, B, st);
+        if (op.K <= 4 * BK || classes || narrow) return launch<64, 64, 2, 2, 2, A_KM, B_KM, OutT, G>(op, A, B, st);
         return launch<64, 64, 2, 2, 4, A_KM, B_KM, OutT, G>(op, A, B, st);
     }
-    switch (gemm_best_tile(op.M, op.N, op.K, splits, batch, G != GATHER_NONE ? COST_GATHER : WGRAD ? COST_WGRAD : COST_PLAIN)) {
+    const GemmTile tile = gemm_best_tile(op.M, op.N, op.K, splits, batch, G != GATHER_NONE ? COST_GATHER : WGRAD ? COST_WGRAD : COST_PLAIN);
+    if (narrow || (classes && tile >= TILE_64x128)) return launch<64, 64, 2, 2, 2, A_KM, B_KM, OutT, G>(op, A, B, st);
+    switch (tile) {
     case TILE_256x256:
         if constexpr (G == GATHER_NONE) return launch<256, 256, 2, 4, 2, A_KM, B_KM, OutT, G>(op, A, B, st);
         [[fallthrough]];

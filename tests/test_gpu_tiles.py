@@ -112,3 +112,48 @@ def test_tiles_with_activation(shape, forward, gradient):
     torch.cuda.synchronize()
     assert rel(plain, dH.float() @ V.float()) < 2e-3
     assert torch.equal(dX, dX2)
+
+
+# Gathers with many workgroups, off the edges of their tiles: (images, height, width, C, S, k, stride), and the tiles of the
+# forward pass and of the data gradient
+GATHERS = [((37, 56, 55, 24, 40, 5, 1), "64,64,2,2,2", "128,32,4,1,4"),
+           ((37, 79, 79, 40, 56, 3, 2), "64,64,2,2,2", "64,64,2,2,2"),
+           ((11, 57, 57, 72, 104, 3, 2), "128,64,4,2,4", "64,64,2,2,2"),
+           ((9, 57, 57, 136, 160, 3, 2), "128,64,4,2,4", "64,64,2,2,2"),
+           ((20, 50, 50, 40, 72, 5, 3), "64,64,2,2,4", "64,64,2,2,2"),
+           ((5, 19, 19, 40, 72, 5, 3), "64,64,2,2,4", "64,64,2,2,4")]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,forward,gradient", GATHERS)
+def test_gather_tiles(shape, forward, gradient):
+    N, hh, ww, C, S, k, s = shape
+    gen = torch.Generator(device="cuda").manual_seed(N + C)
+
+    def normal(*shape, std=1.0):
+        return torch.randn(*shape, device="cuda", generator=gen).mul_(std).to(BF)
+
+    geo = lrd.conv_geom(N, hh, ww, C, S, 1, 1, k, s, k // 2)
+    ho, wo = geo.out_hw()
+    X, W, dY = normal(N, hh, ww, C), normal(S, k, k, C, std=(k * k * C) ** -0.5), normal(N, ho, wo, S)
+    Y, dX = (torch.full(t, float("nan"), device="cuda", dtype=BF) for t in ((N, ho, wo, S), (N, hh, ww, C)))
+    ws = torch.empty(lrd.dense_conv_workspace_bytes(geo, lrd.BF16) + 16, dtype=torch.uint8, device="cuda")
+    with lrd.ProfileLog(4) as log:
+        lrd.dense_conv_fwd(X, W, Y, geo, ws)
+        lrd.dense_conv_bwd(dY, X, W, dX, None, geo, ws)
+        torch.cuda.synchronize()
+    # (a data gradient of stride 1 is a forward gather with flipped weights)
+    assert [row["kernel"] for row in log.rows()] == [f"gemm2_kernel<{forward},A_KC,B_KC,bf16,conv>",
+                                                    f"gemm2_kernel<{gradient},A_KC,{'B_KC' if s == 1 else 'B_KM'},bf16,conv>"]
+    # the same sums in fp32, tap by tap
+    pad = torch.nn.functional.pad(X.float(), (0, 0, k // 2, k // 2, k // 2, k // 2))
+    dpad, want = torch.zeros_like(pad), torch.zeros(N, ho, wo, S, device="cuda")
+    for u in range(k):
+        for v in range(k):
+            at = (slice(None), slice(u, u + (ho - 1) * s + 1, s), slice(v, v + (wo - 1) * s + 1, s))
+            want += pad[at] @ W[:, u, v].float().t()
+            dpad[at] += dY.float() @ W[:, u, v].float()
+    dwant = dpad[:, k // 2:k // 2 + hh, k // 2:k // 2 + ww]
+    # one rounding to bf16 is at most 2^-9 of a value
+    assert ((Y.float() - want).norm() / want.norm()).item() < 2e-3
+    assert ((dX.float() - dwant).norm() / dwant.norm()).item() < 2e-3
