@@ -69,9 +69,13 @@ int choose_splits(int64_t M, int64_t N, int64_t K)
 
 // Products whose result is a [tokens x r] activation (H = X.V^T, dH = dY.U) have few output tiles
 // when r is small and a long K when the wide side of the layer is the reduction.  While 64 x 64
-// tiles still give every compute unit a workgroup (T = 8192, r = 192: 384 of them) the unsplit
-// kernel is as fast as any split plus its reduce (27.7 us against 25.6-29 us at K = 3072, cold
-// operands), so K is cut only below that, down to slices of 768.
+// tiles still give every compute unit a workgroup, the unsplit kernel is as fast as any split plus
+// its reduce (cold operands: 8192 x 192 over 3072 22.3 us against 26.4 us and more, over 4096 30.0
+// against 29.7 us; 4096 x 256 over 4096 22.1 against 22.1 us), so K is cut only below that, down to
+// slices of 768.  There it pays with few tokens and a long K (48 x 256 over 4096 16.2 -> 8.7 us in
+// 5 slices, 509 x 192 over 3072 13.0 -> 9.5 us in 4, 2048 x 192 over 4096 16.7 -> 14.9 us in 5); with
+// more tokens and K = 1536 or 3072 the sum costs what the slices win, or more (4096 x 192 over 3072
+// 17.3 against 19.4 us in 3, 2048 x 192 over 1536 8.3 against 10.1 us in 2).
 int choose_splits_act(int64_t M, int64_t N, int64_t K, bool in_bf16)
 {
     if (!in_bf16 || N % 8 != 0) return 1;           // only the aligned MFMA path reduces into bf16

@@ -3,8 +3,8 @@
 //
 // The fp32 path runs small products (a few hundred tokens, one layer), so it is bound by latency and by how
 // many compute units get work, not by bandwidth: a workgroup takes a small tile of the result, cuts K over its
-// waves, and every wave fetches its operand fragments straight from memory (L2) into registers, one step ahead
-// of the matrix instructions; there is no LDS and no barrier before the waves' sums meet at the end.
+// waves, and every wave fetches its operand fragments straight from memory (L2) into registers, three or
+// seven steps ahead of the matrix instructions; there is no LDS and no barrier before the waves' sums meet at the end.
 // [256 x 208] over K = 768: 5.2 us (208 workgroups of 16 x 16 tiles; about 2.5 us of it are the launch)
 // against 94 us on 16 workgroups of 64 x 64 FMA tiles with two barriers per 16 k; [2048 x 1024] over K = 1024:
 // 62 us = 69 TFLOP/s of about 153.
@@ -200,7 +200,8 @@ hipError_t launch(const MatOp& op, int splits, hipStream_t st)
 bool f32_gemm_supported(const MatOp& op)
 {
     if (op.in_bf16 || !op.out_f32 || op.gather != GATHER_NONE || op.batch != 1) return false;
-    if (op.M < 2 || op.N < 2 || op.K < 1) return false;     // (a K-major operand is read in pairs of rows)
+    // A K-major operand is read in pairs of rows: a single token and rank 1 stay with the FMA engine.
+    if (op.M < 2 || op.N < 2 || op.K < 1) return false;
     const int64_t lim = int64_t(1) << 30;
     if (op.M >= lim || op.N >= lim || op.K >= lim || ceil_div(op.N, 16) > 65535) return false;
     return (op.a_sk == 1 || op.a_sm == 1) && (op.b_sk == 1 || op.b_sn == 1);

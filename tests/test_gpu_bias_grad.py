@@ -1,5 +1,6 @@
-"""GPU parity of the bias gradient (column sums of dY) at the edges of its row and column blocks, with and
-without workspace to cut the rows (both factors frozen and no dX: there is none)."""
+"""GPU parity of the bias gradient (column sums of dY) at the edges of its row and column blocks, with the workspace of a
+data gradient to cut the rows in and with what both factors frozen and no dX leave: from 512 tokens on that of the sliced
+weight gradients, below it none."""
 import numpy as np
 import pytest
 import torch
