@@ -17,32 +17,41 @@ namespace lrd {
 // multiplication, smaller ones fill the chip when the result is small.
 namespace {
 struct StepTime { float full, one; };      // every unit at its workgroups per unit; at most one per unit
-struct TileCost { int bm, bn, per_cu; StepTime step[GEMM_COSTS]; };
+struct TileCost { int bm, bn, per_cu; StepTime step[GEMM_COSTS]; int ends; };
 // (COST_WGRAD: 64-column tiles of a k-major operand fetch 128 bytes per row, which costs most when memory is busy: 12 x
 // [192 x 3072] over 8192 239 us in 64 x 128 tiles, 215 us in 256 x 256 ones; COST_GATHER: address arithmetic with each
 // load, which 64 x 64 tiles with one wave per SIMD cannot hide: 128 x 1152 over 25088 pixels 0.47 us a step.)
 constexpr TileCost TILES[GEMM_TILES] = {
-    {256, 256, 1, {{1.84f, 1.84f}, {1.84f, 1.84f}, {1e9f, 1e9f}}},     // (no gathers)
-    {128, 256, 1, {{0.98f, 0.98f}, {1.00f, 1.00f}, {1.20f, 1.20f}}},
-    {128, 128, 1, {{0.62f, 0.62f}, {0.64f, 0.64f}, {0.75f, 0.75f}}},
-    {128, 128, 2, {{1.17f, 0.75f}, {1.20f, 0.80f}, {1.20f, 0.90f}}},
-    {64, 128, 1, {{0.390f, 0.390f}, {0.55f, 0.44f}, {0.550f, 0.550f}}},
-    {128, 64, 1, {{0.395f, 0.395f}, {0.55f, 0.44f}, {0.545f, 0.545f}}},
-    {64, 64, 2, {{0.44f, 0.24f}, {0.50f, 0.26f}, {0.65f, 0.47f}}},
+    {256, 256, 1, {{1.84f, 1.84f}, {1.84f, 1.84f}, {1e9f, 1e9f}}, 2},     // (no gathers)
+    {128, 256, 1, {{0.98f, 0.98f}, {1.00f, 1.00f}, {1.20f, 1.20f}}, 6},
+    {128, 128, 1, {{0.62f, 0.62f}, {0.64f, 0.64f}, {0.75f, 0.75f}}, 2},
+    {128, 128, 2, {{1.17f, 0.75f}, {1.20f, 0.80f}, {1.20f, 0.90f}}, 2},
+    {64, 128, 1, {{0.390f, 0.390f}, {0.55f, 0.44f}, {0.550f, 0.550f}}, 2},
+    {128, 64, 1, {{0.395f, 0.395f}, {0.55f, 0.44f}, {0.545f, 0.545f}}, 2},
+    {64, 64, 2, {{0.44f, 0.24f}, {0.50f, 0.26f}, {0.65f, 0.47f}}, 1},
 };
-inline float gemm_tile_cost(const TileCost& t, int64_t M, int64_t N, int64_t K, int64_t splits, int64_t batch, GemmCost kind)
+// Weight gradients, whose slices are given and few steps long: a last round of a few workgroups runs at the rate of one to
+// a unit, and a workgroup fills its stages and stores its fp32 tile besides (`ends`, in steps).  312 x 2808 over 6272
+// pixels, 8 slices of 13 steps, 47.1 us in the 880 workgroups of 64 x 128 tiles that rounds and steps alone choose, 38.5
+// us in 528 of 128 x 128, two to a unit; 1536 x 320 over 3000 tokens, 10 slices of 5 steps, 22.2 us in 128 x 256 tiles,
+// 21.0 us in 128 x 128.  (Not from 64 workgroups on: 12 x [192 x 3072] over 8192 would go to 1728 workgroups of 64 x 64,
+// 3 % of the FFN stack slower than in 144 of 256 x 256.)
+inline float gemm_tile_cost(const TileCost& t, int64_t M, int64_t N, int64_t K, int64_t splits, int64_t batch, GemmCost kind, bool wgrad)
 {
     const int64_t wgs = ceil_div(M, t.bm) * ceil_div(N, t.bn) * splits * batch, steps = ceil_div(ceil_div(K, 64), splits);
-    return (float)ceil_div(wgs, 256 * t.per_cu) * (float)steps * (wgs <= 256 ? t.step[kind].one : t.step[kind].full);
+    const StepTime& step = t.step[kind];
+    const int64_t slots = 256 * t.per_cu, left = wgs % slots, few = wgs > slots ? 64 : 256;
+    if (!wgrad) return (float)ceil_div(wgs, slots) * (float)steps * (wgs <= 256 ? step.one : step.full);
+    return ((float)(wgs / slots) * step.full + (left == 0 ? 0.f : left <= few ? step.one : step.full)) * (float)(steps + t.ends);
 }
 }  // namespace
 
-GemmTile gemm_best_tile(int64_t M, int64_t N, int64_t K, int64_t splits, int64_t batch, GemmCost kind)
+GemmTile gemm_best_tile(int64_t M, int64_t N, int64_t K, int64_t splits, int64_t batch, GemmCost kind, bool wgrad)
 {
     int best = TILE_64x64;
     float least = 3e38f;
     for (int i = 0; i < GEMM_TILES; ++i) {
-        const float c = gemm_tile_cost(TILES[i], M, N, K, splits, batch, kind);
+        const float c = gemm_tile_cost(TILES[i], M, N, K, splits, batch, kind, wgrad);
         if (c < least) { least = c; best = i; }
     }
     return (GemmTile)best;

@@ -101,7 +101,7 @@ int choose_splits_batched(int64_t M, int64_t N, int64_t K, int64_t batch);
 // `splits` slices of K.
 enum GemmCost { COST_PLAIN, COST_WGRAD, COST_GATHER, GEMM_COSTS };     // both operands k-major; convolution gathers
 enum GemmTile { TILE_256x256, TILE_128x256, TILE_128x128, TILE_128x128_PAIR, TILE_64x128, TILE_128x64, TILE_64x64, GEMM_TILES };
-GemmTile gemm_best_tile(int64_t M, int64_t N, int64_t K, int64_t splits, int64_t batch, GemmCost kind);
+GemmTile gemm_best_tile(int64_t M, int64_t N, int64_t K, int64_t splits, int64_t batch, GemmCost kind, bool wgrad);
 
 // Fused pair  C2[M x N2] = (A[M x K1] . B1[R x K1]^T) . B2[N2 x R]^T : the rank-R intermediate
 // stays on chip; optionally it is also stored (mid_save, [M x R], operand dtype).

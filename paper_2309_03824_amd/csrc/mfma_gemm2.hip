@@ -883,7 +883,7 @@ hipError_t by_tile(const MatOp& op, const Operand& A, const Operand& B, hipStrea
         if (op.K <= 4 * BK || classes || narrow) return launch<64, 64, 2, 2, 2, A_KM, B_KM, OutT, G>(op, A, B, st);
         return launch<64, 64, 2, 2, 4, A_KM, B_KM, OutT, G>(op, A, B, st);
     }
-    const GemmTile tile = gemm_best_tile(op.M, op.N, op.K, splits, batch, G != GATHER_NONE ? COST_GATHER : WGRAD ? COST_WGRAD : COST_PLAIN);
+    const GemmTile tile = gemm_best_tile(op.M, op.N, op.K, splits, batch, G != GATHER_NONE ? COST_GATHER : WGRAD ? COST_WGRAD : COST_PLAIN, WGRAD);
     if (narrow || (classes && tile >= TILE_64x128)) return launch<64, 64, 2, 2, 2, A_KM, B_KM, OutT, G>(op, A, B, st);
     switch (tile) {
     case TILE_256x256:

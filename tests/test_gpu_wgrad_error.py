@@ -61,3 +61,31 @@ def test_batched_weight_gradient_error(L, M, N, K, slices):
     torch.cuda.synchronize()
     ref = torch.stack([dY[l].double().t().contiguous() @ H[l].double() for l in range(L)])
     assert ((dU - ref).norm() / ref.norm()).item() <= bound(K, slices)
+
+
+# Every tile that weight gradients are given (rows, columns, waves down and across, stages), off its edges
+@pytest.mark.parametrize("M,N,K,slices,tile", [(3080, 1000, 8001, 3, "256,256,2,4,2"), (264, 4104, 6001, 5, "128,256,2,4,3"),
+                                               (200, 3080, 8201, 10, "128,128,2,4,2"), (104, 1000, 16001, 14, "64,128,2,4,4"),
+                                               (776, 200, 2001, 7, "64,64,2,2,4"), (24, 40, 70, 1, "64,64,2,2,4")])
+def test_weight_gradient_tiles(M, N, K, slices, tile):
+    with lrd.ProfileLog(2) as log:
+        error = dense_error(M, N, K, BF)
+    assert (log.rows()[0]["kernel"], log.rows()[0]["splits"]) == (f"gemm2_kernel<{tile},A_KM,B_KM,f32>", slices)
+    assert error <= bound(K, slices)
+
+
+@pytest.mark.parametrize("N,hw,C,S,slices,tile", [(37, 14, 128, 128, 12, "128,64,4,2,4"), (33, 7, 312, 312, 6, "128,128,2,4,2"),
+                                                  (21, 28, 72, 64, 40, "64,128,2,4,4"), (5, 9, 24, 40, 1, "64,64,2,2,4")])
+def test_convolution_weight_gradient_tiles(N, hw, C, S, slices, tile):
+    gen = torch.Generator(device="cuda").manual_seed(N + C)
+    geo = lrd.conv_geom(N, hw, hw, C, S, 1, 1, 3, 1, 1)
+    X, dY, W = normal(gen, N, hw, hw, C), normal(gen, N, hw, hw, S), normal(gen, S, 3, 3, C)
+    dW = torch.full((S, 3, 3, C), float("nan"), device="cuda")
+    ws = torch.empty(lrd.dense_conv_workspace_bytes(geo, lrd.BF16) + 16, dtype=torch.uint8, device="cuda")
+    with lrd.ProfileLog(2) as log:
+        lrd.dense_conv_bwd(dY, X, W, None, dW, geo, ws)
+        torch.cuda.synchronize()
+    assert (log.rows()[0]["kernel"], log.rows()[0]["splits"]) == (f"gemm2_kernel<{tile},A_KM,B_KM,f32,conv>", slices)
+    pad, rows = torch.nn.functional.pad(X.double(), (0, 0, 1, 1, 1, 1)), dY.double().reshape(-1, S).t().contiguous()
+    ref = torch.stack([torch.stack([rows @ pad[:, u:u + hw, v:v + hw].reshape(-1, C) for v in range(3)], 1) for u in range(3)], 1)
+    assert ((dW - ref).norm() / ref.norm()).item() <= bound(N * hw * hw, slices)
