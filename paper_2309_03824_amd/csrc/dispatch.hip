@@ -1,4 +1,5 @@
 // Engine selection for a single matrix product and the split-K policy.
+#include <algorithm>
 #include <atomic>
 #include <cstdio>
 #include <mutex>
@@ -95,6 +96,23 @@ int choose_splits_act(int64_t M, int64_t N, int64_t K, bool in_bf16)
     if (s > by_k) s = by_k;
     if (s > 8) s = 8;
     return s < 2 ? 1 : (int)s;
+}
+
+// The most rows of partial sums (slices x rows) of choose_splits_act over every number of rows up to M.  Fewer rows are
+// cut into more slices, so the product rises and falls; it peaks at the most rows that still get s slices, s = 2 .. 8.
+int64_t most_act_rows(int64_t M, int64_t N, int64_t K, bool in_bf16)
+{
+    auto rows = [&](int64_t m) {
+        const int s = choose_splits_act(m, N, K, in_bf16);
+        return s > 1 ? s * m : 0;
+    };
+    int64_t most = rows(M);
+    for (int s = 2; s <= 8; ++s) {
+        const int64_t tiles = std::min(255, 511 / (s - 1));       // ceil(512 / tiles) >= s, and fewer than 256
+        const int64_t m = std::min(M, 64 * (tiles / ceil_div(N, 64)));
+        if (m > 0) most = std::max(most, rows(m));
+    }
+    return most;
 }
 
 // Weight gradients of `batch` layers of one shape in one launch: 256 x 256 tiles over all members already give most

@@ -118,19 +118,12 @@ size_t partial_bytes(int64_t M, int64_t N, int64_t K)
 // every smaller number (a last batch runs in the workspace of the others).
 enum Tokens { THESE, UP_TO };
 
-// The same for a product whose result is a narrow activation.  Fewer tokens are cut into more slices, so the bytes
-// rise and fall with the tokens; the slices change only from one row of 64 x 64 tiles to the next, and from 256 tiles on
-// there are none.
+// The same for a product whose result is a narrow activation.
 size_t act_partial_bytes(int64_t M, int64_t N, int64_t K, lrd_dtype dt, Tokens tokens = THESE)
 {
-    auto bytes = [&](int64_t m) {
-        int s = choose_splits_act(m, N, K, dt == LRD_BF16);
-        return s > 1 ? round256((size_t)s * (size_t)m * (size_t)N * sizeof(float)) : 0;
-    };
-    size_t most = bytes(M);
-    if (tokens == UP_TO)
-        for (int64_t m = 64; m < M && ceil_div(m, 64) * ceil_div(N, 64) < 256; m += 64) most = std::max(most, bytes(m));
-    return most;
+    const int s = choose_splits_act(M, N, K, dt == LRD_BF16);
+    const int64_t rows = tokens == UP_TO ? most_act_rows(M, N, K, dt == LRD_BF16) : s > 1 ? s * M : 0;
+    return round256((size_t)rows * (size_t)N * sizeof(float));
 }
 
 // Split products of one linear pass run one after the other on the stream and share one region.

@@ -96,6 +96,7 @@ hipError_t apply_epilogue(const MatOp& op, hipStream_t st);        // unfused fo
 int choose_splits(int64_t M, int64_t N, int64_t K);
 // Split-K count for a product whose result is a narrow bf16 activation (1 = not split).
 int choose_splits_act(int64_t M, int64_t N, int64_t K, bool in_bf16);
+int64_t most_act_rows(int64_t M, int64_t N, int64_t K, bool in_bf16);
 int choose_splits_batched(int64_t M, int64_t N, int64_t K, int64_t batch);
 // Output tiles of the MFMA product kernel for long reductions, and the fastest of them for a product cut into
 // `splits` slices of K.
