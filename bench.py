@@ -1045,12 +1045,16 @@ def measure_peaks(torch, lrd):
 
 # HBM bytes per launch of the product kernels as the traffic counters saw them (FETCH_SIZE, WRITE_SIZE per
 # dispatch, scaled by what the same counters read for a plain copy of known size: 2.00 and 1.00), by kernel
-# and product shape; profiles/encoder_step_hbm_traffic.md holds the runs.  Reported only for a kernel and a
-# mix of shapes that were profiled as they are now.
+# and product shape; profiles/encoder_step_hbm_traffic.md holds the runs.  A name carries tile, waves, stages,
+# operand layouts and epilogue; reported only for a kernel and a mix of shapes that were profiled.
 MIB = float(1 << 20)
 PROFILED_TRAFFIC = {
-    "gemm2_kernel<128,128,2,4,A_KC,B_KC,bf16>": {"8192x4096x256+act": (20.2 + 128.1) * MIB, "3 x 8192x1024x256": (24.2 + 48.0) * MIB,
-                                                 "8192x1024x256": (8.2 + 16.0) * MIB},
+    "gemm2_kernel<64,128,2,4,4,A_KC,B_KC,bf16>": {"8192x256x1024": (20.1 + 4.0) * MIB, "8192x256x4096": (80.1 + 4.0) * MIB},
+    "gemm2_kernel<64,128,2,4,4,A_KC,B_KM,bf16>": {"8192x256x1024": (20.1 + 4.0) * MIB, "8192x256x4096": (80.1 + 4.0) * MIB},
+    "gemm2_kernel<128,128,2,4,2,A_KC,B_KC,bf16,gelu>": {"8192x4096x256+act": (20.1 + 128.4) * MIB},
+    "gemm2_kernel<128,128,2,4,1,A_KC,B_KM,bf16,gelu_grad>": {"8192x4096x256+act": (84.1 + 64.0) * MIB},
+    "gemm2_kernel<128,128,2,4,2,A_KC,B_KC,bf16>": {"3 x 8192x1024x256": (17.1 + 48.0) * MIB, "8192x1024x256": (8.1 + 16.0) * MIB},
+    "gemm2_kernel<128,128,2,4,2,A_KC,B_KM,bf16>": {"8192x1024x256": (8.1 + 16.0) * MIB},
 }
 
 
@@ -1083,8 +1087,7 @@ def kernel_roofline(rows):
     if seen and all(k in seen for k in shapes):
         traffic = sum(seen[k] * c for k, c in shapes.items()) / n
     roof.update(traffic=traffic, traffic_note="HBM bytes per launch from rocprofv3 FETCH_SIZE / WRITE_SIZE runs of this command, copy-calibrated "
-                "(profiles/encoder_step_hbm_traffic.md, taken at commit d2842f5; csrc/mfma_gemm2.hip's kernel body is unchanged since); "
-                "null when this kernel or its shapes were not the profiled ones", kernel=name, avg_us=total_us / n, launches=n, bytes_per_launch=nbytes / n, flops_per_launch=flops / n,
+                "(profiles/encoder_step_hbm_traffic.md, taken at commit b0766fe); null when this kernel or its shapes were not the profiled ones", kernel=name, avg_us=total_us / n, launches=n, bytes_per_launch=nbytes / n, flops_per_launch=flops / n,
                 share_of_logged_time=total_us / sum(r["us"] for r in rows), shapes=shapes,
                 note="algorithmic bytes per launch = both operands read once + result written once (+ the activation tensor the "
                      "epilogue writes or reads); duration from HIP events on the launch stream around every launch of this kernel "
