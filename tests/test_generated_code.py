@@ -7,15 +7,18 @@ import subprocess
 
 import pytest
 
-from conftest import ROOT
+from paper_2309_03824_amd import build
 
-OBJ = os.path.join(ROOT, "paper_2309_03824_amd", "_build", "mfma_gemm2.hip.o")
+OBJ = os.path.join(build.OBJ, "mfma_gemm2.hip.o")
 LLVM = "/opt/rocm/llvm/bin/"
 WAIT_STATES = 5      # between a vector instruction's write of a scalar register and a vector-memory read of it
 
 
 def listing(tmp_path):
     """{kernel: [(address, mnemonic, operands, branch target)]}"""
+    if not os.path.exists(OBJ):
+        os.makedirs(build.OBJ, exist_ok=True)
+        build._compile(os.path.join(build.CSRC, "mfma_gemm2.hip"))
     bundle, code = str(tmp_path / "bundle"), str(tmp_path / "code")
     subprocess.run([LLVM + "llvm-objcopy", "--dump-section", ".hip_fatbin=" + bundle, OBJ, str(tmp_path / "rest.o")], check=True)
     subprocess.run([LLVM + "clang-offload-bundler", "--unbundle", "--type=o", "--targets=hipv4-amdgcn-amd-amdhsa--gfx950", "--input=" + bundle,
