@@ -238,6 +238,7 @@ hipError_t run_matop(const MatOp& op_in, hipStream_t st)
         e = flip_conv_weights(op.B, op.scratch, op.cs.O, op.cs.I, op.cs.k, st);
         if (e == hipSuccess) e = mfma_gemm2(flipped, st);
     }
+    else if (mfma_wide_supported(op)) e = mfma_wide(op, st);
     else if (mfma_gemm2_supported(op)) e = mfma_gemm2(op, st);
     else {
         epilogue_done = op.epilogue == EPI_NONE;

@@ -83,6 +83,8 @@ bool mfma_matop_supported(const MatOp& op);                         // bf16 MFMA
 hipError_t mfma_matop(const MatOp& op, hipStream_t st);
 bool mfma_gemm2_supported(const MatOp& op);                        // aligned fast path covers it?
 hipError_t mfma_gemm2(const MatOp& op, hipStream_t st);
+bool mfma_wide_supported(const MatOp& op);                         // short reduction, wide result
+hipError_t mfma_wide(const MatOp& op, hipStream_t st);
 bool f32_gemm_supported(const MatOp& op);                          // fp32 operands, no gather
 hipError_t f32_gemm(const MatOp& op, hipStream_t st);
 bool conv_direct_supported(const MatOp& op);                       // 3 x 3 stride-1 convolution with 32 / 64 channels?
