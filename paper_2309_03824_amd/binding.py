@@ -196,6 +196,10 @@ def _dt(t) -> int:
 
 def _stream(stream):
     if stream is None:
+        # the raw handle of the current device's current stream: the same as current_stream().cuda_stream, which takes 2.8 us
+        # to make two Python objects on the way, as much as a launch (48 x 1024 -> 4096 at rank 256: 12.5 -> 9.9 us a call)
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
