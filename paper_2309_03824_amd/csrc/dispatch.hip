@@ -238,6 +238,8 @@ hipError_t run_matop(const MatOp& op_in, hipStream_t st)
         e = flip_conv_weights(op.B, op.scratch, op.cs.O, op.cs.I, op.cs.k, st);
         if (e == hipSuccess) e = mfma_gemm2(flipped, st);
     }
+    else if (mfma_small_fwd_supported(op)) e = mfma_small_fwd(op, st);
+    else if (mfma_small_data_supported(op)) e = mfma_small_bwd(&op, nullptr, nullptr, st);
     else if (mfma_wide_supported(op)) e = mfma_wide(op, st);
     else if (mfma_gemm2_supported(op)) e = mfma_gemm2(op, st);
     else {
@@ -259,6 +261,23 @@ hipError_t run_matop(const MatOp& op_in, hipStream_t st)
     }
     if (e != hipSuccess || epilogue_done) return e;
     return apply_epilogue(op, st);
+}
+
+hipError_t run_small_bwd(const MatOp* data, const MatOp* grad, const SmallSums* sums, hipStream_t st)
+{
+    // each product has a record of its own, around the launch that they share
+    const MatOp* ops[2] = {data, grad};
+    hipEvent_t ev0[2], ev1[2];
+    int logged[2] = {-1, -1};
+    for (int i = 0; i < 2; ++i)
+        if (ops[i] && (logged[i] = log_begin(&ev0[i], &ev1[i])) >= 0) (void)hipEventRecord(ev0[i], st);
+    const hipError_t e = mfma_small_bwd(data, grad, sums, st);
+    for (int i = 0; i < 2; ++i)
+        if (logged[i] >= 0) {
+            (void)hipEventRecord(ev1[i], st);
+            log_end(logged[i], ops[i]->role, ops[i]->gather, ops[i]->epilogue, 1, ops[i]->M, ops[i]->N, ops[i]->K, 1);
+        }
+    return e;
 }
 
 }  // namespace lrd

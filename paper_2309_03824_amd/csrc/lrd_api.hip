@@ -381,39 +381,56 @@ lrd_status linear_bwd_impl(const void* dY, const void* X, const void* H, const v
     }
     if (!cv.ok) return LRD_ERR_WORKSPACE;
 
+    MatOp d1, d2;
     if (need_dH) {
-        bool fused = false;
-        if (dt == LRD_BF16 && dX) {
-            ChainOp ch;
-            ch.A = dY; ch.lda = out;
-            ch.B1 = U; ch.b1_sn = 1; ch.b1_sk = r;     // B1(j, o) = U[o][j]
-            ch.B2 = V; ch.b2_sn = 1; ch.b2_sk = in;    // B2(i, j) = V[j][i]
-            ch.C = dX; ch.ldc = in;
-            ch.mid_save = train_v ? dH : nullptr; ch.ldmid = r;
-            ch.M = T; ch.K1 = out; ch.R = r; ch.N2 = in;
-            ch.role = LRD_ROLE_DGRAD_UP;
-            if (want_fusion(ch)) {
-                LRD_TRY(run_chain(ch, st));
-                if (Z_in) LRD_TRY(gelu_bwd(dX, Z_in, dX, T * in, true, st));
-                fused = true;
-            }
+        d1 = nn(dY, out, U, r, dH, r, T, r, out, dt);
+        d1.role = LRD_ROLE_DGRAD_UP;
+    }
+    if (dX) {
+        d2 = nn(dH, r, V, in, dX, in, T, in, r, dt);
+        d2.role = LRD_ROLE_DGRAD_DOWN;
+        if (Z_in) {
+            d2.epilogue = EPI_ACT_GRAD;
+            d2.aux = const_cast<void*>(Z_in);
+            d2.ldaux = in;
         }
-        if (!fused) {
-            MatOp d1 = nn(dY, out, U, r, dH, r, T, r, out, dt);
-            d1.role = LRD_ROLE_DGRAD_UP;
-            share_splits(d1, region, dt, SPLIT_ACT);
-            LRD_TRY(run_matop(d1, st));
-            if (dX) {
-                MatOp d2 = nn(dH, r, V, in, dX, in, T, in, r, dt);
-                d2.role = LRD_ROLE_DGRAD_DOWN;
-                if (Z_in) {
-                    d2.epilogue = EPI_ACT_GRAD;
-                    d2.aux = const_cast<void*>(Z_in);
-                    d2.ldaux = in;
-                }
-                LRD_TRY(run_matop(d2, st));
-            }
+    }
+    bool fused = false;
+    ChainOp ch;
+    if (dt == LRD_BF16 && dX) {
+        ch.A = dY; ch.lda = out;
+        ch.B1 = U; ch.b1_sn = 1; ch.b1_sk = r;     // B1(j, o) = U[o][j]
+        ch.B2 = V; ch.b2_sn = 1; ch.b2_sk = in;    // B2(i, j) = V[j][i]
+        ch.C = dX; ch.ldc = in;
+        ch.mid_save = train_v ? dH : nullptr; ch.ldmid = r;
+        ch.M = T; ch.K1 = out; ch.R = r; ch.N2 = in;
+        ch.role = LRD_ROLE_DGRAD_UP;
+        fused = want_fusion(ch);
+    }
+    const MatOp *data1 = need_dH ? &d1 : nullptr, *data2 = dX ? &d2 : nullptr, *grad1 = train_u ? &wu : nullptr, *grad2 = train_v ? &wv : nullptr;
+    if (!fused && (data1 || grad1) && mfma_small_bwd_supported(data1, grad1) && mfma_small_bwd_supported(data2, grad2)) {
+        // few tokens: two launches of what does not wait for one another (the region of the sliced products is free)
+        if (train_u && !H) {
+            MatOp re = nt(X, in, V, in, Hre, r, T, r, in, dt, false);
+            share_splits(re, region, dt, SPLIT_ACT);
+            LRD_TRY(run_matop(re, st));
         }
+        SmallSums sums;
+        sums.dY = dY; sums.part = (float*)region; sums.out = dbias; sums.T = T; sums.n = out;
+        const bool with_sums = dbias && ceil_div(T, 32) * out * (int64_t)sizeof(float) <= (int64_t)region_bytes;
+        LRD_TRY(run_small_bwd(data1, grad1, with_sums ? &sums : nullptr, st));
+        sums.dY = nullptr;
+        LRD_TRY(run_small_bwd(data2, grad2, with_sums ? &sums : nullptr, st));
+        if (dbias && !with_sums) LRD_TRY(column_sums(dY, dbias, T, out, true, ws, cv.used, st));
+        return LRD_OK;
+    }
+    if (fused) {
+        LRD_TRY(run_chain(ch, st));
+        if (Z_in) LRD_TRY(gelu_bwd(dX, Z_in, dX, T * in, true, st));
+    } else if (need_dH) {
+        share_splits(d1, region, dt, SPLIT_ACT);
+        LRD_TRY(run_matop(d1, st));
+        if (dX) LRD_TRY(run_matop(d2, st));
     }
     if (train_u) {
         if (!H) {

@@ -85,6 +85,19 @@ bool mfma_gemm2_supported(const MatOp& op);                        // aligned fa
 hipError_t mfma_gemm2(const MatOp& op, hipStream_t st);
 bool mfma_wide_supported(const MatOp& op);                         // short reduction, wide result
 hipError_t mfma_wide(const MatOp& op, hipStream_t st);
+// Few tokens: forward products; and the products of a backward pass that share a launch (see mfma_small.hip).
+bool mfma_small_fwd_supported(const MatOp& op);
+hipError_t mfma_small_fwd(const MatOp& op, hipStream_t st);
+bool mfma_small_data_supported(const MatOp& op);                    // dH = dY.U, dX = dH.V
+bool mfma_small_bwd_supported(const MatOp* data, const MatOp* grad);     // one of those, and dU = dY^T.H or dV = dH^T.X, in a launch
+struct SmallSums {                                                  // column sums of dY [T x n]
+    const void* dY = nullptr;                                       // given: to one partial row per 32 rows; null: their sum to `out`
+    float* part = nullptr;
+    float* out = nullptr;
+    int64_t T = 0, n = 0;
+};
+hipError_t mfma_small_bwd(const MatOp* data, const MatOp* grad, const SmallSums* sums, hipStream_t st);     // any of them null
+hipError_t run_small_bwd(const MatOp* data, const MatOp* grad, const SmallSums* sums, hipStream_t st);      // with the event log
 bool f32_gemm_supported(const MatOp& op);                          // fp32 operands, no gather
 hipError_t f32_gemm(const MatOp& op, hipStream_t st);
 bool conv_direct_supported(const MatOp& op);                       // 3 x 3 stride-1 convolution with 32 / 64 channels?

@@ -1,0 +1,100 @@
+"""Layers with few tokens: the products that cut K over the waves of a workgroup and share launches in the backward pass, at rows,
+columns and k that end inside a block, a step and a wave's share; against fp32 products of the same bf16 operands."""
+import pytest
+import torch
+
+from paper_2309_03824_amd import binding as lrd
+
+BF, F32 = torch.bfloat16, torch.float32
+
+# (tokens, in, out, rank) and how the waves cut the four products H, Y, dH, dX (8: K in eight, 2: in two); "-": output tiles
+SHAPES = [((1, 64, 96, 32), "2222"), ((7, 1024, 160, 64), "8282"), ((33, 96, 1056, 96), "2282"), ((48, 1024, 4096, 256), "8888"),
+          ((100, 2080, 544, 160), "8882"), ((509, 768, 3072, 192), "8-82"), ((509, 544, 512, 256), "8882"), ((1000, 512, 480, 128), "8282"),
+          ((1024, 1536, 256, 96), "8282")]
+
+
+def rel(a, b):
+    return ((a.float() - b).norm() / b.norm()).item()
+
+
+def inputs(T, n_in, n_out, r):
+    gen = torch.Generator(device="cuda").manual_seed(T + n_in + r)
+
+    def normal(*shape, std=1.0, dt=BF):
+        return torch.randn(*shape, device="cuda", generator=gen).mul_(std).to(dt)
+
+    return (normal(T, n_in), normal(T, n_out), normal(n_out, r, std=r ** -0.5), normal(r, n_in, std=n_in ** -0.5), normal(n_out, std=0.1, dt=F32),
+            normal(T, n_in))
+
+
+def nan(*shape, dt=BF):
+    return torch.full(shape, float("nan"), device="cuda", dtype=dt)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,cuts", SHAPES)
+@pytest.mark.parametrize("with_h,with_dx,act", [(True, True, False), (False, True, True), (True, False, False)])
+def test_small_layers(shape, cuts, with_h, with_dx, act):
+    T, n_in, n_out, r = shape
+    X, dY, U, V, bias, Z = inputs(*shape)
+    Y, H, dX = nan(T, n_out), nan(T, r), nan(T, n_in)
+    dU, dV, db = nan(n_out, r, dt=F32), nan(r, n_in, dt=F32), nan(n_out, dt=F32)
+    ws = torch.empty(lrd.linear_workspace_bytes(T, n_in, n_out, r, lrd.BF16, 0), dtype=torch.uint8, device="cuda")
+    with lrd.ProfileLog(16) as log:
+        lrd.linear_fwd(X, V, U, bias, Y, H, ws)
+        lrd.linear_bwd_act(dY, X, H if with_h else None, V, U, dX if with_dx else None, dV, dU, db, 0, Z if act else None,
+                           lrd.ACT_GELU if act else lrd.ACT_NONE, ws)
+        torch.cuda.synchronize()
+    names = [row["kernel"] for row in log.rows()]
+    want = [f"small_fwd_kernel<{c}>" if c != "-" else None for c in cuts[:2]]
+    want += [] if with_h else want[:1]
+    want += [f"small_bwd_kernel<{cuts[2]}>"] * 2 + [f"small_bwd_kernel<{cuts[3] if with_dx else 2}>"] * (2 if with_dx else 1)
+    assert len(names) == len(want) and all(w is None and n.startswith("gemm2") or n == w for n, w in zip(names, want)), names
+    # one rounding to bf16 is at most 2^-9 of a value; dX and dV go through a dH rounded on either side, whose roundings may
+    # differ by one step where the fp32 sums do; the gradient of GELU rounds dX once more (and is off by 2.6e-4 itself)
+    dH = (dY.float() @ U.float()).to(BF).float()
+    assert rel(H, X.float() @ V.float().t()) < 2e-3
+    assert rel(Y, H.float() @ U.float().t() + bias) < 2e-3
+    if with_dx:
+        z = Z.float().requires_grad_()
+        slope = torch.autograd.grad(torch.nn.functional.gelu(z).sum(), z)[0] if act else 1.0
+        assert rel(dX, (dH @ V.float()) * slope) < (7e-3 if act else 4e-3)
+    assert rel(dU, dY.float().t() @ H.float()) < 2e-5
+    assert rel(dV, dH.t() @ X.float()) < 2e-3
+    assert rel(db, dY.double().sum(0)) < 1e-6
+
+
+@pytest.mark.gpu
+def test_small_frozen_factors_and_no_bias():
+    """Jobs that are absent from a launch: each mask gives the same bits for what it computes, and leaves the rest alone."""
+    T, n_in, n_out, r = 200, 512, 768, 128
+    X, dY, U, V, bias, _ = inputs(T, n_in, n_out, r)
+    ws = torch.empty(lrd.linear_workspace_bytes(T, n_in, n_out, r, lrd.BF16, 0), dtype=torch.uint8, device="cuda")
+    Y, H = nan(T, n_out), nan(T, r)
+    lrd.linear_fwd(X, V, U, bias, Y, H, ws)
+    full = None
+    for mask in range(4):
+        for with_dx, with_bias in ((True, True), (True, False), (False, False)):
+            dX, dU, dV, db = nan(T, n_in), nan(n_out, r, dt=F32), nan(r, n_in, dt=F32), nan(n_out, dt=F32)
+            lrd.linear_bwd(dY, X, H, V, U, dX if with_dx else None, None if mask & 1 else dV, None if mask & 2 else dU, db if with_bias else None, mask, ws)
+            torch.cuda.synchronize()
+            full = full or (dX, dU, dV, db)
+            for got, ref, there in zip((dX, dU, dV, db), full, (with_dx, not mask & 2, not mask & 1, with_bias)):
+                assert torch.equal(got, ref) if there else got.isnan().all()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("T", [1, 300, 1024])
+def test_small_weight_gradients_are_as_exact_as_their_chains(T):
+    """Eight waves, each a chain of additions a 32nd of its rows long: against 64 bits, 2^-24 times the root of half the chain and
+    the eight sums after it, with a factor of two for the products' own sums of 32."""
+    n_in, n_out, r = 256, 320, 64
+    X, dY, U, V, bias, _ = inputs(T, n_in, n_out, r)
+    ws = torch.empty(lrd.linear_workspace_bytes(T, n_in, n_out, r, lrd.BF16, 0), dtype=torch.uint8, device="cuda")
+    Y, H, dX = nan(T, n_out), nan(T, r), nan(T, n_in)
+    dU, dV = nan(n_out, r, dt=F32), nan(r, n_in, dt=F32)
+    lrd.linear_fwd(X, V, U, bias, Y, H, ws)
+    lrd.linear_bwd(dY, X, H, V, U, dX, dV, dU, None, 0, ws)
+    torch.cuda.synchronize()
+    chain = (T + 255) // 256 + 8
+    assert ((dU.double() - (ref := dY.double().t() @ H.double())).norm() / ref.norm()).item() < 2 ** -24 * 2 * (8 + chain / 2) ** 0.5
