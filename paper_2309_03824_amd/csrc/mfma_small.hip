@@ -32,7 +32,7 @@ __device__ __forceinline__ bf16x8 transposed(const char* lo_at, const char* hi_a
     return __builtin_bit_cast(bf16x8, v);
 }
 
-// C[M x N] (bf16) = A . B^T: K a multiple of 32, N of 32.
+// C[M x N] (bf16) = A . B^T: K and N multiples of 16.
 struct ActJob {
     const bf16_t* A;
     const bf16_t* B;
@@ -68,26 +68,26 @@ __device__ __forceinline__ void act_tile(const ActJob& g, int block, char* smem,
     const int lane = tid & 63, wave = (int)uni(tid >> 6);
     const int ks = wave % KS, nb = wave / KS;
     const int q = lane >> 4, r16 = lane & 15;
-    const int m0 = block / g.col_blocks * 32, n0 = block % g.col_blocks * (32 * NB), col = n0 + nb * 32;
+    const int m0 = block / g.col_blocks * 32, n0 = block % g.col_blocks * (32 * NB), col = min(n0 + nb * 32, g.N);
     const int per = ((g.K + KS - 1) / KS + 31) & ~31, kbeg = min(ks * per, g.K), kend = min(kbeg + per, g.K);
-    const int steps = col < g.N ? (kend - kbeg + 63) / 64 : 0;
-    const int rows = min(g.M - m0, 32);
+    const int rows = min(g.M - m0, 32), cols = min(g.N - col, 32);
+    const int steps = cols > 0 ? (kend - kbeg + 63) / 64 : 0;
     char* slab = smem + wave * SLAB;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)slab;
 
     // descriptors end with the wave's last k (k-contiguous: of its last row; other rows are masked in the last step)
     const char* abase = uni_ptr(g.A + (int64_t)m0 * g.lda + kbeg);
     uint32_t aspan = uni((uint32_t)(((int64_t)(rows - 1) * g.lda + kend - kbeg) * 2));
-    const int bcol = min(col, g.N - 32);
-    const char* bbase = uni_ptr(B_KM ? g.B + (int64_t)kbeg * g.ldb + bcol : g.B + (int64_t)bcol * g.ldb + kbeg);
-    uint32_t bspan = uni(B_KM ? 0u : (uint32_t)((31ll * g.ldb + kend - kbeg) * 2));
+    const char* bbase = uni_ptr(B_KM ? g.B + (int64_t)kbeg * g.ldb + col : g.B + (int64_t)col * g.ldb + kbeg);
+    uint32_t bspan = uni(cols > 0 && !B_KM ? (uint32_t)(((int64_t)(cols - 1) * g.ldb + kend - kbeg) * 2) : 0u);
     int64_t bld = (int64_t)uni(g.ldb);
-    int krows = (int)uni((uint32_t)(kend - kbeg));
+    int krows = (int)uni((uint32_t)(kend - kbeg)), bcols = (int)uni((uint32_t)cols);
     settle(abase, aspan);
     settle(bbase, bspan);
     settle(bbase, bld, krows);
+    settle(bbase, bld, bcols);
     uint32_t aoff[4], boff[4];
-    int ak[4], bk[4];
+    int ak[4];
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
         const int r = p * 8 + (lane >> 3);
@@ -96,12 +96,10 @@ __device__ __forceinline__ void act_tile(const ActJob& g, int block, char* smem,
         if (B_KM) {
             // [64 k][32 columns], 64 bytes a row; chunks 0, 1 and 2, 3 change places in rows k & 8, so that the rows of one
             // transposing read, k .. k + 3 and those 8 further, fall on different banks
-            const int k = p * 16 + (lane >> 2);
-            bk[p] = k;
-            boff[p] = ((uint32_t)k * g.ldb + ((lane & 3) ^ (k & 8 ? 2 : 0)) * 8) * 2u;
+            const int k = p * 16 + (lane >> 2), c = ((lane & 3) ^ (k & 8 ? 2 : 0)) * 8;
+            boff[p] = c < cols ? ((uint32_t)k * g.ldb + c) * 2u : BUF_OOB;
         } else {
-            bk[p] = ak[p];
-            boff[p] = ((uint32_t)r * g.ldb + bk[p]) * 2u;
+            boff[p] = r < cols ? ((uint32_t)r * g.ldb + ak[p]) * 2u : BUF_OOB;
         }
     }
     auto load = [&](int t) {
@@ -111,8 +109,8 @@ __device__ __forceinline__ void act_tile(const ActJob& g, int block, char* smem,
         for (int p = 0; p < 4; ++p) load_to_lds(to + p * 1024, abase + k0 * 2, aspan - k0 * 2, ak[p] < left ? aoff[p] : BUF_OOB);
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
-            if constexpr (B_KM) load_to_lds(to + 4096 + p * 1024, bbase + k0 * bld * 2, (uint32_t)((min(left, 64) - 1) * bld + 32) * 2u, boff[p]);
-            else load_to_lds(to + 4096 + p * 1024, bbase + k0 * 2, bspan - k0 * 2, bk[p] < left ? boff[p] : BUF_OOB);
+            if constexpr (B_KM) load_to_lds(to + 4096 + p * 1024, bbase + k0 * bld * 2, (uint32_t)((min(left, 64) - 1) * bld + bcols) * 2u, boff[p]);
+            else load_to_lds(to + 4096 + p * 1024, bbase + k0 * 2, bspan - k0 * 2, ak[p] < left ? boff[p] : BUF_OOB);
         }
     };
     const uint32_t fk = r16 * 128 + ((q ^ kc_swz(r16)) << 4);      // k-contiguous: block of 16 rows at + 2048, second 32 k at ^ 64
@@ -350,6 +348,7 @@ hipError_t allow_lds(Kernel kern, int bytes, bool& done)
     return e;
 }
 
+constexpr int64_t MOST_TOKENS = 1024;      // above, the tiles are as fast or faster in every shape tried
 // How the waves cut a product: its K in eight, or in two with four blocks side by side; the cheaper of the two by rounds of
 // workgroups over the chip times the steps of a wave (of 64 k) and about three more for its start and its end.
 struct Cut {
@@ -380,14 +379,14 @@ ActJob act_job(const MatOp& op, bool b_km)
 
 bool act_ok(const MatOp& op)
 {
-    return mfma_gemm2_supported(op) && op.gather == GATHER_NONE && !op.out_f32 && op.batch == 1 && op.a_sk == 1 && op.K % 32 == 0 && op.N % 32 == 0 &&
-           op.M < 32768 && op.N < 65536 && op.ldc <= BUF_MAX_LD && op.ldaux <= BUF_MAX_LD &&
+    return mfma_gemm2_supported(op) && op.gather == GATHER_NONE && !op.out_f32 && op.batch == 1 && op.a_sk == 1 && op.K % 16 == 0 && op.N % 16 == 0 &&
+           op.M <= MOST_TOKENS && op.N < 65536 && op.ldc <= BUF_MAX_LD && op.ldaux <= BUF_MAX_LD &&
            (op.epilogue == EPI_NONE || (op.epilogue == EPI_ACT_GRAD) == (op.b_sk != 1));
 }
 
 // A product by itself: one round of workgroups, and few enough steps that the tiles' wider blocks, which bring each operand
-// less often, do not win (1536 x 192 over 768 cut in two, six steps: 13.1 against 12.5 us with the product after it; 1024 x 1024
-// over 4096 cut in two, 32 steps: 34.6 against 28.2 us; 1024 x 256 over 4096 cut in eight, eight steps: even).
+// less often, do not win (1024 x 1024 over 4096 cut in two, 32 steps: 34.6 against 28.2 us with the product after it; 1024 x 256
+// over 4096 cut in eight, eight steps: even).
 bool alone_ok(const MatOp& op)
 {
     if (!act_ok(op)) return false;
@@ -424,7 +423,7 @@ bool mfma_small_bwd_supported(const MatOp* data, const MatOp* grad)
 {
     int64_t work = 0;
     if (data) {
-        if (data->b_sk == 1 || !act_ok(*data) || data->M > 1024) return false;
+        if (data->b_sk == 1 || !act_ok(*data)) return false;
         const Cut c = cut(*data);
         work += c.blocks * (c.steps + 3);
     }
@@ -433,7 +432,7 @@ bool mfma_small_bwd_supported(const MatOp* data, const MatOp* grad)
         MatOp op = *grad;
         op.K = std::max<int64_t>(op.K, 8);
         if (!mfma_gemm2_supported(op) || op.gather != GATHER_NONE || !op.out_f32 || op.batch != 1 || op.a_sk == 1 || op.b_sk == 1 || op.sgd || op.crop ||
-            op.K > 1024 || op.M >= 65536 || op.N >= 65536 || op.ldc > BUF_MAX_LD)
+            op.K > MOST_TOKENS || op.M >= 65536 || op.N >= 65536 || op.ldc > BUF_MAX_LD)
             return false;
         const int64_t blocks = ceil_div(op.M, 64) * ceil_div(op.N, 64);
         work += (blocks + std::max<int64_t>(0, blocks - 256)) * (2 * ceil_div(op.K, 512) + 3);

@@ -10,7 +10,7 @@ BF, F32 = torch.bfloat16, torch.float32
 # (tokens, in, out, rank) and how the waves cut the four products H, Y, dH, dX (8: K in eight, 2: in two); "-": output tiles
 SHAPES = [((1, 64, 96, 32), "2222"), ((7, 1024, 160, 64), "8282"), ((33, 96, 1056, 96), "2282"), ((48, 1024, 4096, 256), "8888"),
           ((100, 2080, 544, 160), "8882"), ((509, 768, 3072, 192), "8-82"), ((509, 544, 512, 256), "8882"), ((1000, 512, 480, 128), "8282"),
-          ((1024, 1536, 256, 96), "8282")]
+          ((1024, 1536, 256, 96), "8282"), ((300, 208, 336, 48), "8282"), ((130, 1040, 1136, 144), "8888")]
 
 
 def rel(a, b):
