@@ -81,112 +81,58 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void f32_gemm_kernel(F32Operand 
                                                                      const float* __restrict__ bias, float* __restrict__ partial, int M,
                                                                      int N, int k_per_split)
 {
-    constexpr int E = 16 * T, NT = 64 * WM * WN * KS, LDT = E + 4;
-    __shared__ float sums[KS][WM * WN][E * LDT];
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int ks = wave % KS, blk = wave / KS, wm = blk / WN, wn = blk % WN;
-    const int m0 = blockIdx.x * E * WM, n0 = blockIdx.y * E * WN;
-    const int mrow = m0 + wm * E, nrow = n0 + wn * E;
-    const int kbeg = blockIdx.z * k_per_split, kend = min(A.K, kbeg + k_per_split);
+    const unsigned bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
+#include "f32_tile.inc"
+}
 
-    f32x4 acc[T][T];
-#pragma unroll
-    for (int i = 0; i < T; ++i)
-#pragma unroll
-        for (int j = 0; j < T; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+struct F32Job {
+    F32Operand A, B;
+    float* C;
+    int64_t ldc;
+    const float* bias;
+    int M, N, K;
+};
+// The same tile with all of K, as one of the jobs of a launch.
+template <int T, bool AKM>
+__device__ __forceinline__ void f32_job_tile(const F32Operand& A, const F32Operand& B, float* C, int64_t ldc, const float* bias, int M, int N, int k_per_split,
+                                             unsigned bx, unsigned by)
+{
+    constexpr int WM = 1, WN = 1, KS = 8, DEPTH = T == 1 ? 8 : 4;
+    constexpr bool BKM = true;
+    constexpr unsigned bz = 0;
+    constexpr float* partial = nullptr;
+#include "f32_tile.inc"
+}
 
-    if (mrow < M && nrow < N) {
-        F32Frag<T, AKM> a[DEPTH];
-        F32Frag<T, BKM> b[DEPTH];
-        auto multiply = [&](int at) {
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-#pragma unroll
-                for (int i = 0; i < T; ++i)
-#pragma unroll
-                    for (int j = 0; j < T; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[at].v[j][c], a[at].v[i][c], acc[i][j], 0, 0, 0);
-        };
-        const int whole = (kend - kbeg) / 16;                                // steps without a tail
-        const int mine = whole > ks ? (whole - ks + KS - 1) / KS : 0;
-        auto fetch = [&](int s, int at) {
-            const int k = kbeg + 16 * (ks + s * KS);
-            a[at].template load<false>(A, mrow, k, kend, lane);
-            b[at].template load<false>(B, nrow, k, kend, lane);
-        };
-#pragma unroll
-        for (int d = 0; d < DEPTH - 1; ++d)
-            if (d < mine) fetch(d, d);
-        int s = 0;
-        for (; s + 2 * DEPTH - 1 <= mine; s += DEPTH) {
-#pragma unroll
-            for (int d = 0; d < DEPTH; ++d) {
-                fetch(s + d + DEPTH - 1, (d + DEPTH - 1) % DEPTH);
-                multiply(d);
-            }
-        }
-        for (; s < mine; s += DEPTH) {
-#pragma unroll
-            for (int d = 0; d < DEPTH; ++d) {
-                if (s + d + DEPTH - 1 < mine) fetch(s + d + DEPTH - 1, (d + DEPTH - 1) % DEPTH);
-                if (s + d < mine) multiply(d);
-            }
-        }
-        if (kbeg + 16 * whole < kend && whole % KS == ks) {
-            a[0].template load<true>(A, mrow, kbeg + 16 * whole, kend, lane);
-            b[0].template load<true>(B, nrow, kbeg + 16 * whole, kend, lane);
-            multiply(0);
-        }
-    }
-    // roles swapped: a lane holds row m = lane & 15 of its block, columns 4 (lane >> 4) + e
-    {
-        const int i16 = lane & 15, g = lane >> 4;
-#pragma unroll
-        for (int i = 0; i < T; ++i)
-#pragma unroll
-            for (int j = 0; j < T; ++j)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int m = AKM ? T * i16 + i : 16 * i + i16;
-                    const int n = BKM ? T * (4 * g + e) + j : 16 * j + 4 * g + e;
-                    sums[ks][blk][m * LDT + n] = acc[i][j][e];
-                }
-    }
-    __syncthreads();
-    float* out = partial ? partial + (int64_t)blockIdx.z * M * N : C;
-    const int64_t ldo = partial ? (int64_t)N : ldc;
-    constexpr int QR = E / 4, QB = E * QR;      // groups of four columns per row and per block
-    for (int q = tid; q < WM * WN * QB; q += NT) {
-        const int bk = q / QB, ml = q / QR % E, nl = q % QR * 4;
-        f32x4 s = *reinterpret_cast<const f32x4*>(&sums[0][bk][ml * LDT + nl]);
-#pragma unroll
-        for (int z = 1; z < KS; ++z) s += *reinterpret_cast<const f32x4*>(&sums[z][bk][ml * LDT + nl]);
-        const int m = m0 + bk / WN * E + ml, n = n0 + bk % WN * E + nl;
-        if (m >= M) continue;
-        if (n + 3 < N) {
-            if (bias) s += *reinterpret_cast<const f32x4u*>(bias + n);
-            *reinterpret_cast<f32x4u*>(out + (int64_t)m * ldo + n) = s;
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (n + e < N) out[(int64_t)m * ldo + n + e] = s[e] + (bias ? bias[n + e] : 0.f);
-        }
-    }
+// A data gradient and a weight gradient that do not wait for one another, in one launch: with few tokens neither fills the chip
+// and 2.5 us of each is the launch (256 x 768 x 768 layer at rank 208, first factor frozen: a pass 23.2 -> 20.6 us).
+template <int TD, int TW>
+__global__ __launch_bounds__(512) void f32_pair_kernel(F32Job d, int d_rows, int d_blocks, F32Job w, int w_rows)
+{
+    const int block = blockIdx.x - d_blocks;
+    if (block < 0) f32_job_tile<TD, false>(d.A, d.B, d.C, d.ldc, d.bias, d.M, d.N, d.K, blockIdx.x % d_rows, blockIdx.x / d_rows);
+    else f32_job_tile<TW, true>(w.A, w.B, w.C, w.ldc, w.bias, w.M, w.N, w.K, block % w_rows, block / w_rows);
+}
+
+F32Job f32_job(const MatOp& op)
+{
+    const bool akm = op.a_sk != 1, bkm = op.b_sk != 1;
+    return {{(const float*)op.A, akm ? op.a_sk : op.a_sm, (int)op.M, (int)op.K}, {(const float*)op.B, bkm ? op.b_sk : op.b_sn, (int)op.N, (int)op.K},
+            (float*)op.C, op.ldc, op.bias, (int)op.M, (int)op.N, (int)op.K};
 }
 
 template <int T, int WM, int WN, int KS, int DEPTH>
 hipError_t launch(const MatOp& op, int splits, hipStream_t st)
 {
     const bool akm = op.a_sk != 1, bkm = op.b_sk != 1;
-    const F32Operand A{(const float*)op.A, akm ? op.a_sk : op.a_sm, (int)op.M, (int)op.K};
-    const F32Operand B{(const float*)op.B, bkm ? op.b_sk : op.b_sn, (int)op.N, (int)op.K};
+    const F32Job g = f32_job(op);
     const int kps = (int)(ceil_div(ceil_div(op.K, splits), 16) * 16);
     splits = (int)ceil_div(op.K, kps);
     float* partial = splits > 1 ? op.partial : nullptr;
     const float* bias = partial ? nullptr : op.bias;
     const dim3 grid((unsigned)ceil_div(op.M, 16 * T * WM), (unsigned)ceil_div(op.N, 16 * T * WN), (unsigned)splits), block(64 * WM * WN * KS);
 #define LRD_F32_LAUNCH(AK, BK_) \
-    hipLaunchKernelGGL((f32_gemm_kernel<T, WM, WN, KS, DEPTH, AK, BK_>), grid, block, 0, st, A, B, (float*)op.C, op.ldc, bias, partial, (int)op.M, (int)op.N, kps)
+    hipLaunchKernelGGL((f32_gemm_kernel<T, WM, WN, KS, DEPTH, AK, BK_>), grid, block, 0, st, g.A, g.B, g.C, g.ldc, bias, partial, g.M, g.N, kps)
     if (akm) { if (bkm) LRD_F32_LAUNCH(true, true); else LRD_F32_LAUNCH(true, false); }
     else { if (bkm) LRD_F32_LAUNCH(false, true); else LRD_F32_LAUNCH(false, false); }
 #undef LRD_F32_LAUNCH
@@ -207,9 +153,11 @@ bool f32_gemm_supported(const MatOp& op)
     return (op.a_sk == 1 || op.a_sm == 1) && (op.b_sk == 1 || op.b_sn == 1);
 }
 
-hipError_t f32_gemm(const MatOp& op, hipStream_t st)
+namespace {
+// The tile that f32_gemm gives a product: E = 16 T, or 64 x 64; and the slices of K over workgroups.
+struct F32Plan { int t; int64_t splits; };
+F32Plan f32_plan(const MatOp& op)
 {
-    note_kernel("f32_gemm_kernel");
     const int64_t t32 = ceil_div(op.M, 32) * ceil_div(op.N, 32), t64 = ceil_div(op.M, 64) * ceil_div(op.N, 64);
     // 64 x 64 tiles (each operand value read half as often) from about one workgroup per compute unit on: 2048 x 432
     // over 1024 36.5 us with 32 x 32 tiles, 34.2 us with these; below, 32 x 32, and while those leave half of the
@@ -218,12 +166,43 @@ hipError_t f32_gemm(const MatOp& op, hipStream_t st)
     // caller asked for slices: the error grows with the root of a chain's length (1000 x 1000 over 20000 in 8 chains
     // 9.0e-7, in 2 1.8e-6).
     const int64_t slices = op.partial && !op.bias ? op.splits : 1;
-    if (t64 >= 192) return launch<2, 2, 2, 2, 4>(op, (int)ceil_div(slices, 2), st);
+    if (t64 >= 192) return {4, ceil_div(slices, 2)};
     // Beyond that, K is cut over workgroups only where the tiles leave most of the chip idle and the reduction is long
     int64_t splits = op.K < 1024 ? 1 : std::max<int64_t>(1, std::min(slices, 256 / t32));
     splits = std::max(splits, ceil_div(slices, 8));
-    if (t32 * splits < 128) return launch<1, 1, 1, 8, 8>(op, (int)splits, st);
-    return launch<2, 1, 1, 8, 4>(op, (int)splits, st);
+    return {t32 * splits < 128 ? 1 : 2, splits};
+}
+}  // namespace
+
+hipError_t f32_gemm(const MatOp& op, hipStream_t st)
+{
+    note_kernel("f32_gemm_kernel");
+    const F32Plan p = f32_plan(op);
+    if (p.t == 4) return launch<2, 2, 2, 2, 4>(op, (int)p.splits, st);
+    if (p.t == 1) return launch<1, 1, 1, 8, 8>(op, (int)p.splits, st);
+    return launch<2, 1, 1, 8, 4>(op, (int)p.splits, st);
+}
+
+// The same tiles as by themselves, in the same order of additions: whatever f32_gemm would run unsliced in 16 x 16 or 32 x 32.
+bool f32_pair_supported(const MatOp& data, const MatOp& grad)
+{
+    if (!f32_gemm_supported(data) || !f32_gemm_supported(grad) || data.a_sk != 1 || data.b_sk == 1 || grad.a_sk == 1 || grad.b_sk == 1 || grad.sgd) return false;
+    const F32Plan d = f32_plan(data), w = f32_plan(grad);
+    return d.t < 4 && w.t < 4 && d.splits == 1 && w.splits == 1;
+}
+
+hipError_t f32_pair(const MatOp& data, const MatOp& grad, hipStream_t st)
+{
+    note_kernel("f32_pair_kernel");
+    const F32Job d = f32_job(data), w = f32_job(grad);
+    const int td = f32_plan(data).t, tw = f32_plan(grad).t;
+    const int dr = (int)ceil_div(data.M, 16 * td), db = dr * (int)ceil_div(data.N, 16 * td), wr = (int)ceil_div(grad.M, 16 * tw);
+    const dim3 grid((unsigned)(db + wr * (int)ceil_div(grad.N, 16 * tw))), block(512);
+    if (td == 1 && tw == 1) hipLaunchKernelGGL((f32_pair_kernel<1, 1>), grid, block, 0, st, d, dr, db, w, wr);
+    else if (td == 1) hipLaunchKernelGGL((f32_pair_kernel<1, 2>), grid, block, 0, st, d, dr, db, w, wr);
+    else if (tw == 1) hipLaunchKernelGGL((f32_pair_kernel<2, 1>), grid, block, 0, st, d, dr, db, w, wr);
+    else hipLaunchKernelGGL((f32_pair_kernel<2, 2>), grid, block, 0, st, d, dr, db, w, wr);
+    return hipGetLastError();
 }
 
 }  // namespace lrd

@@ -408,7 +408,8 @@ lrd_status linear_bwd_impl(const void* dY, const void* X, const void* H, const v
         fused = want_fusion(ch);
     }
     const MatOp *data1 = need_dH ? &d1 : nullptr, *data2 = dX ? &d2 : nullptr, *grad1 = train_u ? &wu : nullptr, *grad2 = train_v ? &wv : nullptr;
-    if (!fused && (data1 || grad1) && mfma_small_bwd_supported(data1, grad1) && mfma_small_bwd_supported(data2, grad2)) {
+    if (!fused && (data1 || grad1) && (data2 || grad2 || dt == LRD_BF16) && small_bwd_supported(data1, grad1) &&
+        small_bwd_supported(data2, grad2)) {
         // few tokens: two launches of what does not wait for one another (the region of the sliced products is free)
         if (train_u && !H) {
             MatOp re = nt(X, in, V, in, Hre, r, T, r, in, dt, false);
@@ -417,11 +418,11 @@ lrd_status linear_bwd_impl(const void* dY, const void* X, const void* H, const v
         }
         SmallSums sums;
         sums.dY = dY; sums.part = (float*)region; sums.out = dbias; sums.T = T; sums.n = out;
-        const bool with_sums = dbias && ceil_div(T, 32) * out * (int64_t)sizeof(float) <= (int64_t)region_bytes;
+        const bool with_sums = dbias && dt == LRD_BF16 && ceil_div(T, 32) * out * (int64_t)sizeof(float) <= (int64_t)region_bytes;
         LRD_TRY(run_small_bwd(data1, grad1, with_sums ? &sums : nullptr, st));
         sums.dY = nullptr;
         LRD_TRY(run_small_bwd(data2, grad2, with_sums ? &sums : nullptr, st));
-        if (dbias && !with_sums) LRD_TRY(column_sums(dY, dbias, T, out, true, ws, cv.used, st));
+        if (dbias && !with_sums) LRD_TRY(column_sums(dY, dbias, T, out, dt == LRD_BF16, ws, cv.used, st));
         return LRD_OK;
     }
     if (fused) {

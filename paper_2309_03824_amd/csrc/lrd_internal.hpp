@@ -97,9 +97,13 @@ struct SmallSums {                                                  // column su
     int64_t T = 0, n = 0;
 };
 hipError_t mfma_small_bwd(const MatOp* data, const MatOp* grad, const SmallSums* sums, hipStream_t st);     // any of them null
-hipError_t run_small_bwd(const MatOp* data, const MatOp* grad, const SmallSums* sums, hipStream_t st);      // with the event log
+// Whether those products can share a launch, and the launch: bf16 or fp32, with the event log.
+bool small_bwd_supported(const MatOp* data, const MatOp* grad);
+hipError_t run_small_bwd(const MatOp* data, const MatOp* grad, const SmallSums* sums, hipStream_t st);
 bool f32_gemm_supported(const MatOp& op);                          // fp32 operands, no gather
 hipError_t f32_gemm(const MatOp& op, hipStream_t st);
+bool f32_pair_supported(const MatOp& data, const MatOp& grad);     // dH and dU, or dX and dV, in one launch
+hipError_t f32_pair(const MatOp& data, const MatOp& grad, hipStream_t st);
 bool conv_direct_supported(const MatOp& op);                       // 3 x 3 stride-1 convolution with 32 / 64 channels?
 hipError_t conv_direct(const MatOp& op, hipStream_t st);
 size_t conv_direct_wgrad_bytes(const ConvShape& cs, bool bf16);    // scratch its weight gradient wants (0: not covered)
