@@ -59,6 +59,7 @@ struct Carver {
     size_t cap, used = 0;
     bool ok = true;
     Carver(void* p, size_t n) : base((char*)p), cap(n) {}
+    bool room(size_t bytes) const { return base && used + round256(bytes) <= cap; }
     void* take(size_t bytes)
     {
         size_t b = round256(bytes);
@@ -213,6 +214,8 @@ size_t linear_bytes(int64_t T, int64_t in, int64_t out, int64_t r, lrd_dtype dt,
     // forward: H when not side-stored; backward: dH and a recomputed H; both: one split-K region
     size_t fwd = act + linear_partial_region(T, in, out, r, dt, false, tokens);
     size_t bwd = 2 * act + linear_partial_region(T, in, out, r, dt, true, tokens);
+    // a size query: room for dV's slices beside dU's, so that one launch sums both (a smaller workspace serves too)
+    if (tokens == UP_TO) bwd += partial_bytes(r, in, T);
     return std::max(fwd, bwd);
 }
 }  // namespace
@@ -380,6 +383,14 @@ lrd_status linear_bwd_impl(const void* dY, const void* X, const void* H, const v
         share_splits(wv, region, dt, SPLIT_WGRAD);
     }
     if (!cv.ok) return LRD_ERR_WORKSPACE;
+    // the sums over both gradients' slices, and of the bias gradient's partial rows, in one launch at the end: where dU is sliced
+    // too, dV's slices need a region of their own for that
+    SumQueue later;
+    const size_t own = train_u && wu.splits > 1 && train_v && wv.splits > 1 ? partial_bytes(r, in, T) : 0;
+    if (own && cv.room(own)) wv.partial = (float*)cv.take(own);
+    const bool apart = !own || wv.partial != wu.partial;
+    if (apart) wu.later = &later;
+    wv.later = &later;
 
     MatOp d1, d2;
     if (need_dH) {
@@ -442,8 +453,12 @@ lrd_status linear_bwd_impl(const void* dY, const void* X, const void* H, const v
         LRD_TRY(run_matop(wu, st));
     }
     if (train_v) LRD_TRY(run_matop(wv, st));
-    // (the products are done with the workspace by then: its first cv.used bytes hold the partial sums)
-    if (dbias) LRD_TRY(column_sums(dY, dbias, T, out, dt == LRD_BF16, ws, cv.used, st));
+    // the bias gradient's partial rows (one per 32 rows at most) take the place of dH, which the products are done with; where
+    // that is too small, or nothing waits for a sum, the sums come first and the whole workspace is free
+    const bool beside = later.n > 0 && need_dH && ceil_div(T, 32) * out * (int64_t)sizeof(float) <= (int64_t)act_bytes;
+    if (dbias && beside) LRD_TRY(column_sums(dY, dbias, T, out, dt == LRD_BF16, dH, act_bytes, st, &later));
+    LRD_TRY(run_sums(later, st));
+    if (dbias && !beside) LRD_TRY(column_sums(dY, dbias, T, out, dt == LRD_BF16, ws, cv.used, st));
     return LRD_OK;
 }
 }  // namespace
@@ -921,6 +936,8 @@ size_t lrd_tucker_conv_workspace_bytes(const lrd_conv_geom* g, lrd_dtype dt, uin
     size_t part = std::max(std::max(partial_bytes(g->S, g->r2, pout), partial_bytes(g->r2, kk * g->r1, pout)),
                            partial_bytes(g->r1, g->C, pin));
     part = std::max(part, round256(conv_direct_wgrad_bytes_up_to(cs, dt == LRD_BF16)));
+    // room for the 1x1 layers' slices beside the core's, so that one launch sums all (a smaller workspace serves too)
+    part += partial_bytes(g->S, g->r2, pout) + partial_bytes(g->r1, g->C, pin);
     // forward: A and B when not side-stored; backward: dA, dB, recomputed A and B, partials, and the
     // flipped core weights of a stride-1 data gradient
     return 2 * (a + b) + part + round256(conv_dgrad_flip_bytes(cs, dt == LRD_BF16));
@@ -1077,6 +1094,17 @@ lrd_status tucker_bwd_impl(const void* dY, const void* X, const void* A, const v
         wg.scratch_bytes = shared_bytes;
     }
     if (t1) splits_for(w1);
+    // the sums over their slices in one launch at the end, each with a region of its own (all or none: a workspace without that
+    // room has them one after the other in the shared one)
+    SumQueue later;
+    {
+        const size_t own2 = t2 && w2.splits > 1 ? partial_bytes(S, r2, pout) : 0, own1 = t1 && w1.splits > 1 ? partial_bytes(r1, C, pin) : 0;
+        if (cv.room(own2 + own1)) {
+            if (own2) w2.partial = (float*)cv.take(own2);
+            if (own1) w1.partial = (float*)cv.take(own1);
+            w2.later = wg.later = w1.later = &later;
+        }
+    }
 
     if (need_dB) LRD_TRY(run_matop(nn(dY, S, P2, r2, dB, r2, pout, r2, S, dt), st));
     if (need_dA) {
@@ -1098,6 +1126,7 @@ lrd_status tucker_bwd_impl(const void* dY, const void* X, const void* A, const v
     if (t2) LRD_TRY(run_matop(w2, st));
     if (tg) LRD_TRY(run_matop(wg, st));
     if (t1) LRD_TRY(run_matop(w1, st));
+    LRD_TRY(run_sums(later, st));
     return LRD_OK;
 }
 }  // namespace

@@ -36,6 +36,22 @@ struct CropFuse {
     mutable bool done = false;
 };
 
+// Sums over split-K slices (and of a bias gradient's partial rows) that a pass puts off to one launch at its end: each is a few
+// microseconds, half of them the launch.  Their partial sums stay in the workspace until then, so each needs a region of its own.
+struct SumTask {
+    const float* partial;
+    float* C;
+    int64_t ldc, M, N;
+    int splits;
+    SgdFuse sgd;               // sgd.w given: the step instead of the sum
+    CropFuse crop;             // crop.dst given: cropped
+};
+struct SumQueue {
+    static constexpr int MOST = 4;
+    SumTask task[MOST];
+    int n = 0;
+};
+
 // One product  C[M x N] = A[M x K] . B[N x K]^T (+ bias[n]),  fp32 accumulation.
 // A(m,k) = A[m*a_sm + k*a_sk], B(n,k) = B[n*b_sn + k*b_sk] (element strides) unless a gather mode
 // replaces the addressing of one operand by a convolution's tap geometry.
@@ -70,6 +86,7 @@ struct MatOp {
     // Optional optimizer step on the finished fp32 result (a dense weight gradient, ldc == N).
     const SgdFuse* sgd = nullptr;
     const CropFuse* crop = nullptr;
+    SumQueue* later = nullptr;     // where an engine may leave the sum over its K-slices (else it runs at once)
     // A batch of products of one shape (the layers of a group): product z reads A + z * a_bs,
     // B + z * b_bs, bias + z * bias_bs and writes C + z * c_bs, aux + z * aux_bs (element strides).
     int batch = 1;
@@ -149,7 +166,8 @@ void note_kernel(const char* name);
 hipError_t gelu_fwd(const void* Z, void* A, int64_t n, bool bf16, hipStream_t st);
 hipError_t gelu_bwd(const void* dA, const void* Z, void* dZ, int64_t n, bool bf16, hipStream_t st);
 // out[c] = sum over t of dY[t][c]; `scratch` (optional) holds partial rows, fewer of them if it is small.
-hipError_t column_sums(const void* dY, float* out, int64_t T, int64_t n, bool bf16, void* scratch, size_t scratch_bytes, hipStream_t st);
+hipError_t column_sums(const void* dY, float* out, int64_t T, int64_t n, bool bf16, void* scratch, size_t scratch_bytes, hipStream_t st,
+                       SumQueue* later = nullptr);
 // Zero-padding / cropping copies of dense row-major matrices (16-byte-aligned bases, elem_bytes 2 or 4), one launch.
 constexpr int COPY_JOBS = 5;
 struct CopyJob {
@@ -170,5 +188,9 @@ size_t conv_dgrad_flip_bytes(const ConvShape& cs, bool bf16);
 // layout allows (then sgd->done is set); with `crop` it is stored cropped (then crop->done is set).
 hipError_t reduce_partials(const float* partial, void* C, bool c_bf16, int64_t ldc, int64_t M, int64_t N,
                            int splits, hipStream_t st, const SgdFuse* sgd = nullptr, const CropFuse* crop = nullptr);
+// The same put off to run_sums, with the same order of additions (`done` is set here); false where the queue cannot take it.
+bool put_off(SumQueue* q, const float* partial, void* C, bool c_bf16, int64_t ldc, int64_t M, int64_t N, int splits, const SgdFuse* sgd = nullptr,
+             const CropFuse* crop = nullptr);
+hipError_t run_sums(SumQueue& q, hipStream_t st);
 
 }  // namespace lrd

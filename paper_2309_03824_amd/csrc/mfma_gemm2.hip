@@ -757,9 +757,12 @@ hipError_t launch_epi(const MatOp& op, const Operand& A, const Operand& B, hipSt
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     // a batch of sliced products is summed as one matrix of batch * M rows (supported() admits only dense results)
-    if (splits > 1)
-        return reduce_partials(op.partial, op.C, !op.out_f32, op.ldc, op.M * bt.batch, op.N, splits, st, op.out_f32 ? op.sgd : nullptr,
-                               op.out_f32 ? op.crop : nullptr);
+    if (splits > 1) {
+        const SgdFuse* sgd = op.out_f32 ? op.sgd : nullptr;
+        const CropFuse* crop = op.out_f32 ? op.crop : nullptr;
+        if (put_off(op.later, op.partial, op.C, !op.out_f32, op.ldc, op.M * bt.batch, op.N, splits, sgd, crop)) return hipSuccess;
+        return reduce_partials(op.partial, op.C, !op.out_f32, op.ldc, op.M * bt.batch, op.N, splits, st, sgd, crop);
+    }
     return hipSuccess;
 }
 
