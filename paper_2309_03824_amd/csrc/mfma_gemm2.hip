@@ -398,8 +398,20 @@ constexpr int gemm2_lds_bytes()
     return main > epi ? main : epi;
 }
 
+// 16 bytes to memory past the caches of this die, kept by the one beside memory.  (The compiler does not see the store's read of
+// its data, which a vector instruction may overwrite one state later.)
+__device__ __forceinline__ void store_through(void* to, u32x4 v)
+{
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(to), "v"(v) : "memory");
+}
+// Results up to this many elements are stored that way: they are what the next product reads at once, and it finds them there.
+// Non-temporal stores send them to memory; the encoder step's [8192 x 256] intermediates come back 0.3 us of 8.9 sooner, its step
+// 4091 -> 4065 us, the FFN stack 1842 -> 1827 us.  With larger ones the write-backs come due in the next kernel instead: with
+// [8192 x 1024] results stored so the step takes 4150 us.
+constexpr int64_t THROUGH_MOST = int64_t(1) << 22;
+
 // bf16 results of one BM x BN tile: registers -> LDS tile (row-major) -> 16 contiguous bytes per
-// lane to global memory, with the optional GELU epilogue.  Results (and the pre-activation the
+// lane to global memory, with the optional GELU epilogue.  Large results (and the pre-activation the
 // gradient epilogue reads) are streamed with non-temporal accesses: 10 % faster on the wide products.  Every wave must be past its last read
 // of the operand tiles in LDS (the staging tile overlays them); ends without a barrier.
 template <int BM, int BN, int WGM, int WGN, bool MAPROWS, int EPI, int TM, int TN>
@@ -447,6 +459,7 @@ __device__ __forceinline__ void store_bf16_tile(const f32x16 (&acc)[TM][TN], bf1
     if (bias) stage(std::true_type{});
     else stage(std::false_type{});
     __syncthreads();
+    const bool through = (int64_t)M * N <= THROUGH_MOST;
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
         int c = tid + q * NT;
@@ -468,7 +481,12 @@ __device__ __forceinline__ void store_bf16_tile(const f32x16 (&acc)[TM][TN], bf1
             for (int e = 0; e < 8; ++e) c8[e] = (bf16_t)((float)c8[e] * gelu_grad_bf16_f((float)z8[q][e]));
             v = __builtin_bit_cast(u32x4, c8);
         }
-        if (ok) __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(out + mrow * ldc + n));
+        if constexpr (EPI == EPI_NONE && !MAPROWS) {
+            if (ok && through) store_through(out + mrow * ldc + n, v);
+            else if (ok) __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(out + mrow * ldc + n));
+        } else {
+            if (ok) __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(out + mrow * ldc + n));
+        }
         if constexpr (EPI == EPI_ACT_STORE) {
             bf16x8 c8 = __builtin_bit_cast(bf16x8, v);
 #pragma unroll
