@@ -1051,8 +1051,8 @@ MIB = float(1 << 20)
 PROFILED_TRAFFIC = {
     "gemm2_kernel<64,128,2,4,4,A_KC,B_KC,bf16>": {"8192x256x1024": (20.1 + 4.0) * MIB, "8192x256x4096": (80.1 + 4.0) * MIB},
     "gemm2_kernel<64,128,2,4,4,A_KC,B_KM,bf16>": {"8192x256x1024": (20.1 + 4.0) * MIB, "8192x256x4096": (80.1 + 4.0) * MIB},
-    "gemm2_kernel<128,128,2,4,2,A_KC,B_KC,bf16,gelu>": {"8192x4096x256+act": (20.1 + 128.4) * MIB},
-    "gemm2_kernel<128,128,2,4,1,A_KC,B_KM,bf16,gelu_grad>": {"8192x4096x256+act": (84.1 + 64.0) * MIB},
+    "wide_kernel<256,4,B_KC,gelu>": {"8192x4096x256+act": (20.1 + 128.0) * MIB},
+    "wide_kernel<256,4,B_KM,gelu_grad>": {"8192x4096x256+act": (84.1 + 64.0) * MIB},
     "gemm2_kernel<128,128,2,4,2,A_KC,B_KC,bf16>": {"3 x 8192x1024x256": (17.1 + 48.0) * MIB, "8192x1024x256": (8.1 + 16.0) * MIB},
     "gemm2_kernel<128,128,2,4,2,A_KC,B_KM,bf16>": {"8192x1024x256": (8.1 + 16.0) * MIB},
 }
@@ -1087,7 +1087,7 @@ def kernel_roofline(rows):
     if seen and all(k in seen for k in shapes):
         traffic = sum(seen[k] * c for k, c in shapes.items()) / n
     roof.update(traffic=traffic, traffic_note="HBM bytes per launch from rocprofv3 FETCH_SIZE / WRITE_SIZE runs of this command, copy-calibrated "
-                "(profiles/encoder_step_hbm_traffic.md, taken at commit b0766fe); null when this kernel or its shapes were not the profiled ones", kernel=name, avg_us=total_us / n, launches=n, bytes_per_launch=nbytes / n, flops_per_launch=flops / n,
+                "(profiles/encoder_step_hbm_traffic.md, taken at commit 3a5dbb5); null when this kernel or its shapes were not the profiled ones", kernel=name, avg_us=total_us / n, launches=n, bytes_per_launch=nbytes / n, flops_per_launch=flops / n,
                 share_of_logged_time=total_us / sum(r["us"] for r in rows), shapes=shapes,
                 note="algorithmic bytes per launch = both operands read once + result written once (+ the activation tensor the "
                      "epilogue writes or reads); duration from HIP events on the launch stream around every launch of this kernel "

@@ -826,6 +826,7 @@ hipError_t by_tile(const MatOp& op, const Operand& A, const Operand& B, hipStrea
     if (!WGRAD && op.K <= 8 * BK) {
         if (op.M > 64 && op.N > 64 && (wgs(128, 128) >= 200 || wgs(64, 64) > 2048)) {
             if constexpr (sizeof(OutT) == 2 && G == GATHER_NONE) {
+                // (Large results in whole chunks of 64 columns are not here: see mfma_wide_supported.)
                 // From three rounds on, 256 x 256 tiles where the multiplication weighs more (16384 x 4096 x 512: 80 us,
                 // 83 us in the next kind, 90 us in the last); else one stage and three workgroups per unit, against two
                 // stages and two of them: 4100 x 4096 x 264 22.6 -> 20.5 us, 8192 x 4096 x 256 with the GELU gradient
