@@ -263,34 +263,28 @@ hipError_t run_matop(const MatOp& op_in, hipStream_t st)
     return apply_epilogue(op, st);
 }
 
-bool small_bwd_supported(const MatOp* data, const MatOp* grad)
+bool small_pair_supported(const MatOp& data, const MatOp& grad)
 {
-    const MatOp* any = data ? data : grad;
-    if (!any) return true;
-    if (any->in_bf16) return mfma_small_bwd_supported(data, grad);
-    // (fp32: one of them alone is run_matop's)
-    return data && grad ? f32_pair_supported(*data, *grad) : !any->sgd && f32_gemm_supported(*any);
+    return data.in_bf16 ? mfma_small_pair_supported(data, grad) : f32_pair_supported(data, grad);
 }
 
-hipError_t run_small_bwd(const MatOp* data, const MatOp* grad, const SmallSums* sums, hipStream_t st)
+hipError_t run_small_bwd(const MatOp& data, const MatOp* grad, const SmallSums* sums, hipStream_t st)
 {
-    const MatOp* any = data ? data : grad;
-    const bool f32 = any && !any->in_bf16;
-    if (f32 && !(data && grad)) return run_matop(data ? *data : *grad, st);
+    const bool f32 = !data.in_bf16;
     // each product has a record of its own, around the launch that they share
-    const MatOp* ops[2] = {data, grad};
+    const MatOp* ops[2] = {&data, grad};
     hipEvent_t ev0[2], ev1[2];
     int logged[2] = {-1, -1};
     for (int i = 0; i < 2; ++i)
         if (ops[i] && (logged[i] = log_begin(&ev0[i], &ev1[i])) >= 0) (void)hipEventRecord(ev0[i], st);
-    const hipError_t e = f32 ? f32_pair(*data, *grad, st) : mfma_small_bwd(data, grad, sums, st);
+    const hipError_t e = f32 ? f32_pair(data, *grad, st) : mfma_small_bwd(&data, grad, sums, st);
     for (int i = 0; i < 2; ++i)
         if (logged[i] >= 0) {
             (void)hipEventRecord(ev1[i], st);
             log_end(logged[i], ops[i]->role, ops[i]->gather, ops[i]->epilogue, 1, ops[i]->M, ops[i]->N, ops[i]->K, 1);
         }
-    if (e != hipSuccess || !f32 || data->epilogue == EPI_NONE) return e;
-    return apply_epilogue(*data, st);      // (fp32 engines do not fuse it)
+    if (e != hipSuccess || !f32 || data.epilogue == EPI_NONE) return e;
+    return apply_epilogue(data, st);      // (fp32 engines do not fuse it)
 }
 
 }  // namespace lrd

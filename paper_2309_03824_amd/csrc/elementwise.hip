@@ -409,18 +409,30 @@ hipError_t gelu_bwd(const void* dA, const void* Z, void* dZ, int64_t n, bool bf1
     return hipGetLastError();
 }
 
+namespace {
+inline int64_t column_sum_width(const void* dY, int64_t n, bool bf16)
+{
+    return n % (bf16 ? 8 : 4) == 0 && (reinterpret_cast<uintptr_t>(dY) & 15u) == 0 ? (bf16 ? 8 : 4) : 1;
+}
+}  // namespace
+
+int64_t column_sum_rows(const void* dY, int64_t T, int64_t n, bool bf16, size_t scratch_bytes, int64_t* partials)
+{
+    // about 512 blocks of at least 32 rows each, as far as the partial rows fit the scratch (without any, one
+    // run of rows goes straight to the result)
+    int64_t rb = std::min(ceil_div(512, ceil_div(n, CS_COLS * column_sum_width(dY, n, bf16))), ceil_div(T, 32));
+    rb = std::max<int64_t>(1, std::min<int64_t>(rb, (int64_t)(scratch_bytes / ((size_t)n * sizeof(float)))));
+    const int64_t rows = ceil_div(T, rb);
+    *partials = ceil_div(T, rows);
+    return rows;
+}
+
 hipError_t column_sums(const void* dY, float* out, int64_t T, int64_t n, bool bf16, void* scratch, size_t scratch_bytes, hipStream_t st, SumQueue* later)
 {
     if (n <= 0) return hipSuccess;
-    const int64_t vec = n % (bf16 ? 8 : 4) == 0 && (reinterpret_cast<uintptr_t>(dY) & 15u) == 0 ? (bf16 ? 8 : 4) : 1;
-    const int64_t cb = ceil_div(n, CS_COLS * vec);
-    // about 512 blocks of at least 32 rows each, as far as the partial rows fit the scratch (without any, one
-    // run of rows goes straight to the result)
-    int64_t rb = std::min(ceil_div(512, cb), ceil_div(T, 32));
-    rb = std::min<int64_t>(rb, scratch ? (int64_t)(scratch_bytes / ((size_t)n * sizeof(float))) : 1);
-    if (rb < 1) rb = 1;
-    const int64_t rows = ceil_div(T, rb);
-    rb = ceil_div(T, rows);
+    const int64_t vec = column_sum_width(dY, n, bf16), cb = ceil_div(n, CS_COLS * vec);
+    int64_t rb;
+    const int64_t rows = column_sum_rows(dY, T, n, bf16, scratch ? scratch_bytes : 0, &rb);
     if (rows >= (int64_t(1) << 31) || cb >= (int64_t(1) << 31)) return hipErrorInvalidValue;
     float* partial = rb > 1 ? (float*)scratch : out;
     const dim3 grid((unsigned)cb, (unsigned)rb);

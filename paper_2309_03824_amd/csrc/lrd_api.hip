@@ -386,6 +386,7 @@ lrd_status linear_bwd_impl(const void* dY, const void* X, const void* H, const v
     // the sums over both gradients' slices, and of the bias gradient's partial rows, in one launch at the end: where dU is sliced
     // too, dV's slices need a region of their own for that
     SumQueue later;
+    const size_t base_used = cv.used;      // the same in every workspace that the call accepts
     const size_t own = train_u && wu.splits > 1 && train_v && wv.splits > 1 ? partial_bytes(r, in, T) : 0;
     if (own && cv.room(own)) wv.partial = (float*)cv.take(own);
     const bool apart = !own || wv.partial != wu.partial;
@@ -418,47 +419,53 @@ lrd_status linear_bwd_impl(const void* dY, const void* X, const void* H, const v
         ch.role = LRD_ROLE_DGRAD_UP;
         fused = want_fusion(ch);
     }
-    const MatOp *data1 = need_dH ? &d1 : nullptr, *data2 = dX ? &d2 : nullptr, *grad1 = train_u ? &wu : nullptr, *grad2 = train_v ? &wv : nullptr;
-    if (!fused && (data1 || grad1) && (data2 || grad2 || dt == LRD_BF16) && small_bwd_supported(data1, grad1) &&
-        small_bwd_supported(data2, grad2)) {
-        // few tokens: two launches of what does not wait for one another (the region of the sliced products is free)
-        if (train_u && !H) {
-            MatOp re = nt(X, in, V, in, Hre, r, T, r, in, dt, false);
-            share_splits(re, region, dt, SPLIT_ACT);
-            LRD_TRY(run_matop(re, st));
-        }
-        SmallSums sums;
-        sums.dY = dY; sums.part = (float*)region; sums.out = dbias; sums.T = T; sums.n = out;
-        const bool with_sums = dbias && dt == LRD_BF16 && ceil_div(T, 32) * out * (int64_t)sizeof(float) <= (int64_t)region_bytes;
-        LRD_TRY(run_small_bwd(data1, grad1, with_sums ? &sums : nullptr, st));
-        sums.dY = nullptr;
-        LRD_TRY(run_small_bwd(data2, grad2, with_sums ? &sums : nullptr, st));
-        if (dbias && !with_sums) LRD_TRY(column_sums(dY, dbias, T, out, dt == LRD_BF16, ws, cv.used, st));
-        return LRD_OK;
+    // Few tokens: products that do not wait for one another share a launch (each with the bits that it has by itself), and the bias
+    // gradient's two steps go with them: its partial rows wait in the region of the K-slices where no product needs that meanwhile.
+    // (Only up to 512 blocks of column_sums, for the products leave few units to them: a pass with bias of 509 x 1024 -> 32000 at rank 256 55.7
+    // us with the sums by themselves, 65.2 with 2000 blocks beside dX and dV.)
+    const bool pair1 = !fused && need_dH && train_u && small_pair_supported(d1, wu), pair2 = !fused && dX && train_v && small_pair_supported(d2, wv);
+    const bool small1 = pair1 || (!fused && need_dH && mfma_small_data_supported(d1)), small2 = pair2 || (!fused && dX && mfma_small_data_supported(d2));
+    SmallSums rows, sum;
+    rows.T = T; rows.n = out; rows.dY = dY; rows.part = (float*)region;
+    bool ride = dbias && dt == LRD_BF16 && (small1 || small2) && out % 8 == 0 && out < 65536 && (!train_u || pair1 || (H && wu.splits == 1)) &&
+                (!train_v || pair2 || wv.splits == 1);
+    if (ride) {
+        rows.rows = column_sum_rows(dY, T, out, true, base_used, &rows.slices);
+        ride = rows.slices * ceil_div(out, 256) <= 512 && (rows.slices == 1 || rows.slices * out * (int64_t)sizeof(float) <= (int64_t)region_bytes);
+        if (rows.slices == 1) rows.part = dbias;
+        sum = rows;
+        sum.dY = nullptr; sum.out = dbias;
     }
+    const bool summed = ride && (rows.slices == 1 || (small1 && small2));
+    auto recompute = [&]() -> hipError_t {
+        MatOp re = nt(X, in, V, in, Hre, r, T, r, in, dt, false);
+        share_splits(re, region, dt, SPLIT_ACT);
+        return run_matop(re, st);
+    };
     if (fused) {
         LRD_TRY(run_chain(ch, st));
         if (Z_in) LRD_TRY(gelu_bwd(dX, Z_in, dX, T * in, true, st));
     } else if (need_dH) {
+        if (pair1 && !H) LRD_TRY(recompute());
         share_splits(d1, region, dt, SPLIT_ACT);
-        LRD_TRY(run_matop(d1, st));
-        if (dX) LRD_TRY(run_matop(d2, st));
+        if (small1) LRD_TRY(run_small_bwd(d1, pair1 ? &wu : nullptr, ride ? &rows : nullptr, st));
+        else LRD_TRY(run_matop(d1, st));
+        if (small2) LRD_TRY(run_small_bwd(d2, pair2 ? &wv : nullptr, !ride ? nullptr : !small1 ? &rows : rows.slices > 1 ? &sum : nullptr, st));
+        else if (dX) LRD_TRY(run_matop(d2, st));
     }
-    if (train_u) {
-        if (!H) {
-            MatOp re = nt(X, in, V, in, Hre, r, T, r, in, dt, false);
-            share_splits(re, region, dt, SPLIT_ACT);
-            LRD_TRY(run_matop(re, st));
-        }
+    if (train_u && !pair1) {
+        if (!H) LRD_TRY(recompute());
         LRD_TRY(run_matop(wu, st));
     }
-    if (train_v) LRD_TRY(run_matop(wv, st));
-    // the bias gradient's partial rows (one per 32 rows at most) take the place of dH, which the products are done with; where
+    if (train_v && !pair2) LRD_TRY(run_matop(wv, st));
+    // else the bias gradient's partial rows (one per 32 rows at most) take the place of dH, which the products are done with; where
     // that is too small, or nothing waits for a sum, the sums come first and the whole workspace is free
     const bool beside = later.n > 0 && need_dH && ceil_div(T, 32) * out * (int64_t)sizeof(float) <= (int64_t)act_bytes;
-    if (dbias && beside) LRD_TRY(column_sums(dY, dbias, T, out, dt == LRD_BF16, dH, act_bytes, st, &later));
+    if (dbias && !ride && beside) LRD_TRY(column_sums(dY, dbias, T, out, dt == LRD_BF16, dH, act_bytes, st, &later));
+    if (ride && !summed && !put_off(&later, rows.part, dbias, false, out, 1, out, (int)rows.slices))
+        LRD_TRY(reduce_partials(rows.part, dbias, false, out, 1, out, (int)rows.slices, st));
     LRD_TRY(run_sums(later, st));
-    if (dbias && !beside) LRD_TRY(column_sums(dY, dbias, T, out, dt == LRD_BF16, ws, cv.used, st));
+    if (dbias && !ride && !beside) LRD_TRY(column_sums(dY, dbias, T, out, dt == LRD_BF16, ws, base_used, st));
     return LRD_OK;
 }
 }  // namespace

@@ -106,17 +106,18 @@ hipError_t mfma_wide(const MatOp& op, hipStream_t st);
 bool mfma_small_fwd_supported(const MatOp& op);
 hipError_t mfma_small_fwd(const MatOp& op, hipStream_t st);
 bool mfma_small_data_supported(const MatOp& op);                    // dH = dY.U, dX = dH.V
-bool mfma_small_bwd_supported(const MatOp* data, const MatOp* grad);     // one of those, and dU = dY^T.H or dV = dH^T.X, in a launch
-struct SmallSums {                                                  // column sums of dY [T x n]
-    const void* dY = nullptr;                                       // given: to one partial row per 32 rows; null: their sum to `out`
+// One of those, and dU = dY^T.H or dV = dH^T.X, in a launch: the results are the bits that each gives by itself.
+bool mfma_small_pair_supported(const MatOp& data, const MatOp& grad);
+struct SmallSums {                                                  // column sums of dY [T x n], as column_sums makes them
+    const void* dY = nullptr;                                       // given: to `slices` partial rows; null: their sum to `out`
     float* part = nullptr;
     float* out = nullptr;
-    int64_t T = 0, n = 0;
+    int64_t T = 0, n = 0, rows = 0, slices = 0;
 };
 hipError_t mfma_small_bwd(const MatOp* data, const MatOp* grad, const SmallSums* sums, hipStream_t st);     // any of them null
-// Whether those products can share a launch, and the launch: bf16 or fp32, with the event log.
-bool small_bwd_supported(const MatOp* data, const MatOp* grad);
-hipError_t run_small_bwd(const MatOp* data, const MatOp* grad, const SmallSums* sums, hipStream_t st);
+// Whether two products can share a launch, bf16 or fp32; and a launch of that kind, of one or both, with the event log.
+bool small_pair_supported(const MatOp& data, const MatOp& grad);
+hipError_t run_small_bwd(const MatOp& data, const MatOp* grad, const SmallSums* sums, hipStream_t st);
 bool f32_gemm_supported(const MatOp& op);                          // fp32 operands, no gather
 hipError_t f32_gemm(const MatOp& op, hipStream_t st);
 bool f32_pair_supported(const MatOp& data, const MatOp& grad);     // dH and dU, or dX and dV, in one launch
@@ -166,6 +167,8 @@ void note_kernel(const char* name);
 hipError_t gelu_fwd(const void* Z, void* A, int64_t n, bool bf16, hipStream_t st);
 hipError_t gelu_bwd(const void* dA, const void* Z, void* dZ, int64_t n, bool bf16, hipStream_t st);
 // out[c] = sum over t of dY[t][c]; `scratch` (optional) holds partial rows, fewer of them if it is small.
+// column_sum_rows: rows of dY to a partial row; *partials of them.
+int64_t column_sum_rows(const void* dY, int64_t T, int64_t n, bool bf16, size_t scratch_bytes, int64_t* partials);
 hipError_t column_sums(const void* dY, float* out, int64_t T, int64_t n, bool bf16, void* scratch, size_t scratch_bytes, hipStream_t st,
                        SumQueue* later = nullptr);
 // Zero-padding / cropping copies of dense row-major matrices (16-byte-aligned bases, elem_bytes 2 or 4), one launch.

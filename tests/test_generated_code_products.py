@@ -8,7 +8,7 @@ import test_generated_code as rules
 from paper_2309_03824_amd import build
 
 
-@pytest.fixture(scope="module", params=[("mfma_wide", 32), ("mfma_small", 4)], ids=lambda p: p[0])
+@pytest.fixture(scope="module", params=[("mfma_wide", 32), ("mfma_small", 5)], ids=lambda p: p[0])
 def kernels(request, tmp_path_factory):
     name, count = request.param
     obj = os.path.join(build.OBJ, name + ".hip.o")
