@@ -1059,12 +1059,17 @@ PROFILED_TRAFFIC = {
 
 
 def kernel_roofline(rows):
-    """Roofline object of the product kernel with the largest total time among the logged launches."""
+    """Roofline object of the product kernel with the largest total time among the logged launches (two products of one launch
+    have a record each and its time once; launches that only sum have no roofline)."""
     groups = {}
     for r in rows:
         groups.setdefault(r["kernel"], []).append(r)
-    name, grp = max(groups.items(), key=lambda kv: sum(r["us"] for r in kv[1]))
-    total_us = sum(r["us"] for r in grp)
+
+    def us_of(records):
+        return sum(r["us"] for r in records if not r["shared"])
+
+    name, grp = max(((k, v) for k, v in groups.items() if v[0]["role"] != 7), key=lambda kv: us_of(kv[1]))
+    total_us = us_of(grp)
     flops = nbytes = 0.0
     shapes = {}
     for r in grp:
@@ -1075,7 +1080,7 @@ def kernel_roofline(rows):
         key = (f"{nb} x " if nb > 1 else "") + f"{M}x{N}x{K}" + ("+act" if r["epilogue"] else "")
         shapes[key] = shapes.get(key, 0) + 1
     t_mfma, t_hbm = flops / (MFMA_BF16_PEAK_TFLOPS * 1e12), nbytes / (HBM_PEAK_GBS * 1e9)
-    n = len(grp)
+    n = sum(not r["shared"] for r in grp)
     if t_hbm >= t_mfma:
         ach = nbytes / (total_us * 1e-6) / 1e9
         roof = dict(bound="hbm", achieved=ach, peak=HBM_PEAK_GBS, unit="GB/s", frac=ach / HBM_PEAK_GBS)
@@ -1088,11 +1093,11 @@ def kernel_roofline(rows):
         traffic = sum(seen[k] * c for k, c in shapes.items()) / n
     roof.update(traffic=traffic, traffic_note="HBM bytes per launch from rocprofv3 FETCH_SIZE / WRITE_SIZE runs of this command, copy-calibrated "
                 "(profiles/encoder_step_hbm_traffic.md, taken at commit 3a5dbb5); null when this kernel or its shapes were not the profiled ones", kernel=name, avg_us=total_us / n, launches=n, bytes_per_launch=nbytes / n, flops_per_launch=flops / n,
-                share_of_logged_time=total_us / sum(r["us"] for r in rows), shapes=shapes,
+                share_of_logged_time=total_us / us_of(rows), shapes=shapes,
                 note="algorithmic bytes per launch = both operands read once + result written once (+ the activation tensor the "
                      "epilogue writes or reads); duration from HIP events on the launch stream around every launch of this kernel "
                      "in an eager pass over the timed steps")
-    by_kernel = {k: dict(launches=len(v), total_us=sum(r["us"] for r in v)) for k, v in groups.items()}
+    by_kernel = {k: dict(launches=sum(not r["shared"] for r in v), total_us=us_of(v)) for k, v in groups.items()}
     return roof, by_kernel
 
 

@@ -40,8 +40,10 @@ int32_t lrd_set_fusion(int32_t mode);
  * core, ...) is bracketed by hipEventRecord on its launch stream with the next pair of caller-owned
  * events, events[2i] before and events[2i + 1] after product i (hipEvent_t passed as void*), and
  * described by record i; products beyond n_pairs are not logged.  A product whose reduction is
- * split (splits > 1) is bracketed together with the kernel that sums its slices.  The caller
- * synchronises and reads the elapsed times itself.  Logging costs two event records per product,
+ * split (splits > 1) is bracketed together with the kernel that sums its slices, unless the pass
+ * puts its sums off to one launch at its end: that launch has a record of its own (LRD_ROLE_SUMS).
+ * Two products that one launch runs have a record each around that launch, the second with
+ * shared = 1: add its time once.  The caller synchronises and reads the elapsed times itself.  Logging costs two event records per product,
  * so it belongs in a separate, eager pass, not in a captured graph.
  */
 enum {
@@ -51,16 +53,19 @@ enum {
     LRD_ROLE_DGRAD_UP = 3,    /* dH = dY.U    */
     LRD_ROLE_DGRAD_DOWN = 4,  /* dX = dH.V    */
     LRD_ROLE_WGRAD_U = 5,     /* dU = dY^T.H  */
-    LRD_ROLE_WGRAD_V = 6      /* dV = dH^T.X  */
+    LRD_ROLE_WGRAD_V = 6,     /* dV = dH^T.X  */
+    LRD_ROLE_SUMS = 7         /* no product: the sums over K-slices (and of a bias gradient's partial rows) put off by a pass;
+                                 M results in all, batch sums */
 };
 typedef struct {
     int32_t role;             /* LRD_ROLE_* */
     int32_t gather;           /* 0 plain product, 1 / 2 / 3 convolution forward / data gradient / weight gradient */
     int32_t epilogue;         /* 0 none, 1 activation stored beside the result, 2 result times activation gradient */
-    int32_t splits;           /* slices of the reduction (1: one kernel) */
+    int32_t splits;           /* slices of the reduction, each a chain of additions of its own */
     int64_t M, N, K;          /* result M x N, reduction length K */
     int64_t batch;            /* products of this shape the launch ran (1 unless batched) */
-    char kernel[64];          /* the kernel that ran the product (template, tile, stages, epilogue), NUL-terminated */
+    char kernel[60];          /* the kernel that ran the product (template, tile, stages, epilogue), NUL-terminated */
+    int32_t shared;           /* 1: ran in the launch of the record before it, and both brackets hold that launch */
 } lrd_profile_record;
 lrd_status lrd_profile_log_start(void** events, int32_t n_pairs);
 /* Stops logging and copies up to `capacity` records to `out` (host, nullable); returns the number of

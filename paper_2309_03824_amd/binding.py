@@ -20,7 +20,7 @@ F32, BF16 = 0, 1
 KIND_SVD, KIND_TUCKER = 0, 1
 FREEZE_L0, FREEZE_L1, FREEZE_L2 = 1, 2, 4
 FUSION_AUTO, FUSION_ALWAYS, FUSION_NEVER = 0, 1, 2
-ROLE_NONE, ROLE_FWD_DOWN, ROLE_FWD_UP, ROLE_DGRAD_UP, ROLE_DGRAD_DOWN, ROLE_WGRAD_U, ROLE_WGRAD_V = range(7)
+ROLE_NONE, ROLE_FWD_DOWN, ROLE_FWD_UP, ROLE_DGRAD_UP, ROLE_DGRAD_DOWN, ROLE_WGRAD_U, ROLE_WGRAD_V, ROLE_SUMS = range(8)
 ROUND_NEAREST, ROUND_DOWN, ROUND_UP = 0, 1, 2
 ACT_NONE, ACT_GELU = 0, 1
 
@@ -54,7 +54,7 @@ class Sgd(Structure):
 
 class ProfileRecord(Structure):
     _fields_ = [("role", c_int32), ("gather", c_int32), ("epilogue", c_int32), ("splits", c_int32),
-                ("M", c_int64), ("N", c_int64), ("K", c_int64), ("batch", c_int64), ("kernel", ctypes.c_char * 64)]
+                ("M", c_int64), ("N", c_int64), ("K", c_int64), ("batch", c_int64), ("kernel", ctypes.c_char * 60), ("shared", c_int32)]
 
 
 class ConvGeom(Structure):
@@ -360,7 +360,8 @@ def measure_stream(src, dst, nbytes: int, mode: int, stream=None):
 
 class ProfileLog:
     """Event log of the library's products (lrd_profile_log_start / _stop): `with ProfileLog(n) as log:`
-    runs eager launches; afterwards log.rows() gives one dict per product with its elapsed microseconds."""
+    runs eager launches; afterwards log.rows() gives one dict per product (and per launch of sums) with its elapsed
+    microseconds, those of a product that shares the launch of the one before it (shared) once more."""
 
     def __init__(self, n_pairs: int):
         self.n = int(n_pairs)
@@ -385,7 +386,7 @@ class ProfileLog:
         for i in range(min(self.count, self.n)):
             r = self.records[i]
             out.append(dict(role=r.role, gather=r.gather, epilogue=r.epilogue, splits=r.splits, M=r.M, N=r.N, K=r.K, batch=r.batch,
-                            kernel=r.kernel.decode(), us=self.events[2 * i].elapsed_us(self.events[2 * i + 1])))
+                            kernel=r.kernel.decode(), shared=bool(r.shared), us=self.events[2 * i].elapsed_us(self.events[2 * i + 1])))
         return out
 
 

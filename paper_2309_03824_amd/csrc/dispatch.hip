@@ -152,13 +152,13 @@ int log_begin(hipEvent_t* start, hipEvent_t* stop)
     return i;
 }
 
-void log_end(int index, int role, int gather, int epilogue, int splits, int64_t M, int64_t N, int64_t K, int64_t batch)
+void log_end(int index, int role, int gather, int epilogue, int splits, int64_t M, int64_t N, int64_t K, int64_t batch, bool shared)
 {
     std::lock_guard<std::mutex> lock(g_log_mutex);
     if (index < 0 || index >= (int)g_log.size()) return;
     lrd_profile_record& r = g_log[index];
     r.role = role; r.gather = gather; r.epilogue = epilogue; r.splits = splits;
-    r.M = M; r.N = N; r.K = K; r.batch = batch;
+    r.M = M; r.N = N; r.K = K; r.batch = batch; r.shared = shared;
     snprintf(r.kernel, sizeof(r.kernel), "%s", t_kernel);
 }
 
@@ -281,7 +281,8 @@ hipError_t run_small_bwd(const MatOp& data, const MatOp* grad, const SmallSums* 
     for (int i = 0; i < 2; ++i)
         if (logged[i] >= 0) {
             (void)hipEventRecord(ev1[i], st);
-            log_end(logged[i], ops[i]->role, ops[i]->gather, ops[i]->epilogue, 1, ops[i]->M, ops[i]->N, ops[i]->K, 1);
+            const MatOp& op = *ops[i];
+            log_end(logged[i], op.role, op.gather, op.epilogue, op.splits > 1 && op.partial ? op.splits : 1, op.M, op.N, op.K, 1, i == 1);
         }
     if (e != hipSuccess || !f32 || data.epilogue == EPI_NONE) return e;
     return apply_epilogue(data, st);      // (fp32 engines do not fuse it)

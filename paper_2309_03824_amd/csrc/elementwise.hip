@@ -3,6 +3,7 @@
 #include <algorithm>
 
 #include "lrd_internal.hpp"
+#include "lrd_measure.h"
 
 namespace lrd {
 namespace {
@@ -524,6 +525,8 @@ hipError_t run_sums(SumQueue& q, hipStream_t st)
     if (q.n == 0) return hipSuccess;
     SumArgs a{};
     uint32_t blocks = 0;
+    int64_t results = 0;
+    int most = 0;
     for (int i = 0; i < SumQueue::MOST; ++i) {
         a.first_block[i] = i < q.n ? blocks : 0xffffffffu;
         if (i >= q.n) continue;
@@ -533,10 +536,21 @@ hipError_t run_sums(SumQueue& q, hipStream_t st)
                      SgdArgs{s.sgd.w, s.sgd.m, s.sgd.copy, s.sgd.copy_bf16 ? 1 : 0, s.sgd.lr, s.sgd.mu, s.sgd.wd},
                      CropArgs{s.crop.dst, (int)s.crop.rows, (int)s.crop.inner, (int)s.crop.inner_keep}};
         blocks += (uint32_t)ceil_div(s.M * s.N / 4, 256 / lanes);
+        results += s.M * s.N;
+        most = std::max(most, s.splits);
+    }
+    hipEvent_t ev0 = nullptr, ev1 = nullptr;
+    const int logged = log_begin(&ev0, &ev1);
+    if (logged >= 0) (void)hipEventRecord(ev0, st);
+    note_kernel("sums_kernel");
+    hipLaunchKernelGGL(sums_kernel, dim3(blocks), dim3(256), 0, st, a);
+    const hipError_t e = hipGetLastError();
+    if (logged >= 0) {
+        (void)hipEventRecord(ev1, st);
+        log_end(logged, LRD_ROLE_SUMS, 0, 0, most, results, 1, 1, q.n);
     }
     q.n = 0;
-    hipLaunchKernelGGL(sums_kernel, dim3(blocks), dim3(256), 0, st, a);
-    return hipGetLastError();
+    return e;
 }
 
 hipError_t reduce_partials(const float* partial, void* C, bool c_bf16, int64_t ldc, int64_t M, int64_t N, int splits,

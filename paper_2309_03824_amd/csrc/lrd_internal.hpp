@@ -160,7 +160,7 @@ hipError_t mfma_chain(const ChainOp& op, hipStream_t st);
 // next record, or returns a negative index when logging is off or the events have run out; log_end
 // fills the record.  note_kernel is called by a launcher with the name of the kernel it launched.
 int log_begin(hipEvent_t* start, hipEvent_t* stop);
-void log_end(int index, int role, int gather, int epilogue, int splits, int64_t M, int64_t N, int64_t K, int64_t batch = 1);
+void log_end(int index, int role, int gather, int epilogue, int splits, int64_t M, int64_t N, int64_t K, int64_t batch = 1, bool shared = false);
 void note_kernel(const char* name);
 
 // Elementwise / reductions.
