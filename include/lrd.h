@@ -142,7 +142,9 @@ lrd_status lrd_select_rank(const double* times, int32_t r_min, int32_t r_max, do
  * ---------------------------------------------------------------------------------------- */
 
 /* Bytes of workspace lrd_linear_fwd / lrd_linear_bwd need for these sizes (upper bound over
- * every nullable-argument combination and every token count up to T).  0 on bad arguments. */
+ * every nullable-argument combination and every token count up to T).  What a query for one
+ * freeze_mask returns serves every other; the one of the call leaves room for what the call can use
+ * besides.  0 on bad arguments. */
 size_t lrd_linear_workspace_bytes(int64_t T, int64_t in, int64_t out, int64_t r, lrd_dtype dt,
                                   uint32_t freeze_mask);
 

@@ -201,21 +201,26 @@ int32_t lrd_set_fusion(int32_t mode)
 
 // ------------------------------------------------------------------------------------ linear
 namespace {
-size_t linear_bytes(int64_t T, int64_t in, int64_t out, int64_t r, lrd_dtype dt, Tokens tokens)
+// Room for dV's slices beside dU's, so that one launch sums both: where both are sliced, in bf16 (the fp32 engines sum at once).
+size_t linear_own_bytes(int64_t T, int64_t in, int64_t out, int64_t r, lrd_dtype dt, uint32_t freeze_mask)
+{
+    if (dt != LRD_BF16 || (freeze_mask & (LRD_FREEZE_L0 | LRD_FREEZE_L1)) || !partial_bytes(out, r, T)) return 0;
+    return partial_bytes(r, in, T);
+}
+size_t linear_bytes(int64_t T, int64_t in, int64_t out, int64_t r, lrd_dtype dt, uint32_t freeze_mask, Tokens tokens)
 {
     if (!dtype_ok(dt) || !linear_dims_ok(T, in, out, r)) return 0;
     if (pads_rank(in, out, r, dt)) {
         const size_t r8 = (size_t)pad8(r);
         size_t pads = round256((size_t)out * r8 * 2) + round256(r8 * (size_t)in * 2) + round256((size_t)T * r8 * 2) +
                       round256((size_t)out * r8 * 4) + round256(r8 * (size_t)in * 4);
-        return pads + linear_bytes(T, in, out, (int64_t)r8, dt, tokens);
+        return pads + linear_bytes(T, in, out, (int64_t)r8, dt, freeze_mask, tokens);
     }
     size_t act = round256((size_t)T * (size_t)r * esize(dt));
     // forward: H when not side-stored; backward: dH and a recomputed H; both: one split-K region
     size_t fwd = act + linear_partial_region(T, in, out, r, dt, false, tokens);
     size_t bwd = 2 * act + linear_partial_region(T, in, out, r, dt, true, tokens);
-    // a size query: room for dV's slices beside dU's, so that one launch sums both (a smaller workspace serves too)
-    if (tokens == UP_TO) bwd += partial_bytes(r, in, T);
+    if (tokens == UP_TO) bwd += linear_own_bytes(T, in, out, r, dt, freeze_mask);      // (a smaller workspace serves too)
     return std::max(fwd, bwd);
 }
 }  // namespace
@@ -223,8 +228,7 @@ size_t linear_bytes(int64_t T, int64_t in, int64_t out, int64_t r, lrd_dtype dt,
 size_t lrd_linear_workspace_bytes(int64_t T, int64_t in, int64_t out, int64_t r, lrd_dtype dt,
                                   uint32_t freeze_mask)
 {
-    (void)freeze_mask;
-    return linear_bytes(T, in, out, r, dt, UP_TO);
+    return linear_bytes(T, in, out, r, dt, freeze_mask, UP_TO);
 }
 
 lrd_status lrd_linear_fwd(const void* X, const void* V, const void* U, const float* bias, void* Y,
@@ -387,10 +391,9 @@ lrd_status linear_bwd_impl(const void* dY, const void* X, const void* H, const v
     // too, dV's slices need a region of their own for that
     SumQueue later;
     const size_t base_used = cv.used;      // the same in every workspace that the call accepts
-    const size_t own = train_u && wu.splits > 1 && train_v && wv.splits > 1 ? partial_bytes(r, in, T) : 0;
+    const size_t own = linear_own_bytes(T, in, out, r, dt, freeze_mask);
     if (own && cv.room(own)) wv.partial = (float*)cv.take(own);
-    const bool apart = !own || wv.partial != wu.partial;
-    if (apart) wu.later = &later;
+    if (!train_u || !train_v || wv.partial != wu.partial) wu.later = &later;
     wv.later = &later;
 
     MatOp d1, d2;
@@ -506,8 +509,7 @@ void* scratch_on_current_device()
 
 int32_t lrd_linear_bwd_static_fits(int64_t T, int64_t in, int64_t out, int64_t r, lrd_dtype dt, uint32_t freeze_mask)
 {
-    (void)freeze_mask;
-    const size_t need = linear_bytes(T, in, out, r, dt, THESE);
+    const size_t need = linear_bytes(T, in, out, r, dt, freeze_mask, THESE);
     if (!dtype_ok(dt) || !linear_dims_ok(T, in, out, r)) return 0;
     return need <= LRD_STATIC_SCRATCH_BYTES ? 1 : 0;
 }
@@ -928,9 +930,19 @@ inline TuckerPads tucker_pads(const lrd_conv_geom& g)
     return t;
 }
 
+// Room for the slices of the 1x1 layers' gradients beside one another's and the core's, which has the shared region: one launch then
+// sums all that are trained, in bf16 (the fp32 engines sum at once).
+struct TuckerOwn { size_t p2, p1; };
+inline TuckerOwn tucker_own(const lrd_conv_geom& g, int64_t pin, int64_t pout, lrd_dtype dt, uint32_t freeze_mask)
+{
+    if (dt != LRD_BF16) return {0, 0};
+    const bool core = !(freeze_mask & LRD_FREEZE_L1);
+    const size_t p2 = freeze_mask & LRD_FREEZE_L2 ? 0 : partial_bytes(g.S, g.r2, pout), p1 = freeze_mask & LRD_FREEZE_L0 ? 0 : partial_bytes(g.r1, g.C, pin);
+    return {core ? p2 : 0, core || p2 ? p1 : 0};
+}
+
 size_t lrd_tucker_conv_workspace_bytes(const lrd_conv_geom* g, lrd_dtype dt, uint32_t freeze_mask)
 {
-    (void)freeze_mask;
     if (!dtype_ok(dt) || !geom_ok(g, true)) return 0;
     if (pads_tucker(*g, dt)) {
         TuckerPads t = tucker_pads(*g);
@@ -943,8 +955,8 @@ size_t lrd_tucker_conv_workspace_bytes(const lrd_conv_geom* g, lrd_dtype dt, uin
     size_t part = std::max(std::max(partial_bytes(g->S, g->r2, pout), partial_bytes(g->r2, kk * g->r1, pout)),
                            partial_bytes(g->r1, g->C, pin));
     part = std::max(part, round256(conv_direct_wgrad_bytes_up_to(cs, dt == LRD_BF16)));
-    // room for the 1x1 layers' slices beside the core's, so that one launch sums all (a smaller workspace serves too)
-    part += partial_bytes(g->S, g->r2, pout) + partial_bytes(g->r1, g->C, pin);
+    const TuckerOwn own = tucker_own(*g, (int64_t)pin, (int64_t)pout, dt, freeze_mask);      // (a smaller workspace serves too)
+    part += own.p2 + own.p1;
     // forward: A and B when not side-stored; backward: dA, dB, recomputed A and B, partials, and the
     // flipped core weights of a stride-1 data gradient
     return 2 * (a + b) + part + round256(conv_dgrad_flip_bytes(cs, dt == LRD_BF16));
@@ -1101,16 +1113,13 @@ lrd_status tucker_bwd_impl(const void* dY, const void* X, const void* A, const v
         wg.scratch_bytes = shared_bytes;
     }
     if (t1) splits_for(w1);
-    // the sums over their slices in one launch at the end, each with a region of its own (all or none: a workspace without that
-    // room has them one after the other in the shared one)
+    // the sums over their slices in one launch at the end (all or none: a workspace without the room has them one after the other)
     SumQueue later;
-    {
-        const size_t own2 = t2 && w2.splits > 1 ? partial_bytes(S, r2, pout) : 0, own1 = t1 && w1.splits > 1 ? partial_bytes(r1, C, pin) : 0;
-        if (cv.room(own2 + own1)) {
-            if (own2) w2.partial = (float*)cv.take(own2);
-            if (own1) w1.partial = (float*)cv.take(own1);
-            w2.later = wg.later = w1.later = &later;
-        }
+    const TuckerOwn own = tucker_own(*g, pin, pout, dt, freeze_mask);
+    if (cv.room(own.p2 + own.p1)) {
+        if (own.p2) w2.partial = (float*)cv.take(own.p2);
+        if (own.p1) w1.partial = (float*)cv.take(own.p1);
+        w2.later = wg.later = w1.later = &later;
     }
 
     if (need_dB) LRD_TRY(run_matop(nn(dY, S, P2, r2, dB, r2, pout, r2, S, dt), st));

@@ -36,6 +36,42 @@ def test_convolution_queries_never_fall(hw, C, S, r1, r2, stride, dt):
 
 
 @pytest.mark.parametrize("n_in,n_out,r", SHAPES)
+def test_linear_queries_ask_for_a_second_set_of_slices_only_where_two_gradients_use_it(n_in, n_out, r):
+    def query(T, dt, mask):
+        return lrd.linear_workspace_bytes(T, n_in, n_out, r, dt, mask)
+
+    for T in (100, 511, 513, 4100, 16384):
+        # fp32 sums at once; a frozen factor has no slices
+        assert len({query(T, lrd.F32, mask) for mask in range(4)}) == 1
+        assert len({query(T, lrd.BF16, mask) for mask in (1, 2, 3)}) == 1
+        extra = query(T, lrd.BF16, 0) - query(T, lrd.BF16, 3)
+        rank = r if r % 8 == 0 else (r + 7) // 8 * 8
+        assert extra % (rank * n_in * 4) < 256 and (extra == 0 or T >= 512), (T, extra)
+        assert extra > 0 or T < 512 or n_out * r > 4 << 20, T      # (the largest gradients are never cut)
+        for mask in range(4):
+            sgd = lrd.linear_sgd_workspace_bytes(T, n_in, n_out, r, lrd.BF16, mask)
+            assert sgd - query(T, lrd.BF16, mask) == sgd_extra(n_in, n_out, r)
+
+
+def sgd_extra(n_in, n_out, r):
+    return sum((n * 4 + 255) // 256 * 256 for n in (n_out * r, r * n_in))
+
+
+def test_convolution_queries_ask_for_slices_of_their_own_only_where_they_are_summed_together():
+    geo = lrd.conv_geom(128, 14, 14, 256, 256, 128, 128, 3, 1, 1)
+
+    def query(mask, dt=lrd.BF16):
+        return lrd.tucker_conv_workspace_bytes(geo, dt, mask)
+
+    assert len({query(mask, lrd.F32) for mask in range(8)}) == 1
+    alone = query(7)
+    assert query(5) == query(6) == query(3) == alone        # one layer trained
+    first, last = query(4) - alone, query(1) - alone        # with the core
+    assert first > 0 and last > 0 and query(0) - alone == first + last
+    assert query(2) - alone == first                        # the 1x1 layers: one of them has the shared region
+
+
+@pytest.mark.parametrize("n_in,n_out,r", SHAPES)
 def test_a_query_within_the_static_scratch_fits_it(n_in, n_out, r):
     for T in range(1, 9000, 61):
         need = lrd.linear_workspace_bytes(T, n_in, n_out, r, lrd.BF16, 0)
