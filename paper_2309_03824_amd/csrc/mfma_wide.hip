@@ -17,6 +17,7 @@
 
 #include "lds_load.hpp"
 #include "lrd_internal.hpp"
+#include "wide_plan.hpp"
 
 namespace lrd {
 namespace {
@@ -239,14 +240,8 @@ hipError_t launch(const MatOp& op, hipStream_t st)
     g.a_bs = op.a_bs; g.b_bs = op.b_bs; g.c_bs = op.c_bs; g.aux_bs = op.aux_bs; g.bias_bs = op.bias_bs;
     g.M = (int)op.M; g.N = (int)op.N; g.K = (int)op.K;
     g.row_blocks = (int)ceil_div(op.M, ROWS * NW);
-    // chunks per workgroup: rounds of workgroups times what one takes, a chunk and a half of it before the first result leaves
     const int all = (int)(op.N / COLS);
-    double least = 1e30;
-    for (int n = 1; n <= all; ++n) {
-        const int64_t wgs = (int64_t)g.row_blocks * ceil_div(all, n) * op.batch;
-        const double cost = (double)ceil_div(wgs, 256 * PER_CU) * (n + 1.5);
-        if (cost < least) { least = cost; g.chunks = n; }
-    }
+    g.chunks = wide_chunks((int64_t)g.row_blocks * op.batch, all, 256 * PER_CU);
     g.ranges = (int)ceil_div(all, g.chunks);
     hipLaunchKernelGGL(kern, dim3((unsigned)((int64_t)g.row_blocks * g.ranges * op.batch)), dim3(64 * NW), lds_bytes, st, g);
     return hipGetLastError();
