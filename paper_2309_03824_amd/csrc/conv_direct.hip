@@ -365,22 +365,13 @@ inline Tiling tiling(int N, int Ho, int Wo)
     return t;
 }
 
-template <class K>
-hipError_t allow_lds(K kern, int lds, bool* done)
-{
-    if (*done) return hipSuccess;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    *done = e == hipSuccess;
-    return e;
-}
-
 template <int CI, int CO, bool WT>
 hipError_t launch_conv(const bf16_t* in, const bf16_t* w, bf16_t* out, int N, int Hi, int Wi, int Ho, int Wo, int pad, hipStream_t st)
 {
     constexpr int lds = conv_lds_bytes<CI, CO, WT>();
     auto kern = conv3x3_direct_kernel<CI, CO, WT>;
-    static bool allowed = false;
-    hipError_t e = allow_lds(kern, lds, &allowed);
+    static OncePerDevice allowed;
+    hipError_t e = allow_lds(kern, lds, allowed);
     if (e != hipSuccess) return e;
     const Tiling t = tiling(N, Ho, Wo);
     // about as many workgroups as fit on the chip at once (LDS decides), each with a run of tiles
@@ -400,8 +391,8 @@ hipError_t launch_wgrad(const bf16_t* x, const bf16_t* dy, float* partial, int N
 {
     constexpr int lds = wgrad_lds_for(CI, CO);
     auto kern = conv3x3_wgrad_direct_kernel<CI, CO>;
-    static bool allowed = false;
-    hipError_t e = allow_lds(kern, lds, &allowed);
+    static OncePerDevice allowed;
+    hipError_t e = allow_lds(kern, lds, allowed);
     if (e != hipSuccess) return e;
     const Tiling t = tiling(N, Ho, Wo);
     const int tiles_per_wg = wgrad_tiles_per_wg(t.ntiles);

@@ -5,8 +5,19 @@
 #include <stdint.h>
 
 #include "lrd_device.hpp"
+#include "once_per_device.hpp"
 
 namespace lrd {
+
+// Leave for a kernel to take `bytes` of dynamic LDS on the current device (more than 64 KB is refused without).
+template <class Kernel>
+hipError_t allow_lds(Kernel kernel, int bytes, OncePerDevice& allowed)
+{
+    int device = 0;
+    const hipError_t e = hipGetDevice(&device);
+    if (e != hipSuccess) return e;
+    return allowed(device, [&] { return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes); });
+}
 
 enum Gather : int {
     GATHER_NONE = 0,

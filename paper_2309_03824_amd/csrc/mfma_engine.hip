@@ -444,25 +444,14 @@ bool make_src(const void* p, int64_t s_row, int64_t s_k, int64_t rows, int64_t K
     return false;
 }
 
-template <class K>
-hipError_t allow_lds(K kernel, int bytes)
-{
-    if (bytes <= 48 * 1024) return hipSuccess;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-}
-
 template <int BM, int BN, bool A_KM, bool B_KM, class OutT>
 hipError_t launch_gemm(const MatOp& op, const Src& A, const Src& B, hipStream_t st)
 {
     constexpr int lds_bytes = 2 * (BM + BN) * LDK * 2;
     auto kern = gemm_kernel<BM, BN, A_KM, B_KM, OutT>;
-    static bool lds_allowed = false;   // per instantiation; setting it twice is harmless
-    hipError_t e = hipSuccess;
-    if (!lds_allowed) {
-        e = allow_lds(kern, lds_bytes);
-        if (e != hipSuccess) return e;
-        lds_allowed = true;
-    }
+    static OncePerDevice lds_allowed;
+    hipError_t e = allow_lds(kern, lds_bytes, lds_allowed);
+    if (e != hipSuccess) return e;
     int splits = (op.splits > 1 && op.partial) ? op.splits : 1;
     int kps = (int)(ceil_div(ceil_div(op.K, splits), BK) * BK);
     splits = (int)ceil_div(op.K, kps);
@@ -535,13 +524,9 @@ hipError_t launch_chain(const ChainOp& op, const Src& A, const Src& B1, const Sr
 {
     constexpr int lds_bytes = chain_lds_bytes<BM, RP>();
     auto kern = chain_kernel<BM, RP, B1_KM, B2_KM>;
-    static bool lds_allowed = false;
-    hipError_t e = hipSuccess;
-    if (!lds_allowed) {
-        e = allow_lds(kern, lds_bytes);
-        if (e != hipSuccess) return e;
-        lds_allowed = true;
-    }
+    static OncePerDevice lds_allowed;
+    hipError_t e = allow_lds(kern, lds_bytes, lds_allowed);
+    if (e != hipSuccess) return e;
     int cvec = pow2_vec((uintptr_t)op.C, op.ldc, op.N2, 2);
     int midvec = op.mid_save ? pow2_vec((uintptr_t)op.mid_save, op.ldmid, op.R, 2) : 1;
     dim3 grid((unsigned)ceil_div(op.M, BM));

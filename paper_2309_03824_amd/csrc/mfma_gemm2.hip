@@ -745,13 +745,9 @@ hipError_t launch_epi(const MatOp& op, const Operand& A, const Operand& B, hipSt
     constexpr int lds_bytes = gemm2_lds_bytes<BM, BN, STAGES, OutT>();
     static_assert(lds_bytes <= 160 * 1024, "LDS of a compute unit");
     auto kern = gemm2_kernel<BM, BN, WGM, WGN, STAGES, A_KM, B_KM, OutT, G, EPI>;
-    static bool lds_allowed = false;
-    if (!lds_allowed) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           lds_bytes);
-        if (e != hipSuccess) return e;
-        lds_allowed = true;
-    }
+    static OncePerDevice lds_allowed;
+    hipError_t e = allow_lds(kern, lds_bytes, lds_allowed);
+    if (e != hipSuccess) return e;
     static const std::string tag = [] {
         char b[64];
         snprintf(b, sizeof(b), "gemm2_kernel<%d,%d,%d,%d,%d,%s,%s,%s%s%s>", BM, BN, WGM, WGN, STAGES, A_KM ? "A_KM" : "A_KC", B_KM ? "B_KM" : "B_KC",
@@ -772,7 +768,7 @@ hipError_t launch_epi(const MatOp& op, const Operand& A, const Operand& B, hipSt
     if (G == GATHER_CONV_DGRAD && op.cs.cls) grid.z = (unsigned)(op.cs.stride * op.cs.stride);   // one slab of workgroups per parity class
     hipLaunchKernelGGL(kern, grid, dim3(NT), lds_bytes, st, A, B, op.cs, (OutT*)op.C, op.ldc, op.bias, partial, (int)op.M,
                        (int)op.N, (int)op.K, kps, (bf16_t*)op.aux, op.ldaux, bt);
-    hipError_t e = hipGetLastError();
+    e = hipGetLastError();
     if (e != hipSuccess) return e;
     // a batch of sliced products is summed as one matrix of batch * M rows (supported() admits only dense results)
     if (splits > 1) {

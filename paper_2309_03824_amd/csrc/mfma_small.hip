@@ -506,19 +506,10 @@ bool alone_ok(const MatOp& op)
 // LDS for each of the workgroups that share a unit (two for up to two rounds of single ones).
 inline int lds_limit(int64_t blocks) { return blocks <= 256 ? 160 * 1024 : 80 * 1024; }
 
-template <class Kernel>
-hipError_t allow_lds(Kernel kern, int bytes, bool& done)
-{
-    if (done) return hipSuccess;
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    done = e == hipSuccess;
-    return e;
-}
-
 template <int NB>
 hipError_t launch_fwd(const MatOp& op, const Cut& c, hipStream_t st)
 {
-    static bool allowed = false;
+    static OncePerDevice allowed;
     typedef ActShape<NB> S;
     const hipError_t e = allow_lds(small_fwd_kernel<NB>, S::RING * S::G * S::STEP, allowed);
     if (e != hipSuccess) return e;
@@ -534,7 +525,7 @@ hipError_t launch_bwd(ActJob d, GradJob w, const SumJob& s, hipStream_t st)
 {
     typedef ActShape<NB> S;
     constexpr int most = std::max(S::RING * S::G * S::STEP, GRAD_RING * GRAD_G * GRAD_STEP);
-    static bool allowed = false;
+    static OncePerDevice allowed;
     const hipError_t e = allow_lds(small_bwd_kernel<NB>, most, allowed);
     if (e != hipSuccess) return e;
     int lds = s.blocks ? 2 * 8 * 32 * 9 * 4 : 0;

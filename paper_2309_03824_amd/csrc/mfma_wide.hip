@@ -221,12 +221,9 @@ hipError_t launch(const MatOp& op, hipStream_t st)
     constexpr int lds_bytes = 2 * KS * SUB + NW * 2048;
     static_assert(PER_CU * lds_bytes <= 160 * 1024, "LDS of a compute unit");
     auto kern = wide_kernel<KS, NW, B_KM, EPI>;
-    static bool lds_allowed = false;
-    if (!lds_allowed) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
-        if (e != hipSuccess) return e;
-        lds_allowed = true;
-    }
+    static OncePerDevice lds_allowed;
+    const hipError_t e = allow_lds(kern, lds_bytes, lds_allowed);
+    if (e != hipSuccess) return e;
     static const std::string tag = [] {
         char b[64];
         snprintf(b, sizeof(b), "wide_kernel<%d,%d,%s%s>", KS * 64, NW, B_KM ? "B_KM" : "B_KC",
