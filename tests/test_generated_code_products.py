@@ -29,6 +29,12 @@ def test_descriptors_are_settled(kernels):
     assert not {k: [hex(a) for a in rules.faults(rows)] for k, rows in kernels.items() if rules.faults(rows)}
 
 
+def test_m0_belongs_to_the_loads(kernels):
+    # (the loads stand in loops: a few places in each kernel)
+    loads = [sum(op.startswith("buffer_load") and args.endswith(" lds") for _, op, args, _ in rows) for rows in kernels.values()]
+    assert min(loads) > 0 and rules.m0_writes(kernels) == sum(loads)
+
+
 def test_nothing_is_spilled(kernels):
     assert not [k for k, rows in kernels.items() if any(op.startswith("scratch_") for _, op, _, _ in rows)]
 
