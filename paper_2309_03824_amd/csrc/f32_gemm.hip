@@ -75,6 +75,9 @@ struct F32Frag {
     }
 };
 
+// Floats of LDS for the sums of `waves` blocks of 16 T x 16 T.
+constexpr int f32_lds(int T, int waves) { return waves * 16 * T * (16 * T + 4); }
+
 // Tile of E WM x E WN results, E = 16 T; KS waves share each E x E block, wave s of them taking steps s, s + KS, ...
 template <int T, int WM, int WN, int KS, int DEPTH, bool AKM, bool BKM>
 __global__ __launch_bounds__(64 * WM * WN * KS) void f32_gemm_kernel(F32Operand A, F32Operand B, float* __restrict__ C, int64_t ldc,
@@ -82,6 +85,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS) void f32_gemm_kernel(F32Operand 
                                                                      int N, int k_per_split)
 {
     const unsigned bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
+    __shared__ __align__(16) float lds[f32_lds(T, WM * WN * KS)];
 #include "f32_tile.inc"
 }
 
@@ -95,23 +99,26 @@ struct F32Job {
 // The same tile with all of K, as one of the jobs of a launch.
 template <int T, bool AKM>
 __device__ __forceinline__ void f32_job_tile(const F32Operand& A, const F32Operand& B, float* C, int64_t ldc, const float* bias, int M, int N, int k_per_split,
-                                             unsigned bx, unsigned by)
+                                             unsigned bx, unsigned by, float* lds_of_launch)
 {
     constexpr int WM = 1, WN = 1, KS = 8, DEPTH = T == 1 ? 8 : 4;
     constexpr bool BKM = true;
     constexpr unsigned bz = 0;
     constexpr float* partial = nullptr;
+    float& lds = *lds_of_launch;
 #include "f32_tile.inc"
 }
 
 // A data gradient and a weight gradient that do not wait for one another, in one launch: with few tokens neither fills the chip
 // and 2.5 us of each is the launch (256 x 768 x 768 layer at rank 208, first factor frozen: a pass 23.2 -> 20.6 us).
+// Both tiles sum in one buffer, the larger of the two's: an array of each, side by side, was 72 KB with 32 x 32 blocks of both.
 template <int TD, int TW>
 __global__ __launch_bounds__(512) void f32_pair_kernel(F32Job d, int d_rows, int d_blocks, F32Job w, int w_rows)
 {
+    __shared__ __align__(16) float lds[f32_lds(TD > TW ? TD : TW, 8)];
     const int block = blockIdx.x - d_blocks;
-    if (block < 0) f32_job_tile<TD, false>(d.A, d.B, d.C, d.ldc, d.bias, d.M, d.N, d.K, blockIdx.x % d_rows, blockIdx.x / d_rows);
-    else f32_job_tile<TW, true>(w.A, w.B, w.C, w.ldc, w.bias, w.M, w.N, w.K, block % w_rows, block / w_rows);
+    if (block < 0) f32_job_tile<TD, false>(d.A, d.B, d.C, d.ldc, d.bias, d.M, d.N, d.K, blockIdx.x % d_rows, blockIdx.x / d_rows, lds);
+    else f32_job_tile<TW, true>(w.A, w.B, w.C, w.ldc, w.bias, w.M, w.N, w.K, block % w_rows, block / w_rows, lds);
 }
 
 F32Job f32_job(const MatOp& op)
@@ -193,11 +200,11 @@ bool f32_pair_supported(const MatOp& data, const MatOp& grad)
 
 hipError_t f32_pair(const MatOp& data, const MatOp& grad, hipStream_t st)
 {
-    note_kernel("f32_pair_kernel");
     const F32Job d = f32_job(data), w = f32_job(grad);
     const int td = f32_plan(data).t, tw = f32_plan(grad).t;
     const int dr = (int)ceil_div(data.M, 16 * td), db = dr * (int)ceil_div(data.N, 16 * td), wr = (int)ceil_div(grad.M, 16 * tw);
     const dim3 grid((unsigned)(db + wr * (int)ceil_div(grad.N, 16 * tw))), block(512);
+    note_kernel(td == 1 ? tw == 1 ? "f32_pair_kernel<1,1>" : "f32_pair_kernel<1,2>" : tw == 1 ? "f32_pair_kernel<2,1>" : "f32_pair_kernel<2,2>");
     if (td == 1 && tw == 1) hipLaunchKernelGGL((f32_pair_kernel<1, 1>), grid, block, 0, st, d, dr, db, w, wr);
     else if (td == 1) hipLaunchKernelGGL((f32_pair_kernel<1, 2>), grid, block, 0, st, d, dr, db, w, wr);
     else if (tw == 1) hipLaunchKernelGGL((f32_pair_kernel<2, 1>), grid, block, 0, st, d, dr, db, w, wr);
