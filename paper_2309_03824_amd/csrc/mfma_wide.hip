@@ -37,6 +37,7 @@ struct WideArgs {
     int64_t a_bs, b_bs, c_bs, aux_bs, bias_bs;
     int M, N, K;
     int row_blocks, ranges, chunks;  // a workgroup: 32 rows per wave x `chunks` chunks, the last of `ranges` with what is left
+    int by_columns;                  // row blocks of a range follow one another, and not the ranges of a row block
 };
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t descriptor(const char* base, uint32_t span)
@@ -53,13 +54,17 @@ __global__ __launch_bounds__(64 * NW, 2) void wide_kernel(WideArgs g)
     static_assert(PER * NW == 8, "whole loads");
     extern __shared__ __align__(16) unsigned char smem[];
     const int lane = threadIdx.x & 63, wave = (int)uni(threadIdx.x >> 6);
-    // Workgroups go to the 8 dies in turn: each die takes a run of row blocks, whose column ranges follow one another.
+    // Workgroups go to the 8 dies in turn: each die takes a run of row blocks, whose column ranges follow one another, so that its
+    // L2 fetches a few rows of A and all of B; or, by columns, a few columns of B and all of A.
     const uint32_t total = gridDim.x, f = blockIdx.x, die = f & 7u, per = total >> 3, more = total & 7u;
     uint32_t t = die * per + min(die, more) + (f >> 3);
-    const int range = (int)(t % (uint32_t)g.ranges);
-    t /= (uint32_t)g.ranges;
-    const int64_t z = t / (uint32_t)g.row_blocks;
-    const int64_t row0 = (int64_t)(t % (uint32_t)g.row_blocks) * (ROWS * NW) + wave * ROWS;
+    const uint32_t inner = g.by_columns ? (uint32_t)g.row_blocks : (uint32_t)g.ranges, outer = g.by_columns ? (uint32_t)g.ranges : (uint32_t)g.row_blocks;
+    const uint32_t at_inner = t % inner;
+    t /= inner;
+    const uint32_t at_outer = t % outer;
+    const int64_t z = t / outer;
+    const int range = (int)(g.by_columns ? at_outer : at_inner);
+    const int64_t row0 = (int64_t)(g.by_columns ? at_inner : at_outer) * (ROWS * NW) + wave * ROWS;
     const int rows = (int)max((int64_t)0, min((int64_t)g.M - row0, (int64_t)ROWS));     // of this wave
     const int first = range * g.chunks, n_chunks = min(g.chunks, g.N / COLS - first);
 
@@ -238,6 +243,10 @@ hipError_t launch(const MatOp& op, hipStream_t st)
     g.M = (int)op.M; g.N = (int)op.N; g.K = (int)op.K;
     g.row_blocks = (int)ceil_div(op.M, ROWS * NW);
     const int all = (int)(op.N / COLS);
+    // By rows each die fetches all of B: slower than tiles once that is the larger part (1024 x 32000 x 256 33.6 us in tiles, 38.9
+    // by rows, 27.9 by columns; 4096 x 50304 x 256 171, 139, 119 us).  A square-ish result is the better written by rows, where
+    // a die's stores run along them (8192 x 16384 x 320 142 us in tiles, 99 by rows, 134 by columns); at 4 M columns both are even.
+    g.by_columns = op.N > 6 * op.M;
     g.chunks = wide_chunks((int64_t)g.row_blocks * op.batch, all, 256 * PER_CU);
     g.ranges = (int)ceil_div(all, g.chunks);
     hipLaunchKernelGGL(kern, dim3((unsigned)((int64_t)g.row_blocks * g.ranges * op.batch)), dim3(64 * NW), lds_bytes, st, g);
@@ -271,6 +280,14 @@ bool mfma_wide_supported(const MatOp& op)
     if (!mfma_gemm2_supported(op) || op.gather != GATHER_NONE || op.out_f32 || op.splits > 1 || op.a_sk != 1) return false;
     if (op.N % COLS != 0 || op.N < 24 * COLS || op.K > 512) return false;
     if (op.M * op.N * op.batch < (op.K <= 256 ? 12000000 : 32000000)) return false;
+    // Rows of the last row block that do not exist cost what others do: not where they are more than a third of all (300 x 128256 x 320
+    // with GELU 55.5 us in tiles, 62.2 here, a block of 256 rows and one of 44; 48 x 262144 x 256 37.0 against 39.8).
+    const int64_t block = ROWS * (op.K <= 256 ? 4 : 8);
+    if (3 * op.M < 2 * block * ceil_div(op.M, block)) return false;
+    // The shortest reductions over the widest results, too, are faster in tiles, which store 256 bytes of a row and not 128 (1024 x
+    // 32000 x 64 with GELU 30.8 against 37.6 us, x 128 33.8 against 38.5; 2000 x 32000 x 128 with its gradient 64.1 against 69.9, plain
+    // 41.1 -> 37.4 here).
+    if (op.N > 24000 && (op.K <= 64 || (op.K <= 128 && (op.M <= 1024 || op.epilogue != EPI_NONE)))) return false;
     if (op.epilogue == EPI_ACT_STORE && op.b_sk != 1) return false;       // no layer pass has these two
     if (op.epilogue == EPI_ACT_GRAD && op.b_sk == 1) return false;
     if (op.M >= (int64_t(1) << 30) || op.ldc > BUF_MAX_LD || (op.epilogue != EPI_NONE && op.ldaux > BUF_MAX_LD)) return false;

@@ -41,7 +41,9 @@ def logged(call, *args):
 SHAPES = [((7873, 64, 1536, 8), "64,4"), ((5000, 128, 2560, 64), "64,4"), ((6177, 128, 1984, 104), "128,4"),
           ((4100, 192, 3072, 136), "192,4"), ((8191, 256, 1536, 192), "192,4"), ((3001, 256, 4160, 256), "256,4"),
           ((10001, 512, 3264, 264), "320,8"), ((8193, 384, 4096, 376), "384,8"), ((21000, 512, 1600, 424), "448,8"),
-          ((8200, 512, 4096, 512), "512,8")]
+          ((8200, 512, 4096, 512), "512,8"),
+          # many more columns than rows: dealt to the dies by columns
+          ((1000, 256, 12544, 120), "128,4"), ((97, 256, 125056, 160), "192,4"), ((701, 512, 46080, 296), "320,8")]
 
 
 @pytest.mark.gpu
@@ -71,6 +73,19 @@ def test_wide_products(shape, depth):
     torch.cuda.synchronize()
     assert rel(plain, dH.float() @ V.float()) < 2e-3
     assert torch.equal(dX, dX2)
+
+
+# Wide results that are faster in tiles: most of the last row block would be empty, or a very short reduction
+@pytest.mark.gpu
+@pytest.mark.parametrize("T,wide,r,act", [(48, 262144, 64, False), (130, 100032, 192, False), (300, 128256, 320, False), (1100, 24064, 64, False),
+                                          (1024, 24064, 128, False), (1100, 24064, 128, True)])
+def test_not_wide(T, wide, r, act):
+    m = Maker(T + r)
+    X, U, V = m.normal(T, r), m.normal(wide, r, std=r ** -0.5), m.normal(r, r, std=r ** -0.5)
+    ws, H, Y, A = workspace(T, r, wide, r), nan(T, r), nan(T, wide), nan(T, wide) if act else None
+    args = (X, V, U, None, Y, A, H, lrd.ACT_GELU, ws) if act else (X, V, U, None, Y, H, ws)
+    assert logged(lrd.linear_fwd_act if act else lrd.linear_fwd, *args).startswith("gemm2_kernel")
+    assert rel(Y, H.float() @ U.float().t()) < 2e-3
 
 
 @pytest.mark.gpu
