@@ -36,8 +36,8 @@ struct WideArgs {
     int64_t lda, ldb, ldc, ldaux;
     int64_t a_bs, b_bs, c_bs, aux_bs, bias_bs;
     int M, N, K;
-    int row_blocks, ranges, chunks;  // a workgroup: 32 rows per wave x `chunks` chunks, the last of `ranges` with what is left
-    int by_columns;                  // row blocks of a range follow one another, and not the ranges of a row block
+    int inner, outer, chunks;        // a workgroup: 32 rows per wave x `chunks` chunks, the last range of columns with what is left
+    int by_columns;                  // row blocks (`inner` of them) of a range follow one another, and not the ranges of a row block
 };
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t descriptor(const char* base, uint32_t span)
@@ -58,13 +58,13 @@ __global__ __launch_bounds__(64 * NW, 2) void wide_kernel(WideArgs g)
     // L2 fetches a few rows of A and all of B; or, by columns, a few columns of B and all of A.
     const uint32_t total = gridDim.x, f = blockIdx.x, die = f & 7u, per = total >> 3, more = total & 7u;
     uint32_t t = die * per + min(die, more) + (f >> 3);
-    const uint32_t inner = g.by_columns ? (uint32_t)g.row_blocks : (uint32_t)g.ranges, outer = g.by_columns ? (uint32_t)g.ranges : (uint32_t)g.row_blocks;
-    const uint32_t at_inner = t % inner;
-    t /= inner;
-    const uint32_t at_outer = t % outer;
-    const int64_t z = t / outer;
-    const int range = (int)(g.by_columns ? at_outer : at_inner);
-    const int64_t row0 = (int64_t)(g.by_columns ? at_inner : at_outer) * (ROWS * NW) + wave * ROWS;
+    // (The order of two loops, chosen on the host: chosen here, the compiler loads the pointers only after these divisions, 0.7 us later.)
+    const uint32_t in = t % (uint32_t)g.inner;
+    t /= (uint32_t)g.inner;
+    const uint32_t out = t % (uint32_t)g.outer;
+    const int64_t z = t / (uint32_t)g.outer;
+    const int range = (int)(g.by_columns ? out : in);
+    const int64_t row0 = (int64_t)(g.by_columns ? in : out) * (ROWS * NW) + wave * ROWS;
     const int rows = (int)max((int64_t)0, min((int64_t)g.M - row0, (int64_t)ROWS));     // of this wave
     const int first = range * g.chunks, n_chunks = min(g.chunks, g.N / COLS - first);
 
@@ -150,6 +150,9 @@ __global__ __launch_bounds__(64 * NW, 2) void wide_kernel(WideArgs g)
     // (rows that do not exist are stored past the descriptor, so that every wave issues the stores its waits count on)
     auto place = [&](int r, int64_t ld, int col0) { return r < rows ? ((uint32_t)r * (uint32_t)ld + col0 + scol * 8) * 2u : BUF_OOB; };
 
+    // Where this loop's 5 KB of code begin counts for 3 % with the gradient of GELU: on a boundary of 128 bytes 8192 x 3072 x 192 takes
+    // 29.3 us, 16 or 48 bytes behind one 30.9; x 256 and x 128 take 40.8 and 33.3 there, 40.0 and 32.0 where the compiler puts them.
+    if constexpr (EPI == EPI_ACT_GRAD && KS == 3) asm volatile(".p2align 7");
     for (int c = 0; c < n_chunks; ++c) {
         // loads of chunk c: older than the stores of chunk c - 1
         if (c == 0) wait_vm<0>();
@@ -241,15 +244,17 @@ hipError_t launch(const MatOp& op, hipStream_t st)
     g.lda = op.a_sm; g.ldb = B_KM ? op.b_sk : op.b_sn; g.ldc = op.ldc; g.ldaux = op.ldaux;
     g.a_bs = op.a_bs; g.b_bs = op.b_bs; g.c_bs = op.c_bs; g.aux_bs = op.aux_bs; g.bias_bs = op.bias_bs;
     g.M = (int)op.M; g.N = (int)op.N; g.K = (int)op.K;
-    g.row_blocks = (int)ceil_div(op.M, ROWS * NW);
+    const int row_blocks = (int)ceil_div(op.M, ROWS * NW);
     const int all = (int)(op.N / COLS);
     // By rows each die fetches all of B: slower than tiles once that is the larger part (1024 x 32000 x 256 33.6 us in tiles, 38.9
     // by rows, 27.9 by columns; 4096 x 50304 x 256 171, 139, 119 us).  A square-ish result is the better written by rows, where
     // a die's stores run along them (8192 x 16384 x 320 142 us in tiles, 99 by rows, 134 by columns); at 4 M columns both are even.
     g.by_columns = op.N > 6 * op.M;
-    g.chunks = wide_chunks((int64_t)g.row_blocks * op.batch, all, 256 * PER_CU);
-    g.ranges = (int)ceil_div(all, g.chunks);
-    hipLaunchKernelGGL(kern, dim3((unsigned)((int64_t)g.row_blocks * g.ranges * op.batch)), dim3(64 * NW), lds_bytes, st, g);
+    g.chunks = wide_chunks((int64_t)row_blocks * op.batch, all, 256 * PER_CU);
+    const int ranges = (int)ceil_div(all, g.chunks);
+    g.inner = g.by_columns ? row_blocks : ranges;
+    g.outer = g.by_columns ? ranges : row_blocks;
+    hipLaunchKernelGGL(kern, dim3((unsigned)((int64_t)row_blocks * ranges * op.batch)), dim3(64 * NW), lds_bytes, st, g);
     return hipGetLastError();
 }
 
