@@ -190,12 +190,20 @@ hipError_t f32_gemm(const MatOp& op, hipStream_t st)
     return launch<2, 1, 1, 8, 4>(op, (int)p.splits, st);
 }
 
-// The same tiles as by themselves, in the same order of additions: whatever f32_gemm would run unsliced in 16 x 16 or 32 x 32.
+// Workgroups of a product in blocks of 16 T x 16 T.
+int64_t f32_blocks(const MatOp& op, int t) { return ceil_div(op.M, 16 * t) * ceil_div(op.N, 16 * t); }
+
+// The same tiles as by themselves, in the same order of additions: whatever f32_gemm would run unsliced in 16 x 16 or 32 x 32.  Not
+// where the gradient's tiles, the last to start, are the longer chains and more than fit beside the others (two workgroups to a unit):
+// they then run on after everything else, 2000 x 768 x 768 at rank 208 with the second factor's gradient 48.4 us apart and 52.4 together,
+// 500 x 1000 -> 384 at rank 150 with the first one's 16.8 and 19.5.
 bool f32_pair_supported(const MatOp& data, const MatOp& grad)
 {
     if (!f32_gemm_supported(data) || !f32_gemm_supported(grad) || data.a_sk != 1 || data.b_sk == 1 || grad.a_sk == 1 || grad.b_sk == 1 || grad.sgd) return false;
     const F32Plan d = f32_plan(data), w = f32_plan(grad);
-    return d.t < 4 && w.t < 4 && d.splits == 1 && w.splits == 1;
+    if (d.t == 4 || w.t == 4 || d.splits > 1 || w.splits > 1) return false;
+    const bool late = d.t == 2 && f32_blocks(data, d.t) + f32_blocks(grad, w.t) > 512 && grad.K > data.K && grad.K >= 256;
+    return !late;
 }
 
 hipError_t f32_pair(const MatOp& data, const MatOp& grad, hipStream_t st)

@@ -8,9 +8,9 @@ from paper_2309_03824_amd import binding as lrd
 pytestmark = pytest.mark.gpu
 
 
-# tokens, in, out, rank, and the blocks of dH and dU, and of dX and dV
+# tokens, in, out, rank, and the blocks of dH and dU, and of dX and dV; None: gradients that would run on after everything else, alone
 @pytest.mark.parametrize("T,n_in,n_out,r,up,down", [(33, 47, 65, 17, "1,1", "1,1"), (1001, 259, 130, 103, "2,1", "2,1"), (100, 700, 520, 301, "1,2", "1,2"),
-                                                    (500, 401, 530, 303, "2,2", "2,2"), (2, 35, 34, 2, "1,1", "1,1"), (256, 768, 768, 208, "1,2", "2,2")])
+                                                    (500, 401, 530, 303, "2,2", "2,2"), (500, 1000, 384, 150, "1,1", None), (1700, 770, 770, 209, None, None), (2, 35, 34, 2, "1,1", "1,1"), (256, 768, 768, 208, "1,2", "2,2")])
 @pytest.mark.parametrize("act", [False, True])
 def test_products_of_a_pair_have_the_bits_of_each_alone(T, n_in, n_out, r, up, down, act):
     gen = torch.Generator(device="cuda").manual_seed(T + r)
@@ -25,7 +25,9 @@ def test_products_of_a_pair_have_the_bits_of_each_alone(T, n_in, n_out, r, up, d
             torch.cuda.synchronize()
         kernels = [row["kernel"] for row in log.rows()]
         alone = ["f32_gemm_kernel"]
-        want = (alone if mask & 2 else [f"f32_pair_kernel<{up}>"] * 2) + (alone if mask & 1 else [f"f32_pair_kernel<{down}>"] * 2)
+        pair1, pair2 = up and not mask & 2, down and not mask & 1
+        want = ([f"f32_pair_kernel<{up}>"] * 2 if pair1 else alone) + ([f"f32_pair_kernel<{down}>"] * 2 if pair2 else alone)
+        want += alone * ((not mask & 2 and not pair1) + (not mask & 1 and not pair2))
         assert kernels == want, mask
         for name, t, there in (("dX", dX, True), ("dU", dU, not mask & 2), ("dV", dV, not mask & 1)):
             assert torch.equal(t, ref.setdefault(name, t)) and not t.isnan().any() if there else t.isnan().all(), (name, mask)
