@@ -404,10 +404,14 @@ __device__ __forceinline__ void store_through(void* to, u32x4 v)
 {
     asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(to), "v"(v) : "memory");
 }
-// Results up to this many elements are stored that way: they are what the next product reads at once, and it finds them there.
-// Non-temporal stores send them to memory; the encoder step's [8192 x 256] intermediates come back 0.3 us of 8.9 sooner, its step
-// 4091 -> 4065 us, the FFN stack 1842 -> 1827 us.  With larger ones the write-backs come due in the next kernel instead: with
-// [8192 x 1024] results stored so the step takes 4150 us.
+// Results up to this many elements (of each member of a batch) are stored that way: they are what the next product reads at once, and
+// it finds them there.  Non-temporal stores send them to memory; without these stores the encoder step takes 1.1 % longer (4207
+// against 4160 us), the FFN stack 0.9 %, forward of a 1024-wide layer at rank 256 25.4 against 23.5 us for 11648 tokens (3.0 M), 30.2
+// against 28.1 for 16000 (4.1 M).  With larger ones the write-backs come due in the next kernel instead: with everything
+// stored so a backward pass with nothing frozen takes 12 % longer from 12 M on (46848 tokens 174 against 196 us, at rank 192
+// 140 against 156 for 43136), and is even at 6 to 8 M, where forward passes gain up to 10 %.  Per member, because each is what one
+// product of the next launch reads: dH of three members of 8192 x 192 with their dX 25.6 -> 24.9 us, 25.7 by the batch's 4.7 M; three of 6144
+// x 256 29.1 against 30.2; encoder step 4155 against 4176 us.
 constexpr int64_t THROUGH_MOST = int64_t(1) << 22;
 
 // bf16 results of one BM x BN tile: registers -> LDS tile (row-major) -> 16 contiguous bytes per
@@ -823,13 +827,13 @@ hipError_t by_tile(const MatOp& op, const Operand& A, const Operand& B, hipStrea
         if (op.M > 64 && op.N > 64 && (wgs(128, 128) >= 200 || wgs(64, 64) > 2048)) {
             if constexpr (sizeof(OutT) == 2 && G == GATHER_NONE) {
                 // (Large results in whole chunks of 64 columns are not here: see mfma_wide_supported.)
-                // From three rounds on, 256 x 256 tiles where the multiplication weighs more (16384 x 4096 x 512: 80 us,
-                // 83 us in the next kind, 90 us in the last); else one stage and three workgroups per unit, against two
-                // stages and two of them: 4100 x 4096 x 264 22.6 -> 20.5 us, 8192 x 4096 x 256 with the GELU gradient
-                // 47.3 -> 43.8 us inside the encoder step.  Two stages stay faster below three workgroups per unit
-                // (8192 x 1024 x 256: 7.9 against 8.2 us) and up to K = 256 without that gradient's second operand to
-                // wait for (in the same step, with GELU 40.3 against 41.6 us, three members of 1024 columns 24.1
-                // against 26.3 us).
+                // From three rounds on, 256 x 256 tiles where the multiplication weighs more (with the K x K product
+                // before it, 65536 x 1024 x 512: 129 us, 145 us in the next kind, 150 us in the last; 40000 x 1480 x 400
+                // 108, 117 and 127); else one stage and three workgroups per unit, against two stages and two of
+                // them: 4100 x 4096 x 264 22.6 -> 20.5 us, 32768 x 1024 x 256 with the GELU gradient, with the
+                // product before it, 55.5 -> 52.4 us.  Two stages stay faster below three workgroups per unit (8192 x
+                // 1024 x 256: 7.9 against 8.2 us) and up to K = 256 without that gradient's second operand to wait
+                // for (three members of 1024 columns 24.1 against 26.3 us).
                 if (op.K > 6 * BK && op.M > 192 && op.N > 192 && wgs(256, 256) >= 768)
                     return launch<256, 256, 2, 4, 2, A_KM, B_KM, OutT, G>(op, A, B, st);
                 if (wgs(128, 128) > 768 && (op.K > 4 * BK || op.epilogue == EPI_ACT_GRAD))

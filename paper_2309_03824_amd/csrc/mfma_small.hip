@@ -494,7 +494,8 @@ bool act_ok(const MatOp& op)
 // 9.7 -> 8.7 us with the product after it, 48 x 512 over 2048 8.8 -> 7.9 us, 48 x 192 over 3072 8.0 against 9.0, 48 x 256 over 4096 8.7
 // against 11.3).  In 64 columns only short ones (509 x 1024 over 256 1.3 us, 600 x 512 over 1024 even).  A k-major operand of 4 MB
 // and more comes faster in the tiles' whole lines (1 x 8192 over 512 3.7 against 5.6 us, 2048 x 1008 8.1 -> 7.2 us), and so do more than 512
-// rows (1024 x 256 over 1024 5.9 against 6.5 us, 509 of them 6.1 -> 5.7).
+// rows (1024 x 256 over 1024 5.9 against 6.5 us, 509 of them 6.1 -> 5.7).  Two steps win 0.2 us of 3.2 with operands from memory and lose 0.2 of
+// 2.7 with those in the caches; from three on they win 0.5 and are even.
 bool alone_ok(const MatOp& op)
 {
     if (!act_ok(op) || (op.b_sk != 1 && (op.K * op.N >= (int64_t(1) << 21) || op.M > 512))) return false;

@@ -5,12 +5,16 @@
 // stores, against 9 us of matrix instructions.  In output tiles each workgroup is a chain load -> multiply -> store whose
 // ends nothing overlaps, and every tile loads its rows of A again.  Here a wave keeps 32 rows of A in registers, all of K, and a
 // workgroup walks along N: B goes by in chunks of 64 columns through two LDS buffers (loads straight into LDS, one chunk
-// ahead), and results leave each wave as whole 128-byte lines by way of 4 KB of LDS of its own, without a barrier.  A wave's
-// waits for a chunk never reach the stores of the chunk before: they are younger than the loads it waits for.
+// ahead), and results leave each wave as whole 128-byte lines by way of 4 KB of LDS of its own, without a barrier.  The wait
+// before a chunk leaves out the stores of the chunk before: they are younger than the loads it waits for.  (The compiler, which does not see
+// that wait, waits for A's registers between the products of every chunk, and with them for those stores and most of the next
+// chunk's loads.  Without those waits the kernel is no faster and often slower, as if they kept the workgroups of a unit apart: 8192 x 8192 x 256
+// with GELU 62.6 -> 67.6 us, 8192 x 3072 x 192 with its gradient 29.2 -> 28.8, encoder step 4105 -> 4120.)
 // v_mfma_f32_16x16x32_bf16 and not 32x32x16: with random operands the shorter form sustains more (16384 x 4096 x 512
 // 61 against 67 us).  Multiplying one chunk while the one before leaves, in a second set of accumulators, gave nothing (63 us).
 // Against output tiles: 8192 x 4096 x 256 with GELU inside the encoder step 40.4 -> 36.2 us, with its gradient 45.0 -> 38.8
-// us; 16384 x 4096 x 256 49.7 -> 36.1 us, 16384 x 4096 x 512 86.9 -> 60.9 us.
+// us; by themselves 16384 x 4096 x 256 53.4 -> 38.4 us, 16384 x 4096 x 512 87.7 -> 60.8 us, inside a layer of that size, where A has
+// just been written and the results fill the caches for the next product, 95 -> 75 and 100 -> 80 us (its data gradient).
 #include <algorithm>
 #include <cstdio>
 #include <string>
